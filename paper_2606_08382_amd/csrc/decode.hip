@@ -25,6 +25,7 @@
 //   query head (Sec. 3.3), casting to the output type.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include <type_traits>
@@ -1482,9 +1483,8 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_kernel(DecodeParams 
 // One workgroup per (query head, sequence), or two that each up-project half
 // of the output columns when the grid is small.  Merges the splits with weights
 // 2^(m_s - M), corrects the few tokens that dominate the softmax with exactly
-// recomputed scores, and applies the value up-projection of the head's KV group.
-// All loads of a phase are issued before their results are used, so each phase
-// costs about one memory round trip.
+// recomputed scores, and applies the value up-projection U_V once per query head
+// (Sec. 3.3), casting to the output type.
 //
 // Exact rescoring.  The split pass scores with fp16 rotated keys and fp16
 // dequantized latents; the relative error of a score is a few fp16 ulps, so a
@@ -1496,17 +1496,12 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_kernel(DecodeParams 
 // reconstruction, RoPE angle reduced in fp64), and their contribution to the
 // normalizer and to the merged value latent is moved from the approximate to the
 // exact weight.
-constexpr int kCombineMaxSplits = 256;  // one split per thread of the weight pass
-constexpr int kRescoreMax = 128;                       // tokens rescored per query head
-constexpr int kRescoreBatch = 32;                      // of them with key latents in LDS at once
-constexpr int kBkVecPerThread = 8;   // B_k block of up to 128 x 128 fp16: 2048 vectors / 256 threads
-// candidate entries are read in chunks of 64 splits, kCandPerThread per thread
-constexpr int kCandChunk = 64 * kCand;
-constexpr int kCandPerThread = kCandChunk / 256;
+constexpr int kCombineMaxSplits = 256;  // split weights held in LDS
+constexpr int kRescoreMax = 128;        // tokens rescored per query head
+constexpr int kCandChunk = 64;          // splits whose candidate entries are read together
 
 __device__ __forceinline__ float h2f(uint16_t u) { return (float)__builtin_bit_cast(_Float16, u); }
 
-// Dequantized key latent channel ch of head g at token t of sequence b.
 // bits of the outlier and inlier regions of a quantized cache
 __device__ __forceinline__ int region_hi_bits(int qmode) { return qmode == STARKV_Q_MIX8_4 ? 8 : 4; }
 __device__ __forceinline__ int region_lo_bits(int qmode) { return qmode == STARKV_Q_MIX4_3 ? 3 : 4; }
@@ -1520,29 +1515,44 @@ __device__ __forceinline__ int code_field(const uint8_t* w, int sh, int bits) {
   return (int)((v >> (sh % 8)) & ((1u << bits) - 1));
 }
 
-__device__ float key_latent(const CombineParams& p, int g, int b, int t, int ch) {
-  const int64_t blk = cache_row(p.rmap, b, t) / 16;
-  const int tau = t % 16, c = ch / 8, wi = ch % 8;
+// Dequantized key latent channels 8c .. 8c + 7 of head g, of token tau of the
+// 16-token block blk: one code load (three bytes at 3 bits) and one (s, z) load.
+__device__ __forceinline__ void key_chunk(const CombineParams& p, int g, int64_t blk, int tau, int c,
+                                          float (&x)[8]) {
   const uint8_t* code = p.cache + p.k_code_off[g] + blk * 16 * p.k_rb[g];
-  if (p.qmode == STARKV_Q_F16)
-    return h2f(*reinterpret_cast<const uint16_t*>(code + c * 256 + tau * 16 + wi * 2));
+  if (p.qmode == STARKV_Q_F16) {
+    const u4 v = *reinterpret_cast<const u4*>(code + c * 256 + tau * 16);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = h2f((uint16_t)(v[e / 2] >> (16 * (e % 2))));
+    return;
+  }
   const int ro = p.k_ro[g], nhi = ro / 8;
   const int hb = region_hi_bits(p.qmode), lb = region_lo_bits(p.qmode);
-  const bool hi = ch < ro;
+  const bool hi = c < nhi;
   const int bits = hi ? hb : lb;
-  // chunk c: 16 tokens x `bits` bytes, outlier chunks first; channel wi at bits*wi
+  // chunk c: 16 tokens x `bits` bytes, outlier chunks first; channel w at bits*w
   const uint8_t* tok = code + (hi ? c * 16 * hb : nhi * 16 * hb + (c - nhi) * 16 * lb) + tau * bits;
-  const int q = bits == 8 ? tok[wi] : code_field(tok, bits * wi, bits);
-  const int grp = hi ? ch / 32 : (ro + 31) / 32 + (ch - ro) / 32;
-  const uint16_t* m = reinterpret_cast<const uint16_t*>(
+  const int grp = hi ? c / 4 : (ro + 31) / 32 + (c - nhi) / 4;
+  const uint32_t m = *reinterpret_cast<const uint32_t*>(
       p.cache + p.k_meta_off[g] + (blk * p.k_ng[g] + grp) * 64 + tau * 4);
-  return __builtin_fmaf((float)q, h2f(m[0]), h2f(m[1]));
+  uint64_t w;
+  if (bits == 8) {
+    const u2 d = *reinterpret_cast<const u2*>(tok);
+    w = (uint64_t)d.x | ((uint64_t)d.y << 32);
+  } else if (bits == 4) {
+    w = *reinterpret_cast<const uint32_t*>(tok);
+  } else {
+    w = (uint32_t)tok[0] | ((uint32_t)tok[1] << 8) | ((uint32_t)tok[2] << 16);
+  }
+  const float s = h2f((uint16_t)m), z = h2f((uint16_t)(m >> 16));
+  const uint32_t mask = (1u << bits) - 1;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf((float)((uint32_t)(w >> (bits * e)) & mask), s, z);
 }
 
-// Dequantized value latent channel r at token t of sequence b.
-__device__ float value_latent(const CombineParams& p, int b, int t, int r) {
-  const int64_t blk = cache_row(p.rmap, b, t) / 32;
-  const int u = t % 32, kq = u % 4, slot = 4 * (u / 16) + (u % 16) / 4;
+// Dequantized value latent channel r of token u of the 32-token block blk.
+__device__ __forceinline__ float value_latent(const CombineParams& p, int64_t blk, int u, int r) {
+  const int kq = u % 4, slot = 4 * (u / 16) + (u % 16) / 4;
   const uint8_t* code = p.cache + p.v_code_off + blk * 32 * p.v_rb;
   if (p.qmode == STARKV_Q_F16)
     return h2f(*reinterpret_cast<const uint16_t*>(code + (r * 4 + kq) * 16 + slot * 2));
@@ -1567,45 +1577,63 @@ __device__ float value_latent(const CombineParams& p, int b, int t, int r) {
                         h2f(reinterpret_cast<const uint16_t*>(m + 16)[slot]));
 }
 
-// floats of the combine kernel's LDS before its shared region (kept a multiple
-// of 4 so that the region is 16-byte aligned)
-__host__ __device__ constexpr int combine_head_floats(int rv) {
-  return (rv + 2 * kCombineMaxSplits + 3 * kRescoreMax + 16 + 3) / 4 * 4;
+// LDS of the combine kernel in floats: a fixed head, then one region that in
+// turn holds the waves' split sums [NW][rv], the rescoring's key latents
+// [rmax][8 NW] and B_k block (fp16 [rmax][D]), its value sums [groups][rv] and
+// the up-projection's partial sums [NW][Dc].
+__host__ __device__ constexpr int combine_head_floats(int rv, int nw) {
+  return (rv + 2 * kCombineMaxSplits + 4 * kRescoreMax + kCandChunk + 4 * nw + 4 + 3 * nw + 3) / 4 * 4;
+}
+__host__ __device__ constexpr int combine_value_groups(int rv, int nw) {
+  return 64 * nw / rv > 1 ? 64 * nw / rv : 1;
 }
 
-// DEEP (grids of at most one workgroup per compute unit): both partial batches
-// of the first 64 splits and the thread's U_V rows are loaded at entry.
-// Otherwise (several workgroups per compute unit) the second batch is loaded
-// when needed and U_V just before the merge, which keeps the kernel at 128
-// VGPRs (four workgroups per compute unit).
-template <bool DEEP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DEEP ? 1 : 4)))
+// NW: waves of the workgroup.
+//
+// NW = 16 (grids of at most one workgroup per compute unit): every load that
+// does not depend on the split weights is issued at entry (64 splits' partials
+// and the thread's U_V rows), and the rescoring spreads over sixteen waves.  It
+// is bound by latency: with four waves and one workgroup per compute unit each
+// SIMD ran a single wave through every dependent step of up to 128 candidates.
+// NW = 4 (several workgroups per compute unit): 128 VGPRs, four workgroups per
+// compute unit cover each other's latency; U_V is loaded just before its use.
+//
+// Rescoring, 8 NW candidates at a time: a thread dequantizes eight channels of
+// one candidate from one code and one (s, z) load; a lane then rebuilds one RoPE
+// pair of its wave's eight candidates at once (two B_k reads feed 16 FMAs), so
+// the products are bound by the FMAs instead of by an LDS round trip per
+// candidate and channel, and the fp64 frequency is formed once per lane.
+// Measured against the one-candidate-and-pair-per-item form on four waves: decode
+// calls of 4 x 128K tokens with about 100 candidates a head 276 -> 191 us, of 4 x 32K
+// 108 -> 83 us, of 6 short contexts 81 -> 52 us, of 8 x 4K 70 -> 50 us.
+template <int NW, int D>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
 void decode_combine_kernel(CombineParams p) {
   extern __shared__ __align__(16) float sm[];
-  const int D = p.head_dim;
+  constexpr bool DEEP = NW == 16;
+  constexpr int NTH = 64 * NW;
+  constexpr int HALF = D / 2;
+  constexpr int KC = kCandChunk / NW;    // candidate entries per thread and chunk
+  constexpr int NB = 8 * NW;             // candidates rescored at a time
   float* a = sm;                         // [rv] merged value latent
   float* wts = a + p.rv;                 // [kCombineMaxSplits] split weights
-  float* c_x = wts + kCombineMaxSplits;  // [kRescoreMax] approximate scores
+  uint32_t* sfl = reinterpret_cast<uint32_t*>(wts + kCombineMaxSplits);  // [..] flags
+  float* c_x = reinterpret_cast<float*>(sfl + kCombineMaxSplits);  // [kRescoreMax] approximate scores
   float* c_d = c_x + kRescoreMax;        // [kRescoreMax] weight corrections
   int* c_t = reinterpret_cast<int*>(c_d + kRescoreMax);   // [kRescoreMax] tokens
-  uint32_t* sfl = reinterpret_cast<uint32_t*>(c_t + kRescoreMax);  // [kCombineMaxSplits] flags
-  float* misc = reinterpret_cast<float*>(sfl + kCombineMaxSplits);  // M, L, L', unused
-  float* wmax = misc + 4;                // [4] per-wave split maxima
-  float* wsum = misc + 8;                // [4] per-wave weighted sums
-  int* wfl = reinterpret_cast<int*>(misc + 12);   // [4] per-wave: a split flagged candidates
-  // One region, 16-byte aligned, serves two phases: the merge (per-wave split
-  // sums, and the rescoring's key latents and B_k block) and, once the merged
-  // latent is in `a`, the up-projection's partial sums.
-  float* uni = sm + combine_head_floats(p.rv);
-  float* red4 = uni;                                   // [4][rv] per-wave split sums
-  float* lat = red4 + 4 * p.rv;                        // [kRescoreBatch][rmax] key latents
-  uint16_t* bks = reinterpret_cast<uint16_t*>(lat + kRescoreBatch * p.rmax);  // [rmax][D] fp16
-  float* red = uni;                                    // [256 / (D/8)][D] partial up-projections
+  int* c_b = c_t + kRescoreMax;          // [kRescoreMax] their 16-token cache blocks
+  int* kcnt = c_b + kRescoreMax;         // [kCandChunk] entries per split
+  int* lcnt = kcnt + kCandChunk;         // [4][NW] entries per threshold
+  float* misc = reinterpret_cast<float*>(lcnt + 4 * NW);
+  float* wmax = misc + 4;                // [NW] per-wave split maxima
+  float* wsum = wmax + NW;               // [NW] per-wave weighted sums
+  int* wfl = reinterpret_cast<int*>(wsum + NW);   // [NW] per-wave: a split flagged candidates
+  float* uni = sm + combine_head_floats(p.rv, NW);
   const int i = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   // output columns c_0 .. c_0 + Dc - 1 of this workgroup (the merge and the
   // rescoring are repeated by each of the col_split workgroups of the head)
   const int Dc = D / p.col_split, c_0 = blockIdx.z * Dc;
-  const int lane = tid & 63, w = tid >> 6;
+  const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = (int)(((int64_t)i * p.n_kv) / p.n_q);
   // this sequence's splits: under the work plan, items first .. first + ns - 1
   // (the split pass wrote the plan), else the fixed split grid
@@ -1627,10 +1655,10 @@ void decode_combine_kernel(CombineParams p) {
   const int64_t lat_lo = (int64_t)p.batch * p.n_q * p.rv;
   if (L == 0) {
     if (to_lat) {
-      for (int r = tid; r < p.rv; r += 256) p.lat[lat_row + r] = p.lat[lat_lo + lat_row + r] = 0;
+      for (int r = tid; r < p.rv; r += NTH) p.lat[lat_row + r] = p.lat[lat_lo + lat_row + r] = 0;
       return;
     }
-    for (int j = c_0 + tid; j < c_0 + Dc; j += 256) {
+    for (int j = c_0 + tid; j < c_0 + Dc; j += NTH) {
       if (p.out_dtype == STARKV_DT_F32) static_cast<float*>(p.out)[out_row + j] = 0.0f;
       else static_cast<uint16_t*>(p.out)[out_row + j] = 0;
     }
@@ -1640,18 +1668,18 @@ void decode_combine_kernel(CombineParams p) {
   const int64_t sstride = (int64_t)p.n_q * p.part_stride;
   // Every load that does not depend on the split weights is issued at once so
   // that they share one memory round trip: each split's maximum, normalizer and
-  // candidate flags (one split per thread), the value-latent partials of the
-  // first 64 splits and this thread's first rows of U_V.
+  // candidate flags (one split per thread), the first value-latent partials and
+  // this thread's first rows of U_V.
   // (m, l, flags, unused) and the four block bounds: two 16-byte loads from a
   // valid split, not in a branch, so that the first wait covers only them
-  const float* ps = part + min(tid, ns - 1) * sstride + p.rv;
+  const float* ps = part + (int64_t)min(tid, ns - 1) * sstride + p.rv;
   const f4 ml0 = *reinterpret_cast<const f4*>(ps);
   const f4 qb0 = *reinterpret_cast<const f4*>(ps + 4);
   const float mv0 = tid < ns ? ml0[0] : -INFINITY;
   const float lv0 = ml0[1];
   const uint32_t fl0 = tid < ns ? __float_as_uint(ml0[2]) : 0u;
   const int D8 = Dc / 8;                 // 16, 8 or 4 column vectors
-  const int groups = 256 / D8;           // row groups of the up-projection
+  const int groups = NTH / D8;           // row groups of the up-projection
   const int j8 = tid % D8, rg = tid / D8;
   const int64_t ldb = (int64_t)p.n_kv * D;
   const uint16_t* bv = p.bv + (int64_t)g * D + c_0 + 8 * j8;
@@ -1659,26 +1687,25 @@ void decode_combine_kernel(CombineParams p) {
   // n_split * sstride floats, far below 4 GiB
   const uint8_t* pbase = reinterpret_cast<const uint8_t*>(part);
   const uint32_t sbytes = (uint32_t)sstride * 4u;
-  // Value-latent partials: wave w takes splits w, w + 4, .., lane l channels
-  // 4l..4l+3 of each 256-channel chunk, one 16-byte load per (split, chunk), so
-  // a chunk of all splits is 64 loads of 1 KiB per workgroup.  A wave loads its
-  // splits in batches of 8 (splits w + 32h + 4k); the two batches of chunk 0
-  // (splits below 64) are loaded now.
-  constexpr int kSplitBatch = 8;
+  // Value-latent partials: wave w takes splits w, w + NW, .., lane l channels
+  // 4l..4l+3 of each 256-channel chunk, one 16-byte load per (split, chunk).  A
+  // wave loads its splits in batches (splits w + NW (k + kSplitBatch h)); the
+  // first batch of chunk 0 is loaded now (64 splits with NW = 16, else 32).
+  constexpr int kSplitBatch = DEEP ? 4 : 8;
+  constexpr int kRound = NW * kSplitBatch;
   const int n_chunk = (p.rv + 255) / 256;
   auto load_batch = [&](int ch, int h, f4 (&pv)[kSplitBatch]) {
     const uint32_t o = (uint32_t)min(256 * ch + 4 * lane, p.rv - 4) * 4u;
 #pragma unroll
     for (int k = 0; k < kSplitBatch; ++k)
       pv[k] = *reinterpret_cast<const f4*>(
-          pbase + o + (uint32_t)min(w + 32 * h + 4 * k, ns - 1) * sbytes);
+          pbase + o + (uint32_t)min(w + kRound * h + NW * k, ns - 1) * sbytes);
   };
-  f4 pv0[kSplitBatch], pv1[kSplitBatch];
+  f4 pv0[kSplitBatch];
   load_batch(0, 0, pv0);
-  if constexpr (DEEP) load_batch(0, 1, pv1);   // (clamped split indices: valid, unused below 33 splits)
-  // rows of U_V per thread per round of loads: 8 when they are loaded at entry,
+  // rows of U_V per thread per round of loads: 4 when they are loaded at entry,
   // 16 when loaded before the merge (then the partials' registers are free)
-  constexpr int kUpRows = DEEP ? 8 : 16;
+  constexpr int kUpRows = DEEP ? 4 : 16;
   // rows past rv load row rv - 1 and are skipped by the product.  The loads are
   // not in a branch, so that no wait before them covers more than it must: with
   // latent output (no U_V) they read the first partials, unused.
@@ -1691,15 +1718,18 @@ void decode_combine_kernel(CombineParams p) {
   };
   u4 w0[kUpRows];
   if constexpr (DEEP) load_rows(rg, w0);
-  const int r_g = p.k_rank[g];
-  {                               // split weights: one split per thread
+  float M, Lsum;
+  bool any_cand;
+  {                               // split weights: one split per thread (ns <= 256 <= NTH)
     float m = mv0;
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
     if (lane == 0) wmax[w] = m;
     __syncthreads();
-    m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+    m = wmax[0];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) m = fmaxf(m, wmax[k]);   // splits live in the first four waves
     const float wv = tid < ns ? __builtin_amdgcn_exp2f(mv0 - m) : 0.0f;
-    wts[tid] = wv;
+    if (tid < kCombineMaxSplits) wts[tid] = wv;
     float l = tid < ns ? wv * lv0 : 0.0f;
     for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
     if (lane == 0) wsum[w] = l;
@@ -1712,57 +1742,45 @@ void decode_combine_kernel(CombineParams p) {
     for (int t = 0; t < 4; ++t)
       if (((fl0 >> (8 * t)) & 0xFFu) != 0u && wv * qb0[t] >= 0.5f * kRescoreTau * ls)
         fl |= 1u << (8 * t);
-    sfl[tid] = fl;
+    if (tid < kCombineMaxSplits) sfl[tid] = fl;
     const bool fw = __ballot(fl != 0u) != 0;
     if (lane == 0) wfl[w] = fw ? 1 : 0;
-    if (tid == 0) { misc[0] = m; misc[1] = ls; }
     __syncthreads();
+    M = m;
+    Lsum = ls;
+    any_cand = (wfl[0] | wfl[1] | wfl[2] | wfl[3]) != 0;
   }
-  const float M = misc[0], Lsum = misc[1];
-  const bool any_cand = (wfl[0] | wfl[1] | wfl[2] | wfl[3]) != 0;
   // weighted sums of this wave's splits, per channel, into red4[w][r]
+  float* red4 = uni;
   auto add_batch = [&](int h, const f4 (&pv)[kSplitBatch], f4& acc) {
 #pragma unroll
     for (int k = 0; k < kSplitBatch; ++k) {
-      const int sp = w + 32 * h + 4 * k;
+      const int sp = w + kRound * h + NW * k;
       if (sp < ns) acc += wts[sp] * pv[k];
     }
   };
   for (int ch = 0; ch < n_chunk; ++ch) {
     f4 acc = (f4){0, 0, 0, 0};
-    if (ch == 0) {
-      add_batch(0, pv0, acc);
-      if (ns > 32) {                           // splits 32 .. 63
-        if constexpr (DEEP) {
-          add_batch(1, pv1, acc);
-        } else {
-          load_batch(0, 1, pv1);
-          add_batch(1, pv1, acc);
-        }
+    for (int h = 0; kRound * h < ns; ++h) {
+      if (ch == 0 && h == 0) {
+        add_batch(0, pv0, acc);
+      } else {
+        f4 pv[kSplitBatch];
+        load_batch(ch, h, pv);
+        add_batch(h, pv, acc);
       }
-    } else {
-      f4 pa[kSplitBatch], pb[kSplitBatch];
-      load_batch(ch, 0, pa);
-      if (ns > 32) load_batch(ch, 1, pb);
-      add_batch(0, pa, acc);
-      if (ns > 32) add_batch(1, pb, acc);
     }
     const int r = 256 * ch + 4 * lane;
     if (r < p.rv) *reinterpret_cast<f4*>(red4 + w * p.rv + r) = acc;
   }
-  // splits beyond 64 (long sequences): further batches added to the wave's own
-  // partial sums, in the same order
-  for (int h = 2; 32 * h < ns; ++h)
-    for (int ch = 0; ch < n_chunk; ++ch) {
-      f4 pv[kSplitBatch];
-      load_batch(ch, h, pv);
-      const int r = 256 * ch + 4 * lane;
-      if (r < p.rv) {
-        f4 acc = *reinterpret_cast<const f4*>(red4 + w * p.rv + r);
-        add_batch(h, pv, acc);
-        *reinterpret_cast<f4*>(red4 + w * p.rv + r) = acc;
-      }
-    }
+  __syncthreads();
+  // merged, not yet normalized; each thread reads back the channels it wrote
+  for (int r = tid; r < p.rv; r += NTH) {
+    float acc = red4[r];
+#pragma unroll
+    for (int k = 1; k < NW; ++k) acc += red4[k * p.rv + r];
+    a[r] = acc;
+  }
 
   // ---- candidate selection: share x (1 + |x|) >= tau, tau raised by 4 until
   // at most kRescoreMax remain (at most 8 thresholds); compaction in entry
@@ -1770,249 +1788,234 @@ void decode_combine_kernel(CombineParams p) {
   // beyond, one pass over the chunks counts the entries above each threshold
   // and a second compacts, reading the chunks again.
   constexpr int kLevels = 8;
-  // Candidate entries of the splits.  Thread tid takes slot `lane` of splits
-  // 64 c + 4 k + w of chunk c (entry order: split, then slot); a slot's block of
-  // 16 entries holds data only when the split set its flag byte, and the rest
-  // read as -inf scores (never selected).
-  static_assert(kCand == 64 && kCandPerThread == 16, "one slot per lane");
-  const float2* cand = p.cand + ((int64_t)first * p.n_q + i) * kCand;
-  auto load_cand = [&](int c, float2 (&ce)[kCandPerThread]) {
-    const float2* cl = cand + (int64_t)(64 * c + w) * p.n_q * kCand + lane;
-    const int64_t cstep = (int64_t)4 * p.n_q * kCand;
+  float inv_l = 1.0f / Lsum;
+  if (any_cand) {
+    // Candidate entries of the splits.  Thread tid takes slot `lane` of splits
+    // 64 c + NW k + w of chunk c (entry order: split, then slot); a slot's block of
+    // 16 entries holds data only when the split set its flag byte, and the rest
+    // read as -inf scores (never selected).
+    static_assert(kCand == 64, "one slot per lane");
+    const float2* cand = p.cand + ((int64_t)first * p.n_q + i) * kCand;
+    auto load_cand = [&](int c, float2 (&ce)[KC], float (&prio)[KC]) {
+      const float2* cl = cand + (int64_t)(kCandChunk * c + w) * p.n_q * kCand + lane;
+      const int64_t cstep = (int64_t)NW * p.n_q * kCand;
 #pragma unroll
-    for (int k = 0; k < kCandPerThread; ++k) {
-      const int s = 64 * c + 4 * k + w;
-      ce[k] = make_float2(-INFINITY, 0.0f);
-      if (s < ns && ((sfl[s] >> (8 * (lane >> 4))) & 0xFFu) != 0u) ce[k] = cl[k * cstep];
-    }
-  };
-  const int n_cchunk = (ns + 63) / 64;
-  auto priorities = [&](const float2 (&ce)[kCandPerThread], float (&prio)[kCandPerThread]) {
+      for (int k = 0; k < KC; ++k) {
+        const int s = kCandChunk * c + NW * k + w;
+        ce[k] = make_float2(-INFINITY, 0.0f);
+        if (s < ns && ((sfl[s] >> (8 * (lane >> 4))) & 0xFFu) != 0u) ce[k] = cl[k * cstep];
+      }
 #pragma unroll
-    for (int k = 0; k < kCandPerThread; ++k) {
-      const float x = ce[k].x;
-      prio[k] = (x == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(x - M) / Lsum * (1.0f + fabsf(x));
-    }
-  };
-  int* kcnt = reinterpret_cast<int*>(lat);   // [kCandPerThread][4] wave counts (lat is free here)
-  // one chunk's entries with prio >= tau go to c_x / c_t from `base` on, in
-  // entry order; returns the next base
-  auto compact = [&](const float2 (&ce)[kCandPerThread], const float (&prio)[kCandPerThread],
-                     float tau, int base) {
-    uint64_t bal[kCandPerThread];
+      for (int k = 0; k < KC; ++k) {
+        const float x = ce[k].x;
+        prio[k] = (x == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(x - M) / Lsum * (1.0f + fabsf(x));
+      }
+    };
+    // entries of a chunk at or above tau, per split; lane s of every wave gets
+    // the number in the chunk's splits before s, and *total their sum
+    auto scan = [&](const float (&prio)[KC], float tau, int* total) {
+      __syncthreads();                   // kcnt's last readers are done
 #pragma unroll
-    for (int k = 0; k < kCandPerThread; ++k) {
-      bal[k] = __ballot(prio[k] >= tau);
-      if (lane == 0) kcnt[4 * k + w] = __builtin_popcountll(bal[k]);
-    }
-    __syncthreads();
-    // the wave counts of four entries at a time, read together
+      for (int k = 0; k < KC; ++k) {
+        const int n = __builtin_popcountll(__ballot(prio[k] >= tau));
+        if (lane == 0) kcnt[NW * k + w] = n;
+      }
+      __syncthreads();
+      const int v = kcnt[lane];
+      int incl = v;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+      }
+      *total = __builtin_amdgcn_readlane(incl, 63);
+      return incl - v;
+    };
+    auto scatter = [&](const float2 (&ce)[KC], const float (&prio)[KC], float tau, int base, int excl) {
 #pragma unroll
-    for (int k0 = 0; k0 < kCandPerThread; k0 += 4) {
-      int4 kc[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) kc[j] = *reinterpret_cast<const int4*>(kcnt + 4 * (k0 + j));
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int k = k0 + j;
-        const int off = base + (w > 0 ? kc[j].x : 0) + (w > 1 ? kc[j].y : 0) + (w > 2 ? kc[j].z : 0);
+      for (int k = 0; k < KC; ++k) {
+        const uint64_t bal = __ballot(prio[k] >= tau);
+        const int off = base + __builtin_amdgcn_readlane(excl, NW * k + w);
         if (prio[k] >= tau) {
-          const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal[k] >> 32),
-                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)bal[k], 0));
-          if (off + rank < kRescoreMax) {
-            c_x[off + rank] = ce[k].x;
-            c_t[off + rank] = __float_as_int(ce[k].y);
+          const int at = off + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
+          if (at < kRescoreMax) {
+            const int t = __float_as_int(ce[k].y);
+            c_x[at] = ce[k].x;
+            c_t[at] = t;
+            c_b[at] = (int)(cache_row(p.rmap, b, t) >> 4);
           }
         }
-        base += kc[j].x + kc[j].y + kc[j].z + kc[j].w;
       }
-    }
-    __syncthreads();                     // kcnt is rewritten by the next chunk
-    return base;
-  };
-  float tau = kRescoreTau;
-  int n_sel = 0;
-  if (!any_cand) {
-    // no split holds a candidate that could reach the threshold
-  } else if (n_cchunk == 1) {
-    float2 ce0[kCandPerThread];
-    load_cand(0, ce0);
-    float prio[kCandPerThread];
-    priorities(ce0, prio);
-    {
-      int c = 0;
+    };
+    // entries at or above threshold j, in 16-bit fields (field j % 2 of word
+    // j / 2; at most 4096 per wave)
+    auto count_levels = [&](const float (&prio)[KC], uint32_t (&lv)[kLevels / 2]) {
 #pragma unroll
-      for (int k = 0; k < kCandPerThread; ++k) c += prio[k] >= tau;
-      for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-      if (lane == 0) kcnt[w] = c;
-      __syncthreads();
-      n_sel = kcnt[0] + kcnt[1] + kcnt[2] + kcnt[3];
-      __syncthreads();
-    }
-    if (n_sel > kRescoreMax) {
-      // the higher thresholds counted in one pass (16-bit fields, as for
-      // several chunks below), then the first that leaves at most kRescoreMax
-      uint32_t lv[kLevels / 2];
-#pragma unroll
-      for (int j = 0; j < kLevels / 2; ++j) lv[j] = 0;
-#pragma unroll
-      for (int k = 0; k < kCandPerThread; ++k) {
+      for (int k = 0; k < KC; ++k) {
         float t = kRescoreTau;
 #pragma unroll
         for (int j = 0; j < kLevels; ++j, t *= 4.0f)
           lv[j / 2] += prio[k] >= t ? 1u << (16 * (j % 2)) : 0u;
       }
+    };
+    // the first threshold that leaves at most kRescoreMax entries (else the last)
+    auto pick_level = [&](uint32_t (&lv)[kLevels / 2], float* tau) {
 #pragma unroll
       for (int j = 0; j < kLevels / 2; ++j) {
         uint32_t v = lv[j];
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if (lane == 0) kcnt[4 * j + w] = (int)v;
+        if (lane == 0) lcnt[NW * j + w] = (int)v;
       }
       __syncthreads();
-      for (int j = 1; j < kLevels; ++j) {
-        tau *= 4.0f;
-        n_sel = 0;
-        for (int ww = 0; ww < 4; ++ww) n_sel += ((uint32_t)kcnt[4 * (j / 2) + ww] >> (16 * (j % 2))) & 0xFFFFu;
-        if (n_sel <= kRescoreMax) break;
+      float t = kRescoreTau;
+      int n = 0;
+      for (int j = 0; j < kLevels; ++j, t *= 4.0f) {
+        n = 0;
+        for (int ww = 0; ww < NW; ++ww)
+          n += ((uint32_t)lcnt[NW * (j / 2) + ww] >> (16 * (j % 2))) & 0xFFFFu;
+        *tau = t;
+        if (n <= kRescoreMax) break;
       }
-      __syncthreads();                   // the counts are read before kcnt is rewritten
-    }
-    // past the cap at every threshold tried (at least kRescoreMax tokens each
-    // holding that much): the first kRescoreMax of the last one, in entry order
-    if (n_sel > 0) compact(ce0, prio, tau, 0);
-    n_sel = min(n_sel, kRescoreMax);
-  } else {
-    // entries at or above threshold j, per thread, in 16-bit fields (field j % 2
-    // of word j / 2; at most 32 per thread and 2048 per wave)
-    uint32_t lv[kLevels / 2];
-#pragma unroll
-    for (int j = 0; j < kLevels / 2; ++j) lv[j] = 0;
-    for (int c = 0; c < n_cchunk; ++c) {
-      float2 ce[kCandPerThread];
-      load_cand(c, ce);
-      float prio[kCandPerThread];
-      priorities(ce, prio);
-#pragma unroll
-      for (int k = 0; k < kCandPerThread; ++k) {
-        float t = kRescoreTau;
-#pragma unroll
-        for (int j = 0; j < kLevels; ++j, t *= 4.0f)
-          lv[j / 2] += prio[k] >= t ? 1u << (16 * (j % 2)) : 0u;
+      return n;
+    };
+    const int n_cchunk = (ns + kCandChunk - 1) / kCandChunk;
+    float2 ce[KC];
+    float prio[KC];
+    float tau = kRescoreTau;
+    int n_sel = 0;
+    if (n_cchunk == 1) {
+      load_cand(0, ce, prio);
+      int excl = scan(prio, tau, &n_sel);
+      if (n_sel > kRescoreMax) {
+        uint32_t lv[kLevels / 2] = {};
+        count_levels(prio, lv);
+        pick_level(lv, &tau);
+        excl = scan(prio, tau, &n_sel);
       }
-    }
-#pragma unroll
-    for (int j = 0; j < kLevels / 2; ++j) {
-      uint32_t v = lv[j];
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-      if (lane == 0) kcnt[4 * j + w] = (int)v;
-    }
-    __syncthreads();
-    for (int j = 0; j < kLevels; ++j) {
-      n_sel = 0;
-      for (int ww = 0; ww < 4; ++ww) n_sel += ((uint32_t)kcnt[4 * (j / 2) + ww] >> (16 * (j % 2))) & 0xFFFFu;
-      if (n_sel <= kRescoreMax || j == kLevels - 1) break;
-      tau *= 4.0f;
-    }
-    __syncthreads();                     // the counts are read before kcnt is rewritten
-    if (n_sel > 0) {
-      int base = 0;
+      // past the cap at every threshold tried (at least kRescoreMax tokens each
+      // holding that much): the first kRescoreMax of the last one, in entry order
+      if (n_sel > 0) scatter(ce, prio, tau, 0, excl);
+    } else {
+      uint32_t lv[kLevels / 2] = {};
       for (int c = 0; c < n_cchunk; ++c) {
-        float2 ce[kCandPerThread];
-        load_cand(c, ce);
-        float prio[kCandPerThread];
-        priorities(ce, prio);
-        base = compact(ce, prio, tau, base);
+        load_cand(c, ce, prio);
+        count_levels(prio, lv);
+      }
+      n_sel = pick_level(lv, &tau);
+      if (n_sel > 0) {
+        int base = 0;
+        for (int c = 0; c < n_cchunk; ++c) {
+          int n;
+          load_cand(c, ce, prio);
+          const int excl = scan(prio, tau, &n);
+          scatter(ce, prio, tau, base, excl);
+          base += n;
+        }
       }
     }
     n_sel = min(n_sel, kRescoreMax);
-  }
-  if (n_sel > 0) {
-    // one round of loads for the rescoring: the KV head's up-projection block
-    // B_k (r_g x D fp16, staged in LDS) and the candidates' key latents
-    const int nbk = r_g * D / 8;           // 16-byte vectors
-    u4 bkv[kBkVecPerThread];
-    {
-      const u4* src = reinterpret_cast<const u4*>(p.bk + (int64_t)p.k_bkrow[g] * D);
-#pragma unroll
-      for (int k = 0; k < kBkVecPerThread; ++k)
-        bkv[k] = src[min(tid + k * 256, nbk - 1)];
-    }
-#pragma unroll
-    for (int k = 0; k < kBkVecPerThread; ++k)
-      if (tid + k * 256 < nbk) reinterpret_cast<u4*>(bks)[tid + k * 256] = bkv[k];
-    // ---- exact scores, kRescoreBatch candidates at a time: their dequantized
-    // key latents, then one (candidate, RoPE pair) item per thread; the items of
-    // a candidate are consecutive lanes of one wave and are summed with shuffles
-    const int HALF = D / 2;
-    const uint16_t* bk = bks;
-    const uint16_t* qs = static_cast<const uint16_t*>(p.q) + ((int64_t)b * p.n_q + i) * D;
-    for (int j0 = 0; j0 < n_sel; j0 += kRescoreBatch) {
-    const int nb = min(kRescoreBatch, n_sel - j0);
-    if (j0 > 0) __syncthreads();         // the previous batch's latents are read
-    for (int it = tid; it < nb * r_g; it += 256) {
-      const int j = it / r_g, ch = it % r_g;
-      lat[j * p.rmax + ch] = key_latent(p, g, b, c_t[j0 + j], ch);
-    }
-    __syncthreads();
-    for (int it0 = 0; it0 < nb * HALF; it0 += 256) {
-      const int it = it0 + tid;
-      const int jb = it / HALF, l = it % HALF;
-      const int j = j0 + jb;
-      float dot = 0.0f;
-      if (jb < nb) {
-        const float* lj = lat + jb * p.rmax;
-        float klo = 0.0f, khi = 0.0f;
-#pragma unroll 8
-        for (int ch = 0; ch < r_g; ++ch) {
-          klo = __builtin_fmaf(lj[ch], h2f(bk[ch * D + l]), klo);
-          khi = __builtin_fmaf(lj[ch], h2f(bk[ch * D + l + HALF]), khi);
-        }
-        const float q_lo = p.q_bf16 ? __uint_as_float((uint32_t)qs[l] << 16) : h2f(qs[l]);
-        const float q_hi = p.q_bf16 ? __uint_as_float((uint32_t)qs[l + HALF] << 16) : h2f(qs[l + HALF]);
-        // angle t * theta^(-2l/D), reduced modulo 2 pi in fp64
-        double ph = (double)c_t[j] * exp2(-(2.0 * l / D) * p.log2_theta);
-        ph -= 6.283185307179586476925286766559 * floor(ph * 0.15915494309189533576888376337251);
-        float sf, cf;
-        sincosf((float)ph, &sf, &cf);
-        dot = q_lo * (klo * cf - khi * sf) + q_hi * (khi * cf + klo * sf);
+    if (n_sel > 0) {
+      // the KV head's up-projection block B_k (r_g x D fp16) in LDS; the region's
+      // split sums were read before the barriers of the selection
+      const int r_g = p.k_rank[g], nch = r_g / 8;
+      float* lat = uni;                                              // [r_g][NB]
+      uint16_t* bks = reinterpret_cast<uint16_t*>(uni + p.rmax * NB);  // [r_g][D]
+      {
+        const u4* src = reinterpret_cast<const u4*>(p.bk + (int64_t)p.k_bkrow[g] * D);
+        for (int v = tid; v < r_g * D / 8; v += NTH) reinterpret_cast<u4*>(bks)[v] = src[v];
       }
-      for (int o = HALF / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
-      if (l == 0 && jb < nb)
-        c_d[j] = __builtin_amdgcn_exp2f(dot * p.score_scale - M) - __builtin_amdgcn_exp2f(c_x[j] - M);
+      __syncthreads();                   // the candidates are visible
+      const uint16_t* qs = static_cast<const uint16_t*>(p.q) + ((int64_t)b * p.n_q + i) * D;
+      // lane: RoPE pair l, candidates cj .. cj + NCL - 1 of the wave's eight
+      constexpr int NCL = HALF / 8;      // 8 with 64 pairs, 4 with 32
+      const int l = lane % HALF, cj = 8 * w + (lane / HALF) * NCL;
+      const float q_lo = load_qf(qs, l, p.q_bf16), q_hi = load_qf(qs, l + HALF, p.q_bf16);
+      const double om = exp2(-(2.0 * l / D) * p.log2_theta);
+      for (int j0 = 0; j0 < n_sel; j0 += NB) {
+        const int nb = min(NB, n_sel - j0);
+        if (j0 > 0) __syncthreads();     // the previous batch's latents are read
+        for (int it = tid; it < nch * NB; it += NTH) {
+          const int j = it % NB, c = it / NB;
+          if (j < nb) {
+            float x[8];
+            key_chunk(p, g, c_b[j0 + j], c_t[j0 + j] % 16, c, x);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) lat[(8 * c + e) * NB + j] = x[e];
+          }
+        }
+        __syncthreads();
+        if (8 * w < nb) {                // candidates past nb hold other latents, unused
+          float klo[NCL], khi[NCL];
+#pragma unroll
+          for (int e = 0; e < NCL; ++e) klo[e] = khi[e] = 0.0f;
+#pragma unroll 4
+          for (int ch = 0; ch < r_g; ++ch) {
+            const float blo = h2f(bks[ch * D + l]), bhi = h2f(bks[ch * D + l + HALF]);
+            const f4* x = reinterpret_cast<const f4*>(lat + ch * NB + cj);
+#pragma unroll
+            for (int e = 0; e < NCL; e += 4) {
+              const f4 xv = x[e / 4];
+#pragma unroll
+              for (int f = 0; f < 4; ++f) {
+                klo[e + f] = __builtin_fmaf(xv[f], blo, klo[e + f]);
+                khi[e + f] = __builtin_fmaf(xv[f], bhi, khi[e + f]);
+              }
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < NCL; ++e) {
+            const int j = min(cj + e, nb - 1);
+            // angle t * theta^(-2l/D), reduced modulo 2 pi in fp64
+            double ph = (double)c_t[j0 + j] * om;
+            ph -= 6.283185307179586476925286766559 * floor(ph * 0.15915494309189533576888376337251);
+            float sf, cf;
+            sincosf((float)ph, &sf, &cf);
+            float dot = q_lo * (klo[e] * cf - khi[e] * sf) + q_hi * (khi[e] * cf + klo[e] * sf);
+            for (int o = HALF / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
+            if (l == 0 && cj + e < nb)
+              c_d[j0 + j] = __builtin_amdgcn_exp2f(dot * p.score_scale - M) -
+                            __builtin_amdgcn_exp2f(c_x[j0 + j] - M);
+          }
+        }
+      }
+      __syncthreads();
+      // the corrected normalizer, the same in every wave
+      float dl = (lane < n_sel ? c_d[lane] : 0.0f) + (lane + 64 < n_sel ? c_d[lane + 64] : 0.0f);
+      for (int o = 32; o > 0; o >>= 1) dl += __shfl_xor(dl, o);
+      inv_l = 1.0f / (Lsum + dl);
+      // value latents of the rescored tokens: thread (group, channel), a group
+      // taking every n_vg-th candidate, eight candidates' loads in flight
+      const int n_vg = combine_value_groups(p.rv, NW);
+      float* vred = uni;                 // [n_vg][rv]: key latents and B_k are read
+      for (int it = tid; it < n_vg * p.rv; it += NTH) {
+        const int r = it % p.rv, vg = it / p.rv;
+        float acc = 0.0f;
+        for (int j0 = vg; j0 < n_sel; j0 += 8 * n_vg) {
+          float vl[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const int j = min(j0 + u * n_vg, n_sel - 1);
+            vl[u] = value_latent(p, c_b[j] >> 1, c_t[j] % 32, r);
+          }
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (j0 + u * n_vg < n_sel) acc = __builtin_fmaf(c_d[j0 + u * n_vg], vl[u], acc);
+        }
+        vred[vg * p.rv + r] = acc;
+      }
+      __syncthreads();
+      for (int r = tid; r < p.rv; r += NTH) {
+        float acc = a[r];
+        for (int vg = 0; vg < n_vg; ++vg) acc += vred[vg * p.rv + r];
+        a[r] = acc;
+      }
     }
-    }
-    __syncthreads();
-    if (tid == 0) {
-      float l2 = Lsum;
-      for (int j = 0; j < n_sel; ++j) l2 += c_d[j];
-      misc[2] = l2;
-    }
-    __syncthreads();
-  } else if (tid == 0) {
-    misc[2] = Lsum;
   }
-  __syncthreads();
-  const float inv_l = 1.0f / misc[2];
-  auto merge_channel = [&](int r) {
-    float acc = red4[r] + red4[p.rv + r] + red4[2 * p.rv + r] + red4[3 * p.rv + r];
-    for (int j0 = 0; j0 < n_sel; j0 += 8) {   // eight candidates' loads in flight
-      float vl[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) vl[u] = j0 + u < n_sel ? value_latent(p, b, c_t[j0 + u], r) : 0.0f;
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (j0 + u < n_sel) acc = __builtin_fmaf(c_d[j0 + u], vl[u], acc);
-    }
-    a[r] = acc * inv_l;
-  };
-  // (shallow form: the first rows of U_V, in flight while the rescored tokens'
-  // value latents load)
   if constexpr (!DEEP) load_rows(rg, w0);
-  for (int r = tid; r < p.rv; r += 256) merge_channel(r);
   __syncthreads();
   if (to_lat) {                 // absorbed output: the latents go to the product pass
-    for (int r = tid; r < p.rv; r += 256) {
-      const float x = a[r];
+    for (int r = tid; r < p.rv; r += NTH) {
+      const float x = a[r] * inv_l;
       const _Float16 h = (_Float16)x;
       p.lat[lat_row + r] = __builtin_bit_cast(uint16_t, h);
       p.lat[lat_lo + lat_row + r] = __builtin_bit_cast(uint16_t, (_Float16)(x - (float)h));
@@ -2028,7 +2031,7 @@ void decode_combine_kernel(CombineParams p) {
       const int r = r0 + k * groups;
       if (r < p.rv) {
         const _Float16* hw = reinterpret_cast<const _Float16*>(&w8[k]);
-        const float ar = a[r];
+        const float ar = a[r] * inv_l;
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[e] += ar * (float)hw[e];
       }
@@ -2040,12 +2043,19 @@ void decode_combine_kernel(CombineParams p) {
     load_rows(r0, w8);
     up_rows(r0, w8);
   }
+  // the wave's lanes of one column vector, then the waves' sums through LDS
+  // (nothing reads the region after the last barrier)
+  float* red = uni;                      // [NW][Dc]
 #pragma unroll
-  for (int e = 0; e < 8; ++e) red[rg * Dc + 8 * j8 + e] = o[e];
+  for (int e = 0; e < 8; ++e) {
+    for (int k = D8; k < 64; k <<= 1) o[e] += __shfl_xor(o[e], k);
+    if (lane < D8) red[w * Dc + 8 * j8 + e] = o[e];
+  }
   __syncthreads();
   if (tid < Dc) {
-    float ov = 0.0f;
-    for (int k = 0; k < groups; ++k) ov += red[k * Dc + tid];
+    float ov = red[tid];
+#pragma unroll
+    for (int k = 1; k < NW; ++k) ov += red[k * Dc + tid];
     if (p.out_dtype == STARKV_DT_F32) {
       static_cast<float*>(p.out)[out_row + c_0 + tid] = ov;
     } else {
@@ -2174,28 +2184,32 @@ int scratch_address(void** out) {
   return 0;
 }
 
+template <int NW, int D>
+static int launch_combine_t(const CombineParams& p, hipStream_t st) {
+  // the shared region: the split sums, the rescoring's key latents and B_k
+  // block, its value sums, or the up-projection's partial sums
+  const size_t dc = (size_t)D / p.col_split;
+  size_t region = (size_t)NW * p.rv;
+  region = std::max(region, (size_t)8 * NW * p.rmax + (size_t)p.rmax * D / 2);
+  region = std::max(region, (size_t)combine_value_groups(p.rv, NW) * p.rv);
+  region = std::max(region, (size_t)NW * dc);
+  const size_t lds = ((size_t)combine_head_floats(p.rv, NW) + region) * sizeof(float);
+  auto k = decode_combine_kernel<NW, D>;
+  static std::atomic<uint64_t> attr{0};
+  if (const int e = allow_lds(reinterpret_cast<const void*>(k), attr)) return e;
+  hipLaunchKernelGGL(k, dim3(p.n_q, p.batch, p.col_split), dim3(64 * NW), lds, st, p);
+  return (int)hipGetLastError();
+}
+
 int launch_decode_combine(const CombineParams& p, void* stream) {
   if (p.n_split > kCombineMaxSplits) return (int)hipErrorInvalidValue;
-  // the shared region: the merge phase (split sums, rescoring latents, B_k
-  // block) or the up-projection's 256 / (D/8) rows of D partial sums
-  const size_t merge = (size_t)4 * p.rv + (size_t)kRescoreBatch * p.rmax + (size_t)p.rmax * p.head_dim / 2;
   if (p.col_split != 1 && (p.col_split != 2 || p.lat)) return (int)hipErrorInvalidValue;
-  const int dc = p.head_dim / p.col_split;
-  const size_t upproj = (size_t)256 / (dc / 8) * dc;
-  const size_t lds = ((size_t)combine_head_floats(p.rv) + (merge > upproj ? merge : upproj)) *
-                     sizeof(float);
-  dim3 grid(p.n_q, p.batch, p.col_split);
+  if (p.head_dim != 64 && p.head_dim != 128) return (int)hipErrorInvalidValue;
   const hipStream_t st = static_cast<hipStream_t>(stream);
-  if ((int64_t)p.n_q * p.batch * p.col_split <= 256) {
-    static std::atomic<uint64_t> attr{0};
-    if (const int e = allow_lds(reinterpret_cast<const void*>(decode_combine_kernel<true>), attr)) return e;
-    hipLaunchKernelGGL(decode_combine_kernel<true>, grid, dim3(256), lds, st, p);
-  } else {
-    static std::atomic<uint64_t> attr{0};
-    if (const int e = allow_lds(reinterpret_cast<const void*>(decode_combine_kernel<false>), attr)) return e;
-    hipLaunchKernelGGL(decode_combine_kernel<false>, grid, dim3(256), lds, st, p);
-  }
-  return (int)hipGetLastError();
+  const bool deep = (int64_t)p.n_q * p.batch * p.col_split <= 256;
+  if (p.head_dim == 128)
+    return deep ? launch_combine_t<16, 128>(p, st) : launch_combine_t<4, 128>(p, st);
+  return deep ? launch_combine_t<16, 64>(p, st) : launch_combine_t<4, 64>(p, st);
 }
 #endif
 
