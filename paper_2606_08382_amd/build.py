@@ -1,7 +1,7 @@
 """Build libstarkv.so (HIP for gfx950) in-tree with hipcc.
 
-The decode split kernel is compiled once per (head_dim, cache precision) so the
-translation units build in parallel.
+The decode split kernels are compiled once per (head_dim, cache precision) so the
+translation units build in parallel, the costliest first.
 """
 from __future__ import annotations
 
@@ -22,9 +22,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # packed fp32 arithmetic stays off (hipcc's host pass warns it does not know it)
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
-UNITS = [("starkv_host.cpp", []), ("append.hip", []), ("output.hip", []), ("stream.hip", []),
-         ("decode.hip", ["-DSK_COMMON"])]
-UNITS += [("decode.hip", [f"-DSK_D={d}", f"-DSK_QM={q}"]) for d in (64, 128) for q in (0, 1, 2, 3)]
+UNITS = [(f, [f"-DSK_D={d}", f"-DSK_QM={q}"]) for f in ("split_poly.hip", "decode.hip")
+          for d in (128, 64) for q in (2, 3, 1, 0)]
+UNITS += [("starkv_host.cpp", []), ("append.hip", []), ("output.hip", []), ("stream.hip", []),
+          ("decode.hip", ["-DSK_COMMON"]), ("split_poly.hip", [])]
 
 
 def _obj_name(src: str, defs) -> str:

@@ -27,109 +27,11 @@
 
 #include <algorithm>
 #include <atomic>
-
 #include <type_traits>
 
-#include "starkv_internal.h"
+#include "decode_device.h"
 
 namespace starkv {
-
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ f4 mfma16(h8 a, h8 b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
-__device__ __forceinline__ uint32_t as_u32(h2 h) { return __builtin_bit_cast(uint32_t, h); }
-
-// A pair of 8-bit or 4-bit codes placed in the low mantissa bits of fp16 1024:
-// the fp16 value is 1024 + code exactly.  Subtracting 1024 is exact; the fma
-// with (s, z) rounds once.
-__device__ __forceinline__ uint32_t deq_pair(uint32_t magic_pair, h2 s, h2 z) {
-  h2 c = as_h2(magic_pair) - (h2){(_Float16)1024.0f, (_Float16)1024.0f};
-  return as_u32(__builtin_elementwise_fma(c, s, z));
-}
-
-// Scores may exceed the shared softmax reference by this much (log2 units)
-// before it is raised: probabilities stay below 2^8 in fp16.
-constexpr float kLazyMargin = 8.0f;
-
-// value-tile precision variants of the split kernel's p.V' phase
-constexpr int kValues8 = 0, kValues4 = 1, kValuesMixed = 2;
-
-__device__ __forceinline__ float wave_max16(float v) {
-  v = fmaxf(v, __shfl_xor(v, 16));
-  v = fmaxf(v, __shfl_xor(v, 32));
-  return v;
-}
-__device__ __forceinline__ float wave_sum16(float v) {
-  v += __shfl_xor(v, 16);
-  v += __shfl_xor(v, 32);
-  return v;
-}
-
-// ceil(x / k) for 0 <= x < 2^17 + 64 and 1 <= k <= 64, with rk = rcp_up(k),
-// the smallest float >= 1/k: the product rounds to the exact quotient's floor
-// (x/k is at least 1/64 below the next integer unless it is one, and the
-// relative error stays below 2^-22).
-__device__ __forceinline__ float rcp_up(int k) {
-  float r = __builtin_amdgcn_rcpf((float)k);           // within 1 ulp of 1/k
-  const float e = __builtin_fmaf(r, (float)k, -1.0f);  // exact residual
-  if (e >= 0.0f) {                                     // step down while still >= 1/k
-    const float d = __uint_as_float(__float_as_uint(r) - 1u);
-    if (__builtin_fmaf(d, (float)k, -1.0f) >= 0.0f) r = d;
-  } else {
-    r = __uint_as_float(__float_as_uint(r) + 1u);
-  }
-  return r;
-}
-__device__ __forceinline__ int div_up_small(int x, int k, float rk) {
-  return (int)((float)(x + k - 1) * rk);
-}
-
-// Work plan of one decode step for up to 64 sequences of ragged lengths: the
-// split length S = kStepTokens * k is the smallest with at most `cap` work
-// items sum_b ceil(L_b / S) (k >= k_lo keeps every sequence at <= 256 splits,
-// k <= 64 keeps S <= 8192), and the items are the sequences' splits in order.
-// Every wave that calls this gets the same plan.  len: the clamped length held
-// by lane b (lanes >= B hold 0).  Returns k; *cnt gets the split count of
-// sequence `lane`.
-__device__ __forceinline__ int wave_split_plan(int len, int B, int k_lo, int cap, int lane,
-                                               int* cnt) {
-  const int m = (len + kStepTokens - 1) / kStepTokens;      // steps of sequence `lane`
-  const int k = min(k_lo + lane, 64);                       // candidate of this lane
-  const float rk = rcp_up(k);
-  int items = 0;
-  for (int j = 0; j < B; ++j) items += div_up_small(__builtin_amdgcn_readlane(m, j), k, rk);
-  const uint64_t ok = __ballot(items <= cap);
-  const int ks = ok ? min(k_lo + (int)__builtin_ctzll(ok), 64) : 64;
-  *cnt = div_up_small(m, ks, rcp_up(ks));
-  return ks;
-}
-
-__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-  return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
-__device__ __forceinline__ float load_qf(const uint16_t* q, int idx, int bf16) {
-  const uint16_t u = q[idx];
-  if (bf16) return __uint_as_float(static_cast<uint32_t>(u) << 16);
-  return (float)__builtin_bit_cast(_Float16, u);
-}
-
-// A value the compiler cannot fold into instructions as a literal, so that it
-// stays in a register (lets v_and_or_b32 take it as an operand).
-__device__ __forceinline__ uint32_t opaque_u32(uint32_t v) {
-  uint32_t r;
-  asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "s"(v));
-  return r;
-}
 
 // 4-bit word of pairs (nibble k, nibble k+4), k = 0..3, with the nibble mask
 // held in a register.
@@ -174,17 +76,6 @@ __host__ __device__ inline SplitLds split_lds(int frags, int nql, int head_dim, 
   return L;
 }
 
-// Asynchronous copy of n_bytes (a multiple of 16) from global memory into LDS by
-// the whole workgroup, 16 bytes per lane, without passing through registers.
-// Completion is tracked by vmcnt.
-__device__ __forceinline__ void copy_to_lds(uint8_t* lds, const uint8_t* src, int n_bytes,
-                                            int w, int lane) {
-  for (int base = w * 1024; base < n_bytes; base += kWaves * 1024) {
-    if (base + lane * 16 < n_bytes)
-      __builtin_amdgcn_global_load_lds(src + base + lane * 16, lds + base, 16, 0, 0);
-  }
-}
-
 // Wait until at most n (wave-uniform) vector memory operations of this wave are
 // outstanding; they complete in issue order.  Counts above 15 wait for all
 // (conservative).
@@ -209,15 +100,6 @@ __device__ __forceinline__ void wait_vm(int n) {
   }
 }
 
-// Workgroup barrier over LDS traffic only: this wave's LDS operations have
-// completed (lgkmcnt(0)), then s_barrier.  The fence of __syncthreads() also
-// waits for every global load and LDS copy still in flight (vmcnt(0)); this
-// barrier leaves them in flight, and the copies it must cover are waited for
-// explicitly (wait_vm) before it.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // The same by one wave: n_bytes (a multiple of 16) at src into lds, one copy
 // instruction per KiB, lane 0 active in each.
 __device__ __forceinline__ void copy_to_lds_wave(uint8_t* lds, const uint8_t* src, int n_bytes,
@@ -226,10 +108,6 @@ __device__ __forceinline__ void copy_to_lds_wave(uint8_t* lds, const uint8_t* sr
     if (base + lane * 16 < n_bytes)
       __builtin_amdgcn_global_load_lds(src + base + lane * 16, lds + base, 16, 0, 0);
   }
-}
-
-__device__ __forceinline__ uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) {
-  return __builtin_amdgcn_perm(hi, lo, sel);
 }
 
 // 8-bit codes d (bytes b0..b3) -> fp16 pairs (1024+b0, 1024+b1) and (1024+b2, 1024+b3)
@@ -775,43 +653,11 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_kernel(DecodeParams 
     qh[v] = il < nql ? p.kh[g0 + il / G].head * G + il % G : 0;
   }
   const int qm = tid < nql ? p.kh[g0 + tid / G].head * G + tid % G : 0;
-  L = L < 0 ? 0 : (L > p.max_ctx ? p.max_ctx : L);
-  // the work item: sequence b, its split, the split length S, and the slot of
-  // the item's partials
-  int b, split, S, pitem;
-  if (p.dyn) {
-    int cnt;
-    S = wave_split_plan(L, p.batch, p.k_lo, p.cap, lane, &cnt) * kStepTokens;
-    if (blockIdx.x == 0 && blockIdx.z == 0 && w == 0) {
-      // the plan of every sequence for the merge pass: its first item (an
-      // exclusive prefix sum of the split counts), split count and length
-      int incl = lane < p.batch ? cnt : 0;
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
-      }
-      if (lane < p.batch)
-        *reinterpret_cast<int4*>(p.plan + 4 * lane) = make_int4(incl - cnt, cnt, L, 0);
-    }
-    pitem = blockIdx.x;
-    // the item's sequence: a scalar walk over the sequences' split counts
-    b = -1;
-    split = pitem;
-    for (int j = 0; j < p.batch; ++j) {
-      const int cj = __builtin_amdgcn_readlane(cnt, j);
-      if (split < cj) { b = j; break; }
-      split -= cj;
-    }
-    if (b < 0) return;                      // past the last item
-    L = __builtin_amdgcn_readlane(L, b);
-  } else {
-    b = blockIdx.y;
-    split = blockIdx.x;
-    S = p.split_len;
-    pitem = b * p.n_split + split;
-  }
-  const int t_begin = split * S;
-  if (t_begin >= L) return;
+  SplitItem item;
+  if (!split_item(p, L, w, lane, &item)) return;
+  const int b = item.b, S = item.S, pitem = item.pitem;
+  L = item.L;
+  const int t_begin = item.split * S;
   const int t_end = min(t_begin + S, L);
   // Paged caches: lane j holds the pool page of the split's j-th page (a split
   // of at most 8192 tokens spans at most 64 pages of at least 128 tokens).
@@ -2077,20 +1923,6 @@ void decode_combine_kernel(CombineParams p) {
 // The file is compiled once per (head_dim, cache precision) with SK_D and SK_QM
 // set, producing the split-kernel instances for that pair, and once with
 // SK_COMMON for the combine kernel and the dispatcher.
-// Raises a kernel's dynamic LDS limit to 160 KiB once per device: `done` holds
-// one bit per device index (indices past 63 set it on every launch).
-static int allow_lds(const void* fn, std::atomic<uint64_t>& done) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return (int)e;
-  const uint64_t bit = dev < 64 ? 1ull << dev : 0;
-  if (bit && (done.load(std::memory_order_acquire) & bit)) return 0;
-  e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  if (e != hipSuccess) return (int)e;
-  done.fetch_or(bit, std::memory_order_release);
-  return 0;
-}
-
 #if defined(SK_D) && defined(SK_QM)
 template <int D, int QM, int CT, int NTW>
 static int launch_split_t(const DecodeParams& p, size_t lds, hipStream_t st) {

@@ -81,7 +81,164 @@ struct starkv_plan {
   uint32_t o_code[STARKV_MAX_KV_HEADS], o_meta[STARKV_MAX_KV_HEADS];
   int32_t lds_bytes;
   RowMap rmap;            // cache rows (contiguous or paged)
+  // polynomial-rotation split kernel, where it applies (see plan_poly)
+  bool poly;
+  PolyShape poly_shape;
+  int32_t poly_n_hg, poly_lds;
+  int32_t poly_first[STARKV_MAX_KV_HEADS + 1], poly_frag_bytes[STARKV_MAX_KV_HEADS];
+  int8_t poly_slot[STARKV_MAX_KV_HEADS][kWaves], poly_tb[STARKV_MAX_KV_HEADS][kWaves];
+  PolyHead poly_kh[STARKV_MAX_KV_HEADS];
+  uint16_t poly_coef[kPolyMaxDegree][48];
 };
+
+namespace {
+
+uint16_t f16_bits(double v) {
+  const _Float16 h = (_Float16)v;
+  uint16_t u;
+  std::memcpy(&u, &h, 2);
+  return u;
+}
+
+// Coefficients c[j][i] of x^i, i < m, in polynomials of degree m - 1 for cos(a_j x) (i
+// even) and sin(a_j x) (i odd) on [-1, 1]: the Chebyshev series cut off there, by
+// discrete orthogonality over 16 nodes (a <= 2.44 leaves nothing beyond degree 24).
+void trig_polynomials(const double* a, int n, int m, double (*c)[kPolyMaxDegree]) {
+  constexpr int N = 16;
+  // node weights of x^i: sum over k of cos(k th) T_k's coefficient of x^i
+  double x[N], wt[N][kPolyMaxDegree] = {};
+  for (int s = 0; s < N; ++s) {
+    const double th = M_PI * (s + 0.5) / N;
+    x[s] = std::cos(th);
+    double tk[kPolyMaxDegree] = {1.0}, tn[kPolyMaxDegree] = {0.0, 1.0};   // T_k, T_{k+1}
+    for (int k = 0; k < m; ++k) {
+      const double f = (k ? 2.0 : 1.0) / N * std::cos(k * th);
+      double t2[kPolyMaxDegree];
+      for (int i = 0; i < m; ++i) {
+        wt[s][i] += f * tk[i];
+        t2[i] = (i ? 2.0 * tn[i - 1] : 0.0) - tk[i];
+      }
+      std::memcpy(tk, tn, sizeof(tk));
+      std::memcpy(tn, t2, sizeof(tn));
+    }
+  }
+  for (int j = 0; j < n; ++j) {
+    for (int i = 0; i < m; ++i) c[j][i] = 0.0;
+    for (int s = 0; s < N / 2; ++s) {          // nodes s and N - 1 - s are opposite
+      const double cs = std::cos(a[j] * x[s]), sn = std::sin(a[j] * x[s]);
+      for (int i = 0; i < m; ++i) c[j][i] += 2.0 * wt[s][i] * (i % 2 ? sn : cs);
+    }
+  }
+}
+
+// Chooses the polynomial-rotation split kernel (split_poly.hip) and its shape.
+//
+// Terms and fast blocks: eight terms serve four query heads per 32-row matrix tile,
+// four terms eight; the first dropped Chebyshev term of the fastest frequency left
+// to the polynomial, 2 J_M(64 w_j), must stay below 2^-12, fp16's rounding of a
+// value below one: 64 w_j <= 2.44 with eight terms, <= 0.46 with four (w_j =
+// theta^(-2j/d); at theta = 5e5, d = 128: one fast block of 16 pairs with eight
+// terms, two with four).  The general kernel stays for more than eight query
+// heads per KV head, rope bases whose frequencies are all fast, value ranks above
+// 512 (accumulators beyond the register file), fp16 caches of ranks above 64 or 256
+// (a lane's prefetched codes), and at most two KV heads per workgroup, where a
+// wave per head leaves waves without key work (measured, one KV head: 4 of 8).
+//
+// Head groups: as few as fit the LDS, balanced by cost; a group of up to four heads
+// gives a head two waves of 64 tokens a step, a larger one a wave of 128.
+bool plan_poly(starkv_plan* P) {
+  const starkv_config& c = P->cfg;
+  const int D = c.head_dim, G = c.n_q_heads / c.n_kv_heads, n_kv = c.n_kv_heads;
+  if (G > 4) return false;
+  PolyShape s;
+  s.m = G <= 4 ? 8 : 4;
+  const double a_max = s.m == 8 ? 2.44 : 0.46;
+  for (s.nhb = 1; s.nhb <= 2; ++s.nhb)
+    if (64.0 * std::pow(c.rope_theta, -2.0 * 16 * s.nhb / D) <= a_max) break;
+  if (s.m == 4) s.nhb = std::max(s.nhb, 2);
+  if (s.nhb > 2 || 32 * s.nhb >= D) return false;
+  const int tiles = (c.value_rank / 16 + kWaves - 1) / kWaves;
+  s.ntw = std::max(tiles, 2);
+  int rmax = 0;
+  for (int g = 0; g < n_kv; ++g) rmax = std::max(rmax, P->key_rank[g]);
+  if (s.ntw > (c.qmode == STARKV_Q_F16 ? 2 : 3) || (c.qmode == STARKV_Q_F16 && rmax > 64)) return false;
+  // (value meta of a step: at most one 16-byte vector per thread)
+  if (P->layout.value_groups * 512 > kThreads * 16) return false;
+  const int ks = (D - 32 * s.nhb) / 16;
+  auto frag_of = [&](int g) { return P->key_rank[g] * (32 * ks + 64 * s.nhb); };
+  auto cost_of = [&](int g) { return 4 + P->key_rank[g] / 16; };
+  const int max_heads = s.m == 8 ? 8 : 4;
+  int by_cost[STARKV_MAX_KV_HEADS];
+  for (int g = 0; g < n_kv; ++g) by_cost[g] = g;
+  std::stable_sort(by_cost, by_cost + n_kv, [&](int x, int y) { return cost_of(x) > cost_of(y); });
+  int members[STARKV_MAX_KV_HEADS][STARKV_MAX_KV_HEADS], count[STARKV_MAX_KV_HEADS];
+  int n_hg = 0, most = 0;
+  for (n_hg = (n_kv + max_heads - 1) / max_heads; n_hg <= n_kv; ++n_hg) {
+    int load[STARKV_MAX_KV_HEADS] = {0}, bytes[STARKV_MAX_KV_HEADS] = {0};
+    for (int h = 0; h < n_hg; ++h) count[h] = 0;
+    for (int i = 0; i < n_kv; ++i) {          // largest first, into the cheapest group
+      const int g = by_cost[i];
+      int best = -1;
+      for (int h = 0; h < n_hg; ++h)
+        if (count[h] < max_heads && (best < 0 || load[h] < load[best])) best = h;
+      members[best][count[best]++] = g;       // (n_hg * max_heads >= n_kv)
+      load[best] += cost_of(g);
+      bytes[best] += frag_of(g);
+    }
+    most = 0;
+    int worst = 0;
+    for (int h = 0; h < n_hg; ++h) {
+      most = std::max(most, count[h]);
+      worst = std::max(worst, bytes[h]);
+    }
+    s.ns = most > 4 ? 4 : 2;
+    s.ct = s.ns == 4 || s.m == 4 ? 2 : 1;
+    if (poly_lds_bytes(s, D, worst, P->layout.value_groups) <= kLdsLimit) {
+      P->poly_lds = poly_lds_bytes(s, D, worst, P->layout.value_groups);
+      break;
+    }
+  }
+  if (n_hg > n_kv || most < 3) return false;
+  P->poly_n_hg = n_hg;
+  const int tb_n = 4 / s.ns;
+  int o = 0;
+  for (int h = 0; h < n_hg; ++h) {
+    P->poly_first[h] = o;
+    int frag = 0, n_units = 0, unit_slot[kWaves], unit_tb[kWaves];
+    for (int i = 0; i < count[h]; ++i, ++o) {
+      const int g = members[h][i];            // costliest first
+      PolyHead& k = P->poly_kh[o];
+      k.code_off = P->layout.key_code_offset[g];
+      k.meta_off = P->layout.key_meta_offset[g];
+      k.head = g;
+      k.rank = P->key_rank[g];
+      k.row_bytes = P->layout.key_row_bytes[g];
+      k.ngroups = P->layout.key_groups[g];
+      k.bk_row = P->bk_row[g];
+      k.frag = frag;
+      frag += frag_of(g);
+      for (int t = 0; t < tb_n; ++t, ++n_units) { unit_slot[n_units] = i; unit_tb[n_units] = t; }
+    }
+    P->poly_frag_bytes[h] = frag;
+    // waves w and w + 4 share a SIMD: the costliest unit is paired with the cheapest
+    for (int w = 0; w < kWaves; ++w) {
+      const int u = w < 4 ? w : 11 - w;
+      P->poly_slot[h][w] = (int8_t)(u < n_units ? unit_slot[u] : -1);
+      P->poly_tb[h][w] = (int8_t)(u < n_units ? unit_tb[u] : 0);
+    }
+  }
+  P->poly_first[n_hg] = o;
+  const int j0 = 16 * s.nhb, nj = D / 2 - j0;
+  double a[48], coef[48][kPolyMaxDegree];
+  for (int j = 0; j < nj; ++j) a[j] = 64.0 * std::pow(c.rope_theta, -2.0 * (j0 + j) / D);
+  trig_polynomials(a, nj, s.m, coef);
+  for (int j = 0; j < nj; ++j)
+    for (int m = 0; m < s.m; ++m) P->poly_coef[m][j] = f16_bits(coef[j][m]);
+  P->poly_shape = s;
+  return true;
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -413,6 +570,7 @@ starkv_status starkv_plan_create(const starkv_config* c, starkv_plan** out) {
     if (lds > P->lds_bytes) P->lds_bytes = lds;
   }
   for (int g = 0; g < c->n_kv_heads; ++g) P->bk_row[g] = info[g].bk_row;
+  P->poly = plan_poly(P);
   *out = P;
   g_last_error.clear();
   return STARKV_OK;
@@ -443,21 +601,20 @@ struct WorkPlan {
   bool dyn;
   int32_t k_lo, cap;
 };
-static WorkPlan work_plan(const starkv_plan* P, int32_t max_ctx) {
+static WorkPlan work_plan(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
   WorkPlan w;
   const int64_t B = P->cfg.batch;
   const int64_t steps = ((int64_t)max_ctx + kStepTokens - 1) / kStepTokens;
   w.dyn = B <= kMaxPlanBatch;
   w.k_lo = (int32_t)std::max<int64_t>(1, (steps + kMaxSplits - 1) / kMaxSplits);
-  const int64_t per_cu = std::max<int64_t>(1, kComputeUnits / P->n_hg);
+  const int64_t per_cu = std::max<int64_t>(1, kComputeUnits / n_hg);
   const int64_t at_max = B * (((int64_t)max_ctx + kMaxSplitTokens - 1) / kMaxSplitTokens);
   w.cap = (int32_t)std::max(per_cu, at_max);
   return w;
 }
 
-int32_t starkv_decode_split_tokens(const starkv_plan* P, int32_t max_ctx) {
-  if (!P || max_ctx < 1) return 0;
-  const WorkPlan wp = work_plan(P, max_ctx);
+static int32_t split_tokens(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
+  const WorkPlan wp = work_plan(P, max_ctx, n_hg);
   if (wp.dyn) {
     // the device plan for max_ctx tokens in every sequence
     const int64_t steps = ((int64_t)max_ctx + kStepTokens - 1) / kStepTokens;
@@ -467,7 +624,7 @@ int32_t starkv_decode_split_tokens(const starkv_plan* P, int32_t max_ctx) {
   }
   // enough splits to give every compute unit a workgroup, at most kMaxSplits
   // per sequence (the combine pass merges up to that many)
-  const int64_t wgs_per_split = (int64_t)P->cfg.batch * P->n_hg;
+  const int64_t wgs_per_split = (int64_t)P->cfg.batch * n_hg;
   int64_t splits = (kComputeUnits + wgs_per_split - 1) / wgs_per_split;
   // and enough that no split exceeds kMaxSplitTokens
   splits = std::max<int64_t>(splits, ((int64_t)max_ctx + kMaxSplitTokens - 1) / kMaxSplitTokens);
@@ -476,6 +633,59 @@ int32_t starkv_decode_split_tokens(const starkv_plan* P, int32_t max_ctx) {
   len = (len + kStepTokens - 1) / kStepTokens * kStepTokens;
   if (len < kStepTokens) len = kStepTokens;
   return (int32_t)len;
+}
+
+// value latent, then m, l, candidate flags, unused, four candidate bounds
+static int part_stride(const starkv_plan* P) { return P->cfg.value_rank + 8; }
+
+// Work items whose partials the workspace holds: the device plan's cap, or
+// every (sequence, split).
+static int64_t part_slots(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
+  const WorkPlan wp = work_plan(P, max_ctx, n_hg);
+  const int32_t len = split_tokens(P, max_ctx, n_hg);
+  return wp.dyn ? wp.cap : (int64_t)P->cfg.batch * ((max_ctx + (int64_t)len - 1) / len);
+}
+
+// Workspace: the split partials [items][H_q][part_stride] fp32, then the
+// rescoring candidates [items][H_q][kCand] (score, token) pairs.
+static int64_t cand_offset(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
+  return align256(part_slots(P, max_ctx, n_hg) * P->cfg.n_q_heads * part_stride(P) * 4);
+}
+
+// Then, for the absorbed output, the normalized value latents as two fp16 parts
+// [2][B][H_q * r_v].
+static int64_t lat_offset(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
+  return cand_offset(P, max_ctx, n_hg) +
+         align256(part_slots(P, max_ctx, n_hg) * P->cfg.n_q_heads * kCand * 8);
+}
+
+// Then the per-sequence work plan the split pass writes for the merge pass
+// [B] (first item, splits, length, 0).
+static int64_t plan_offset(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
+  return lat_offset(P, max_ctx, n_hg) +
+         align256((int64_t)2 * P->cfg.batch * P->cfg.n_q_heads * P->cfg.value_rank * 2);
+}
+
+static int64_t workspace_bytes(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
+  return plan_offset(P, max_ctx, n_hg) + align256((int64_t)16 * P->cfg.batch);
+}
+
+// Workgroups per work item that the work plan counts with: the split kernel's head
+// groups.  The polynomial-rotation kernel needs fewer groups, hence has more
+// items and a larger workspace; where that would exceed the fixed scratch array
+// of the no-allocation entry point and the general kernel's plan does not, the
+// items stay those of the general kernel's plan.
+static int32_t plan_groups(const starkv_plan* P, int32_t max_ctx) {
+  if (!P->poly || P->poly_n_hg >= P->n_hg) return P->poly ? P->poly_n_hg : P->n_hg;
+  const int64_t limit = (int64_t)kScratchBytes;
+  if (workspace_bytes(P, max_ctx, P->poly_n_hg) > limit && workspace_bytes(P, max_ctx, P->n_hg) <= limit)
+    return P->n_hg;
+  return P->poly_n_hg;
+}
+
+int32_t starkv_decode_split_tokens(const starkv_plan* P, int32_t max_ctx) {
+  if (!P || max_ctx < 1) return 0;
+  return split_tokens(P, max_ctx, plan_groups(P, max_ctx));
 }
 
 int32_t starkv_decode_splits(const starkv_plan* P, int32_t max_ctx) {
@@ -488,55 +698,25 @@ starkv_status starkv_decode_describe(const starkv_plan* P, int32_t max_ctx,
                                      starkv_decode_info* out) {
   if (!P || !out) return fail(STARKV_ERR_INVALID_ARG, "plan or out is NULL");
   if (max_ctx < 1) return fail(STARKV_ERR_INVALID_ARG, "max_ctx %d < 1", max_ctx);
-  const WorkPlan wp = work_plan(P, max_ctx);
+  const WorkPlan wp = work_plan(P, max_ctx, plan_groups(P, max_ctx));
   starkv_decode_info d;
   d.head_dim = P->cfg.head_dim;
   d.qmode = P->cfg.qmode;
-  d.score_tiles = P->ct;
-  d.value_tiles = P->ntw;
-  d.head_groups = P->n_hg;
+  d.score_tiles = P->poly ? P->poly_shape.ct : P->ct;
+  d.value_tiles = P->poly ? P->poly_shape.ntw : P->ntw;
+  d.head_groups = P->poly ? P->poly_n_hg : P->n_hg;
   d.device_plan = wp.dyn ? 1 : 0;
   d.k_lo = wp.dyn ? wp.k_lo : 0;
   d.split_tokens = starkv_decode_split_tokens(P, max_ctx);
   d.items = wp.dyn ? wp.cap : P->cfg.batch * starkv_decode_splits(P, max_ctx);
-  d.lds_bytes = P->lds_bytes;
+  d.lds_bytes = P->poly ? P->poly_lds : P->lds_bytes;
   *out = d;
   return STARKV_OK;
 }
 
-// value latent, then m, l, candidate flags, unused, four candidate bounds
-static int part_stride(const starkv_plan* P) { return P->cfg.value_rank + 8; }
-
-// Work items whose partials the workspace holds: the device plan's cap, or
-// every (sequence, split).
-static int64_t part_slots(const starkv_plan* P, int32_t max_ctx) {
-  const WorkPlan wp = work_plan(P, max_ctx);
-  return wp.dyn ? wp.cap : (int64_t)P->cfg.batch * starkv_decode_splits(P, max_ctx);
-}
-
-// Workspace: the split partials [items][H_q][part_stride] fp32, then the
-// rescoring candidates [items][H_q][kCand] (score, token) pairs.
-static int64_t cand_offset(const starkv_plan* P, int32_t max_ctx) {
-  return align256(part_slots(P, max_ctx) * P->cfg.n_q_heads * part_stride(P) * 4);
-}
-
-// Then, for the absorbed output, the normalized value latents as two fp16 parts
-// [2][B][H_q * r_v].
-static int64_t lat_offset(const starkv_plan* P, int32_t max_ctx) {
-  return cand_offset(P, max_ctx) +
-         align256(part_slots(P, max_ctx) * P->cfg.n_q_heads * kCand * 8);
-}
-
-// Then the per-sequence work plan the split pass writes for the merge pass
-// [B] (first item, splits, length, 0).
-static int64_t plan_offset(const starkv_plan* P, int32_t max_ctx) {
-  return lat_offset(P, max_ctx) +
-         align256((int64_t)2 * P->cfg.batch * P->cfg.n_q_heads * P->cfg.value_rank * 2);
-}
-
 size_t starkv_decode_workspace_bytes(const starkv_plan* P, int32_t max_ctx) {
   if (!P || max_ctx < 1) return 0;
-  return (size_t)(plan_offset(P, max_ctx) + align256((int64_t)16 * P->cfg.batch));
+  return (size_t)workspace_bytes(P, max_ctx, plan_groups(P, max_ctx));
 }
 
 static starkv_status check_common(const starkv_plan* P, int32_t max_ctx, size_t ws_bytes,
@@ -587,40 +767,57 @@ starkv_status starkv_decode_split(const starkv_plan* P, const void* cache, const
                                   ws_bytes, false);
   if (st != STARKV_OK) return st;
   const starkv_config& c = P->cfg;
-  DecodeParams p;
-  std::memset(&p, 0, sizeof(p));
-  p.cache = static_cast<const uint8_t*>(cache);
-  p.q = q;
-  p.bk = static_cast<const uint16_t*>(B_k);
-  p.ctx_len = ctx_len_dev;
-  p.part = static_cast<float*>(ws);
-  p.cand = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + cand_offset(P, max_ctx));
-  p.plan = reinterpret_cast<int32_t*>(static_cast<uint8_t*>(ws) + plan_offset(P, max_ctx));
-  p.batch = c.batch;
-  p.n_q = c.n_q_heads;
-  p.n_kv = c.n_kv_heads;
-  p.group_q = c.n_q_heads / c.n_kv_heads;
-  p.rmap = P->rmap;
-  p.max_ctx = max_ctx;
-  p.split_len = starkv_decode_split_tokens(P, max_ctx);
-  p.n_split = starkv_decode_splits(P, max_ctx);
-  {
-    const WorkPlan wp = work_plan(P, max_ctx);
+  const int32_t n_hg = plan_groups(P, max_ctx);
+  const WorkPlan wp = work_plan(P, max_ctx, n_hg);
+  // the fields that both split kernels take
+  auto common = [&](auto& p) {
+    std::memset(&p, 0, sizeof(p));
+    p.cache = static_cast<const uint8_t*>(cache);
+    p.q = q;
+    p.bk = static_cast<const uint16_t*>(B_k);
+    p.ctx_len = ctx_len_dev;
+    p.part = static_cast<float*>(ws);
+    p.cand = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) + cand_offset(P, max_ctx, n_hg));
+    p.plan = reinterpret_cast<int32_t*>(static_cast<uint8_t*>(ws) + plan_offset(P, max_ctx, n_hg));
+    p.batch = c.batch;
+    p.n_q = c.n_q_heads;
+    p.n_kv = c.n_kv_heads;
+    p.group_q = c.n_q_heads / c.n_kv_heads;
+    p.rmap = P->rmap;
+    p.max_ctx = max_ctx;
+    p.split_len = starkv_decode_split_tokens(P, max_ctx);
+    p.n_split = starkv_decode_splits(P, max_ctx);
     p.dyn = wp.dyn;
     p.k_lo = wp.k_lo;
     p.cap = wp.cap;
+    p.q_bf16 = c.q_dtype == STARKV_DT_BF16;
+    p.score_scale = (float)(1.4426950408889634 / std::sqrt((double)c.head_dim));
+    p.log2_theta = std::log2(c.rope_theta);
+    p.v_code_off = P->layout.value_code_offset;
+    p.v_meta_off = P->layout.value_meta_offset;
+    p.rv = c.value_rank;
+    p.v_ro = P->layout.value_outlier_channels;
+    p.v_ng8 = (p.v_ro + 31) / 32;
+    p.v_ng = P->layout.value_groups;
+    p.v_row_bytes = P->layout.value_row_bytes;
+    p.part_stride = part_stride(P);
+  };
+  if (P->poly) {
+    PolyParams p;
+    common(p);
+    p.n_hg = P->poly_n_hg;
+    std::memcpy(p.hg_first, P->poly_first, sizeof(p.hg_first));
+    std::memcpy(p.hg_frag_bytes, P->poly_frag_bytes, sizeof(p.hg_frag_bytes));
+    std::memcpy(p.wave_slot, P->poly_slot, sizeof(p.wave_slot));
+    std::memcpy(p.wave_tb, P->poly_tb, sizeof(p.wave_tb));
+    std::memcpy(p.kh, P->poly_kh, sizeof(p.kh));
+    std::memcpy(p.coef, P->poly_coef, sizeof(p.coef));
+    const int e = launch_decode_split_poly(p, P->poly_shape, c.head_dim, c.qmode, P->poly_lds,
+                                           static_cast<void*>(stream));
+    return hip_status(e, "decode_split launch");
   }
-  p.q_bf16 = c.q_dtype == STARKV_DT_BF16;
-  p.score_scale = (float)(1.4426950408889634 / std::sqrt((double)c.head_dim));
-  p.log2_theta = std::log2(c.rope_theta);
-  p.v_code_off = P->layout.value_code_offset;
-  p.v_meta_off = P->layout.value_meta_offset;
-  p.rv = c.value_rank;
-  p.v_ro = P->layout.value_outlier_channels;
-  p.v_ng8 = (p.v_ro + 31) / 32;
-  p.v_ng = P->layout.value_groups;
-  p.v_row_bytes = P->layout.value_row_bytes;
-  p.part_stride = part_stride(P);
+  DecodeParams p;
+  common(p);
   p.n_hg = P->n_hg;
   std::memcpy(p.hg_first, P->hg_first, sizeof(p.hg_first));
   std::memcpy(p.hg_frags, P->hg_frags, sizeof(p.hg_frags));
@@ -659,10 +856,11 @@ static void combine_params(const starkv_plan* P, const void* cache, const void* 
                            int32_t max_ctx, void* out, void* ws, CombineParams& p) {
   const starkv_config& c = P->cfg;
   const starkv_layout& L = P->layout;
+  const int32_t n_hg = plan_groups(P, max_ctx);
   std::memset(&p, 0, sizeof(p));
   p.part = static_cast<const float*>(ws);
-  p.cand = reinterpret_cast<const float2*>(static_cast<const uint8_t*>(ws) + cand_offset(P, max_ctx));
-  p.plan = reinterpret_cast<const int32_t*>(static_cast<const uint8_t*>(ws) + plan_offset(P, max_ctx));
+  p.cand = reinterpret_cast<const float2*>(static_cast<const uint8_t*>(ws) + cand_offset(P, max_ctx, n_hg));
+  p.plan = reinterpret_cast<const int32_t*>(static_cast<const uint8_t*>(ws) + plan_offset(P, max_ctx, n_hg));
   p.bv = static_cast<const uint16_t*>(B_v);
   p.bk = static_cast<const uint16_t*>(B_k);
   p.cache = static_cast<const uint8_t*>(cache);
@@ -678,7 +876,7 @@ static void combine_params(const starkv_plan* P, const void* cache, const void* 
   p.split_len = starkv_decode_split_tokens(P, max_ctx);
   p.n_split = starkv_decode_splits(P, max_ctx);
   {
-    const WorkPlan wp = work_plan(P, max_ctx);
+    const WorkPlan wp = work_plan(P, max_ctx, n_hg);
     p.dyn = wp.dyn;
     p.k_lo = wp.k_lo;
     p.cap = wp.cap;
@@ -764,7 +962,7 @@ starkv_status starkv_decode_combine_absorbed(const starkv_plan* P, const void* c
   if (st != STARKV_OK) return st;
   st = check_absorbed(P, W_abs, d_out, out);
   if (st != STARKV_OK) return st;
-  uint16_t* lat = reinterpret_cast<uint16_t*>(static_cast<uint8_t*>(ws) + lat_offset(P, max_ctx));
+  uint16_t* lat = reinterpret_cast<uint16_t*>(static_cast<uint8_t*>(ws) + lat_offset(P, max_ctx, plan_groups(P, max_ctx)));
   CombineParams cp;
   combine_params(P, cache, q, B_k, nullptr, ctx_len_dev, max_ctx, nullptr, ws, cp);
   cp.lat = lat;

@@ -97,6 +97,49 @@ struct DecodeParams {
   uint32_t o_code[STARKV_MAX_KV_HEADS], o_meta[STARKV_MAX_KV_HEADS];
 };
 
+// One KV head as seen by the polynomial-rotation split kernel.
+struct PolyHead {
+  int64_t code_off, meta_off;  // key planes (bytes)
+  int32_t head;                // KV head (query heads head*G .. head*G + G - 1)
+  int32_t rank;
+  int32_t row_bytes, ngroups;
+  int32_t bk_row;              // first row of this head in B_k
+  int32_t frag;                // byte offset of its up-projection operands in LDS
+};
+
+constexpr int kPolyMaxDegree = 8;   // polynomial coefficients per RoPE frequency
+
+// The polynomial-rotation split kernel (split_poly.hip).  Fields as in
+// DecodeParams where named alike.
+struct PolyParams {
+  const uint8_t* cache;
+  const void* q;
+  const uint16_t* bk;
+  const int32_t* ctx_len;
+  float* part;
+  float2* cand;
+  int32_t* plan;
+  int32_t batch, n_q, n_kv, group_q;
+  RowMap rmap;
+  int32_t max_ctx, split_len, n_split;
+  int32_t dyn, k_lo, cap;
+  int32_t q_bf16;
+  float score_scale;
+  double log2_theta;
+  int64_t v_code_off, v_meta_off;
+  int32_t rv, v_ro, v_ng8, v_ng, v_row_bytes;
+  int32_t part_stride;
+  int32_t n_hg;
+  int32_t hg_first[STARKV_MAX_KV_HEADS + 1];
+  int32_t hg_frag_bytes[STARKV_MAX_KV_HEADS];
+  // per head group, the work of every wave: slot within the group (-1: no key
+  // work) and token range of the step
+  int8_t wave_slot[STARKV_MAX_KV_HEADS][kWaves], wave_tb[STARKV_MAX_KV_HEADS][kWaves];
+  PolyHead kh[STARKV_MAX_KV_HEADS];
+  // fp16 coefficients [m][j - j0] of cos (m even) and sin (m odd) of 64 w_j x
+  uint16_t coef[kPolyMaxDegree][48];
+};
+
 constexpr int kCand = 64;      // rescoring candidates per (sequence, split, query head):
                                // the top two scores of each of 32 lane slots
 // a candidate is rescored when its share of the softmax times (1 + |score|)
@@ -185,6 +228,15 @@ int split_lds_bytes(int frags, int nql, int head_dim, int ct, int raw_bytes, int
                     int v_row_bytes);
 int launch_decode_split_ntw(const DecodeParams& p, int head_dim, int qmode, int ct, int ntw,
                             size_t lds_bytes, void* stream);
+// Shape of a polynomial-rotation instance: high frequency blocks (16 RoPE pairs
+// each, rebuilt and rotated per token), polynomial terms of the others, tokens
+// per lane of a 128-token step, 16-query tiles, value tiles per wave.
+struct PolyShape {
+  int32_t nhb, m, ns, ct, ntw;
+};
+int poly_lds_bytes(const PolyShape& s, int head_dim, int frag_bytes, int v_ng);
+int launch_decode_split_poly(const PolyParams& p, const PolyShape& s, int head_dim, int qmode,
+                             size_t lds_bytes, void* stream);
 int launch_decode_combine(const CombineParams& p, void* stream);
 // The no-allocation decode path's workspace: a fixed device array of kScratchBytes
 // per device.  *out gets its device address on the current device (taken once).
