@@ -47,31 +47,32 @@ __device__ __forceinline__ f16v mfma32(h8 a, h8 b, f16v c) {
 }
 #endif
 
-// LDS layout (byte offsets), identical on the host.
+// LDS layout (byte offsets), identical on the host.  The areas whose size depends on
+// the model come last, so that the other offsets are constants of an instance.
 struct PolyLds {
-  int frag, q, zero, coef, cs, red, alpha, flag, meta, pbuf, total;
-  int meta_stride, p_stride;        // one of the two buffers
+  int q, zero, coef, cs, red, alpha, flag, qmap, pbuf, meta;
+  int p_stride;                     // one of the two probability buffers
   static constexpr int kBlockPad = 64;
 };
 __host__ __device__ constexpr int poly_p_block(int ct) { return 4 * ct * 256 + PolyLds::kBlockPad; }
-__host__ __device__ inline PolyLds poly_lds(int frag_bytes, int D, int nhb, int m, int ct, int v_ng) {
-  PolyLds L;
+__host__ __device__ constexpr PolyLds poly_lds(int D, int nhb, int m, int ct) {
+  PolyLds L{};
   const int qs = (D + 8) * 2, ks = (D - 32 * nhb) / 16;
-  L.frag = 0;
-  L.q = frag_bytes;
+  L.q = 0;
   L.zero = L.q + kWaves * (32 / m) * qs;
   L.coef = L.zero + qs;
   L.cs = L.coef + ks * 2 * m * 16;
   L.red = L.cs + nhb * 8192;
   L.alpha = L.red + ct * 16 * 2 * 4;
   L.flag = L.alpha + ct * 16 * 4;
-  L.meta = L.flag + 2 * kWaves * 4;
-  L.meta_stride = 4 * v_ng * 128;
-  L.pbuf = L.meta + 2 * L.meta_stride;
+  L.qmap = L.flag + 2 * kWaves * 4;
+  L.pbuf = L.qmap + ct * 16 * 4;
   L.p_stride = 4 * poly_p_block(ct);
-  L.total = L.pbuf + 2 * L.p_stride;
+  L.meta = L.pbuf + 2 * L.p_stride;
   return L;
 }
+// two buffers of value meta, then the up-projection operands
+__host__ __device__ constexpr int poly_meta_bytes(int v_ng) { return 4 * v_ng * 128; }
 
 #if defined(SK_D) && defined(SK_QM)
 
@@ -117,13 +118,20 @@ __host__ __device__ constexpr int meta_pair(int qm, int np, int p) {
       return o;
   return p;
 }
-// Channel e of an operand's eight: 8-bit and fp16 chunks in order, 4- and 3-bit
-// ones 0,4,1,5,2,6,3,7, the 4-bit half of an 8/4 pair 0,2,4,6,1,3,5,7.
-__device__ __forceinline__ int chunk_channel(int qm, int np, int c, int e) {
-  const PairKind k = pair_kind(qm, np, c / 2);
-  if (k == kF16 || k == k8 || (k == k84 && c % 2 == 0)) return e;
-  if (k == k84) return e < 4 ? 2 * e : 2 * (e - 4) + 1;
-  return e % 2 == 0 ? e / 2 : 4 + e / 2;
+// Order of an operand's eight channels: 8-bit and fp16 chunks in order (0), 4- and
+// 3-bit ones 0,4,1,5,2,6,3,7 (1), the 4-bit half of an 8/4 pair 0,2,4,6,1,3,5,7 (2).
+// The last two are each other's inverse.
+__device__ __forceinline__ int chunk_order(int qm, int np, int c) {
+  if (qm == STARKV_Q_F16) return 0;
+  if (qm != STARKV_Q_MIX8_4) return 1;
+  const int n = wide_chunks(qm, np);
+  return c < n ? 0 : (n & 1) && c == n ? 2 : 1;
+}
+__device__ __forceinline__ int chunk_channel(int order, int e) {      // channel of element e
+  return order == 0 ? e : order == 1 ? (e >> 1) + 4 * (e & 1) : ((e & 3) << 1) + (e >> 2);
+}
+__device__ __forceinline__ int chunk_element(int order, int ch) {     // element of channel ch
+  return chunk_channel(order ? 3 - order : 0, ch);
 }
 
 // (code pair + offset) -> fp16: the codes sit in the mantissa of `base`, whose unit
@@ -184,6 +192,9 @@ __device__ __forceinline__ uint32_t pick(uint32_t mask, uint32_t a, uint32_t b) 
   return (a & ~mask) | (b & mask);
 }
 
+// Pairs up to which a head's lane addresses stay in registers across the step loop.
+constexpr int kKeepPairs = 2;
+
 // A vector at a wave-uniform base plus a 32-bit lane offset.
 template <class T>
 __device__ __forceinline__ T load_at(const uint8_t* base, uint32_t off) {
@@ -198,9 +209,8 @@ __device__ __forceinline__ void load_keys(const uint8_t* code, const uint8_t* me
                                           KeyRaw<QM, NS, NP>& raw) {
   constexpr uint32_t RUN = 16 / NS;      // lanes per 16-token block
   constexpr uint32_t WB = wide_bytes(QM), NB = narrow_bytes(QM);
-  // lane offsets are formed here, step by step, instead of being kept in registers
-  // for every pair count
-  asm volatile("" : "+v"(cl), "+v"(hf));
+  // (with many pairs the lane offsets are formed in every step, see poly_scores)
+  if (NP > kKeepPairs) asm volatile("" : "+v"(cl), "+v"(hf));
   const uint32_t t = cl % RUN;
   const uint32_t blk_off = cl / RUN * (16 * row_bytes);
   const uint32_t meta_off = cl / RUN * (64 * ngroups) + t * NS * 4;
@@ -289,7 +299,7 @@ __device__ __forceinline__ h8 key_operand(const KeyRaw<QM, NS, NP>& raw, int p, 
 // ------------------------------------------------------------------ kernel
 // LDS areas of a wave (wave-uniform).
 struct PolyWave {
-  const uint8_t* low;      // B_k rows of the slow dimensions, [step][half][row][8 dims]
+  const uint8_t* low;      // B_k rows of the slow dimensions, [step][half][row + 1 pad][8 dims]
   const uint8_t* high;     // B_k of the fast dimensions, [block][pair][half][row][8 channels]
   const uint8_t* q;        // the wave's query rows
   const uint8_t* zero;     // a row of zeros
@@ -304,11 +314,12 @@ __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, 
   constexpr int KS = (D - 32 * NHB) / 16;    // 16-dimension steps of the slow dimensions
   constexpr int NT2 = (NP + 1) / 2;
   constexpr int R = 16 * NP;
-  // The lane's addresses are formed here in every step: kept across the loop they
-  // would be spilled, and a reload from scratch waits for all loads in flight.
-  asm volatile("" : "+v"(lane));
+  // With many pairs the lane's addresses are formed in every step: kept across the
+  // loop they would be spilled, and a reload from scratch waits for all loads in
+  // flight.
+  if (NP > kKeepPairs) asm volatile("" : "+v"(lane));
   const int cl = lane & 31, hf = lane >> 5;
-  const int row_a = hf * R + cl, row_b = hf * R + (cl & 15);
+  const int row_a = hf * (R + 1) + cl, row_b = hf * (R + 1) + (cl & 15);
   const uint8_t *qsrc_lo, *qsrc_hi, *qop, *coef, *cs;
   {
     // row (query i, term m) of the products with W_m
@@ -339,7 +350,7 @@ __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, 
       const h8 xv = qv * cv;
 #pragma unroll
       for (int t = 0; t < NT2; ++t) {
-        const int row = (32 * t + 32 <= R ? row_a : row_b) + ks * 2 * R + 32 * t;
+        const int row = (32 * t + 32 <= R ? row_a : row_b) + ks * 2 * (R + 1) + 32 * t;
         const h8 a = *reinterpret_cast<const h8*>(W.low + row * 16);
         acc[t] = mfma32(a, xv, acc[t]);
       }
@@ -417,9 +428,45 @@ __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, 
     for (int iq = 0; iq < 16 / M; ++iq) asm volatile("" : "+v"(sc[s][iq]));
 }
 
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
+                                                               0xF, 0xF, true));
+}
+// reductions over the lane's 8, 16 or 32 neighbours (a power-of-two group), to all of them
+template <int N, class Op>
+__device__ __forceinline__ float reduce_lanes(float v, Op op) {
+  v = op(v, dpp<0xB1>(v));                       // quad_perm 1,0,3,2
+  v = op(v, dpp<0x4E>(v));                       // quad_perm 2,3,0,1
+  v = op(v, dpp<0x141>(v));                      // row_half_mirror
+  if (N > 8) v = op(v, dpp<0x140>(v));           // row_mirror
+  if (N > 16) v = op(v, __shfl_xor(v, 16));
+  return v;
+}
+
+// Chebyshev nodes cos(pi (k + 1/2) / 10), k < 5, and the weights of a function's values
+// there in the monomial coefficients of its series: 2 (2 - [i = 0]) / 10 sum_i cos(i th_k)
+// T_i's coefficient of x^m, i < M.
+__device__ constexpr float kNodes[5] = {0.987688341f, 0.891006524f, 0.707106781f, 0.4539905f,
+                                        0.156434465f};
+__device__ constexpr float kWeights8[5][8] = {
+    {-0.0919299097f, -0.53109233f, 2.40404465f, 5.93814338f, -8.69662246f, -15.813291f, 7.52365123f, 11.6221568f},
+    {0.221701708f, 1.51999504f, -5.38852433f, -16.2170694f, 17.2714307f, 39.7229543f, -12.1735234f, -25.2848215f},
+    {-0.2f, -2.2627417f, 3.2f, 20.3646753f, -3.2f, -36.2038672f, 0.0f, 18.1019336f},
+    {-0.0689153034f, 2.34301927f, 7.3662331f, -3.73302358f, -19.2491395f, -2.48278063f, 12.1735234f, 4.00472231f},
+    {1.13914351f, 4.51639422f, -7.58175341f, -26.3417852f, 13.8743312f, 44.4425757f, -7.52365123f, -22.809767f}};
+__device__ constexpr float kWeights4[5][4] = {
+    {-0.180422607f, -0.674132493f, 0.760845213f, 1.42561044f},
+    {-0.0351141009f, 0.168681252f, 0.470228202f, 0.250295144f},
+    {0.2f, 1.13137085f, 0.0f, -1.13137085f},
+    {0.435114101f, 1.36682221f, -0.470228202f, -1.58030134f},
+    {0.580422607f, 0.607362386f, -0.760845213f, -0.7263848f}};
+
 // NHB: fast blocks of 16 RoPE pairs; M: polynomial terms; NS: tokens per lane;
-// CT: 16-query tiles; NTW: 16-channel value tiles per wave.
-template <int D, int QM, int NHB, int M, int NS, int CT, int NTW>
+// CT: 16-query tiles; NTW: 16-channel value tiles per wave; MAXP: most pairs (of 8
+// channels) of a key head (heads of up to 64 channels have instances of their own, whose
+// registers the longer heads' loops do not crowd).
+template <int D, int QM, int NHB, int M, int NS, int CT, int NTW, int MAXP>
 __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyParams p) {
   extern __shared__ __align__(16) uint8_t smem[];
   constexpr int HALF = D / 2;
@@ -429,22 +476,67 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   constexpr int NQ = 16 / M;                // queries per lane
   constexpr int MQ = 32 / M;                // query rows per wave
   constexpr int TB = 4 / NS;                // waves per head
-  constexpr int MAXP = QM == STARKV_Q_F16 ? 4 : D / 16;
   constexpr int PB = poly_p_block(CT);
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cl = lane & 31, hf = lane >> 5;
   const int col = lane & 15, quad = lane >> 4;
+  // All kernel arguments at once (see PolyParams).
   const int hg = blockIdx.z;
-  const int g0 = p.hg_first[hg], g1 = p.hg_first[hg + 1];
-  const int G = p.group_q;
-  const int nql = (g1 - g0) * G;
+  const PolyWaveInfo info = p.wave[hg][w];
+  const int G = p.group_q, nql = p.nql[hg];
+  asm volatile("" :: "s"(p.cache), "s"(p.q), "s"(p.bk), "s"(p.ctx_len), "s"(p.part), "s"(p.plan),
+               "s"(p.v_code_off), "s"(p.v_meta_off), "s"(p.log2_theta), "s"(p.rmap.table),
+               "s"(p.batch), "s"(p.n_q), "s"(p.max_ctx), "s"(p.dyn), "s"(p.cap), "s"(p.rv),
+               "s"(p.v_row_bytes), "s"(p.part_stride), "s"(info.code_off), "s"(info.rank),
+               "s"(info.slot), "s"(nql));
 
   // ---------------------------------------------------------------- prologue
+  // Loads that need no work item are issued before the context lengths are waited
+  // for: the head's B_k rows.
+  const int l_ctx = p.dyn ? (lane < p.batch ? p.ctx_len[lane] : 0) : p.ctx_len[blockIdx.y];
+  constexpr PolyLds LL = poly_lds(D, NHB, M, CT);
+  const int vmeta_bytes = poly_meta_bytes(p.v_ng);
+  uint8_t* frag = smem + LL.meta + 2 * vmeta_bytes + info.frag;
+  const int slot = info.slot, tb = info.tb;
+  const bool has = info.has != 0;
+  const int R = info.rank, np = R / 16;
+  const int row_bytes = info.row_bytes, ngroups = info.ngroups;
+  const uint8_t* code_plane = p.cache + ((uint64_t)info.code_off << 8);
+  const uint8_t* meta_plane = p.cache + ((uint64_t)info.meta_off << 8);
+  const int qj = lane & (HALF - 1);
+  // B_k rows of the slow dimensions: lane (row lane / VPR, vector lane % VPR) of RPI
+  // rows per load, the head's waves taking turns
+  constexpr int VPR = D / 8, RPI = 64 / VPR;
+  constexpr int kBkBatch = 64 / RPI / TB;    // 64 rows
+  const int bk_row = lane / VPR, bk_vec = lane % VPR;
+  const uint16_t* bk = p.bk + (int)info.bk_row * D;
+  u4 bkv[kBkBatch];
+  auto load_bk = [&](int r0) {
+#pragma unroll
+    for (int k = 0; k < kBkBatch; ++k) {
+      const int r = min(r0 + RPI * (tb + TB * k), R - RPI) + bk_row;   // (ranks are multiples of 16)
+      bkv[k] = *reinterpret_cast<const u4*>(bk + r * D + 8 * bk_vec);
+    }
+  };
+  // B_k of the fast dimensions: lane (chunk lane / 4, vector lane % 4: low 0..7, low
+  // 8..15, high 0..7, high 8..15 of a block), eight channels of eight dimensions
+  // each; the head's waves take turns over the blocks
+  u4 fast[8];
+  const int fc = min(lane >> 2, R / 8 - 1);
+  const int f_order = chunk_order(QM, np, fc);
+  auto load_fast = [&](int blk) {
+    const uint16_t* src = bk + 16 * blk + 8 * (lane & 1) + (lane & 2 ? HALF : 0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      fast[e] = *reinterpret_cast<const u4*>(src + (8 * fc + chunk_channel(f_order, e)) * D);
+  };
+  if (has) {
+    load_bk(0);
+    load_fast(NHB > 1 ? tb & (NHB - 1) : 0);
+  }
   SplitItem item;
-  if (!split_item(p, p.dyn ? (lane < p.batch ? p.ctx_len[lane] : 0) : p.ctx_len[blockIdx.y], w, lane,
-                  &item))
-    return;
+  if (!split_item(p, l_ctx, w, lane, &item)) return;
   const int b = item.b;
   const int t_begin = item.split * item.S;
   const int t_end = min(t_begin + item.S, item.L);
@@ -463,17 +555,6 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     const int pg = __builtin_amdgcn_readlane(l_page, min((t >> p.rmap.shift) - pg_first, 63));
     return ((int64_t)pg << p.rmap.shift) + (t & ((1 << p.rmap.shift) - 1));
   };
-  const PolyLds LL = poly_lds(p.hg_frag_bytes[hg], D, NHB, M, CT, p.v_ng);
-  const int slot = p.wave_slot[hg][w];       // -1: no head
-  const int tb = p.wave_tb[hg][w];
-  const bool has = slot >= 0;
-  const PolyHead& kh = p.kh[g0 + (has ? slot : 0)];
-  const int np = kh.rank / 16;
-  const int row_bytes = kh.row_bytes, ngroups = kh.ngroups;
-  const uint8_t* code_plane = p.cache + kh.code_off;
-  const uint8_t* meta_plane = p.cache + kh.meta_off;
-
-
   // value tiles of this wave: lane (channel col, 32-token block quad)
   const int NT = p.rv / 16;
   uint32_t v_off[NTW];
@@ -519,7 +600,6 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   // value meta of a step: loaded into registers a step ahead, written to LDS before
   // the step's barrier (a buffer per parity: the other one may still be read)
   constexpr int MW = 1;
-  const int vmeta_bytes = 4 * p.v_ng * 128;
   u4 vmr[MW];
   auto load_vmeta = [&](int step) {
     const uint8_t* src = p.cache + p.v_meta_off + (step_row(step) >> 5) * p.v_ng * 128;
@@ -530,7 +610,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     }
   };
   auto store_vmeta = [&](int step) {
-    uint8_t* dst = smem + LL.meta + (step & 1) * LL.meta_stride;
+    uint8_t* dst = smem + LL.meta + (step & 1) * vmeta_bytes;
 #pragma unroll
     for (int k = 0; k < MW; ++k) {
       const int o = (tid + k * kThreads) * 16;
@@ -540,112 +620,136 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   if (QM != STARKV_Q_F16) load_vmeta(0);
   load_values(0);
 
-  // B_k operands of the head, shared by its waves.  Slow dimensions: row i =
-  // channel of accumulator row i (see poly_scores), eight consecutive dimensions
-  // per 16-byte vector, copied straight into LDS; fast dimensions: transposed,
-  // eight channels of one dimension per vector.
-  const uint8_t* frag = smem + LL.frag + kh.frag;
-  const int R = kh.rank;
-  const int low_bytes = R * KS * 32;
-  if (has) {
-    const uint16_t* bk = p.bk + (int64_t)kh.bk_row * D;
-    uint8_t* low = smem + LL.frag + kh.frag;
-    for (int v = tb; v < KS * 2; v += TB) {
-      const int ks = v >> 1, kc = v & 1;
-      const int dim = (ks < KS / 2 ? J0 + 16 * ks : HALF + J0 + 16 * (ks - KS / 2)) + 8 * kc;
-      for (int r0 = 0; r0 < R; r0 += 64) {
-        const int row = r0 + lane;
-        if (row < R) {
-          const int rho = row & 31, rr = 4 * (rho >> 3) + (rho & 3);
-          const int c = 2 * (2 * (row >> 5) + (rr >> 3)) + ((rho >> 2) & 1);   // chunk
-          const int ch = 8 * c + chunk_channel(QM, np, c, rr & 7);
-          __builtin_amdgcn_global_load_lds(bk + ch * D + dim, low + ((ks * 2 + kc) * R + r0) * 16, 16, 0, 0);
-        }
-      }
-    }
-    uint8_t* high = low + low_bytes;
-    for (int f = tb; f < NHB * np; f += TB) {
-      const int blk = f / np, pr = f % np;
-      const int c = 2 * pr + hf;
-      const int dim = (cl < 16 ? 0 : HALF - 16) + 16 * blk + cl;
-      uint32_t e8[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) e8[e] = bk[(8 * c + chunk_channel(QM, np, c, e)) * D + dim];
-      u4 v;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = e8[2 * k] | (e8[2 * k + 1] << 16);
-      *reinterpret_cast<u4*>(high + (f * 64 + lane) * 16) = v;
-    }
-  }
   // Queries: lane j holds RoPE pair j of the head's queries (with 32 pairs, the two
   // halves of the wave share them), the rotation of its base position and by one
   // step.  A row in LDS: D dimensions, the fast ones in the order of the rotated
   // key operand.
   constexpr int QL = D == 128 ? MQ : MQ / 2;
-  const int qj = lane & (HALF - 1);
   auto qrow = [&](int k) { return D == 128 ? k : (lane >> 5) + 2 * k; };
-  float ql[QL], qh[QL];
-  float2 rot, rot_step;
+  uint16_t q_lo[QL], q_hi[QL];
+#pragma unroll
+  for (int k = 0; k < QL; ++k) {             // (rows past the head's queries repeat the last)
+    const uint16_t* qs = static_cast<const uint16_t*>(p.q) +
+                         ((int64_t)b * p.n_q + info.head * G + min(qrow(k), G - 1)) * D;
+    q_lo[k] = qs[qj];
+    q_hi[k] = qs[qj + HALF];
+  }
   uint8_t* qbase = smem + LL.q + w * MQ * QSB;
   uint8_t* zero = smem + LL.zero;
-  {
-    const double om = exp2(-(2.0 * qj / D) * p.log2_theta);
-    auto turn = [&](double t) {
-      double a = t * om;
-      a -= 6.283185307179586476925286766559 * floor(a * 0.15915494309189533576888376337251);
-      double sa, ca;
-      sincos(a, &sa, &ca);
-      return make_float2((float)ca, (float)sa);
-    };
-    rot = turn((double)(t_begin + 64));
-    rot_step = turn((double)kStepTokens);
+  int* qmap = reinterpret_cast<int*>(smem + LL.qmap);         // query head of a probability row
+  // turns per token of the lane's RoPE pair, theta^(-2j/D) / (2 pi)
+  const double turn = 0.15915494309189533576888376337251 * exp2(-(2.0 * qj / D) * p.log2_theta);
+  // Polynomial coefficients of the slow pairs, [slow step][half of it][m][8 dims]: the
+  // low dimensions of the pairs, then the high ones, whose odd terms are negated
+  // (q'_j k_j+h is subtracted).  Wave m forms x^m's: the Chebyshev series of cos (m
+  // even) or sin (m odd) of 64 w_j x, cut off at degree M - 1, by discrete
+  // orthogonality over ten nodes (five of either sign: the weights are doubled;
+  // 64 w_j <= 2.44 leaves nothing the nodes cannot tell apart).
+  if (w < M && lane >= J0 && lane < HALF) {
+    const float a = 64.0f * (float)(6.283185307179586476925286766559 * turn);
+    float c = 0.0f;
 #pragma unroll
-    for (int k = 0; k < QL; ++k) {
-      const int i = qrow(k);
-      ql[k] = qh[k] = 0.0f;
-      if (has && i < G) {
-        const uint16_t* qs = static_cast<const uint16_t*>(p.q) + ((int64_t)b * p.n_q + kh.head * G + i) * D;
-        ql[k] = load_qf(qs, qj, p.q_bf16) * p.score_scale;
-        qh[k] = load_qf(qs, qj + HALF, p.q_bf16) * p.score_scale;
-      }
-    }
-    // rotations of the fast pairs for the 128 token offsets of a step: vector
-    // (block, token range, s, cos | sin, half, lane), 8 frequencies each
-    for (int it = tid; it < NHB * 256; it += kThreads) {
-      const int l = it & 63, rest = it >> 6;      // rest = (block, token range, s)
-      const int s = rest % NS, r2 = rest / NS, tr = r2 % TB, blk = r2 / TB;
-      const float u = (float)(32 * NS * tr + NS * (l & 31) + s - 64);
-      u4 cv, sv;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        float cc[2], ss[2];
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int r = 2 * k + e;
-          const int j = 16 * blk + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
-          const float omj = (float)exp2(-(2.0 * j / D) * p.log2_theta);
-          sincosf(u * omj, &ss[e], &cc[e]);
-        }
-        cv[k] = as_u32(__builtin_convertvector((f2){cc[0], cc[1]}, h2));
-        sv[k] = as_u32(__builtin_convertvector((f2){ss[0], ss[1]}, h2));
-      }
-      u4* dst = reinterpret_cast<u4*>(smem + LL.cs) + rest * 128 + l;
-      dst[0] = cv;
-      dst[64] = sv;
-    }
-  }
-  // polynomial coefficients [slow step][half][m][8 dims]; the odd terms of the high
-  // dimensions enter with the other sign (q'_j k_j+h is subtracted)
-  for (int it = tid; it < KS * 2 * M * 8; it += kThreads) {
-    const int e = it & 7, m = (it >> 3) % M, kk = (it >> 3) / M, ks = kk >> 1, kc = kk & 1;
-    const int j = 16 * (ks < KS / 2 ? ks : ks - KS / 2) + 8 * kc + e;
-    reinterpret_cast<uint16_t*>(smem + LL.coef)[it] =
-        p.coef[m][j] ^ ((m & 1) && ks >= KS / 2 ? 0x8000u : 0u);
+    for (int k = 0; k < 5; ++k)
+      c += (M == 8 ? kWeights8[k][w] : kWeights4[k][w & 3]) *
+           (w & 1 ? sinf(a * kNodes[k]) : cosf(a * kNodes[k]));
+    const int j = lane - J0;
+    _Float16* dst = reinterpret_cast<_Float16*>(smem + LL.coef) + ((j >> 3) * M + w) * 8 + (j & 7);
+    dst[0] = (_Float16)c;
+    dst[KS / 2 * 2 * M * 8] = (_Float16)(w & 1 ? -c : c);
   }
   for (int i = tid; i < QSB / 2; i += kThreads) reinterpret_cast<uint16_t*>(zero)[i] = 0;
   // probability rows that no wave writes stay zero
-  for (int i = tid; i < 2 * LL.p_stride / 4; i += kThreads)
-    reinterpret_cast<uint32_t*>(smem + LL.pbuf)[i] = 0u;
+  for (int i = tid; i < 2 * LL.p_stride / 16; i += kThreads)
+    reinterpret_cast<u4*>(smem + LL.pbuf)[i] = (u4){0, 0, 0, 0};
+  if (has && tb == 0 && lane < G) qmap[slot * G + lane] = info.head * G + lane;
+  // Rotations of the fast pairs for the 128 token offsets of a step: vector
+  // (block, token range, s, cos | sin, half, lane), 8 frequencies each
+  if (w < NHB * 4) {
+    const int s = w % NS, tr = w / NS % TB, blk = w / 4;
+    const float u = (float)(32 * NS * tr + NS * cl + s - 64);
+    u4 cv, sv;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float cc[2], ss[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int r = 2 * k + e;             // lane j holds pair j's turns
+        const float tj = __shfl((float)turn, 16 * blk + 8 * (r >> 2) + 4 * hf + (r & 3));
+        // at most 11 turns, known to 2^-20 of a turn: far below the fp16 rounding
+        const float a = __builtin_amdgcn_fractf(u * tj);
+        ss[e] = __builtin_amdgcn_sinf(a);
+        cc[e] = __builtin_amdgcn_cosf(a);
+      }
+      cv[k] = as_u32(__builtin_convertvector((f2){cc[0], cc[1]}, h2));
+      sv[k] = as_u32(__builtin_convertvector((f2){ss[0], ss[1]}, h2));
+    }
+    u4* dst = reinterpret_cast<u4*>(smem + LL.cs) + w * 128 + lane;
+    dst[0] = cv;
+    dst[64] = sv;
+  }
+  // B_k operands of the head, shared by its waves.  Slow dimensions: row i =
+  // channel of accumulator row i (see poly_scores), eight consecutive dimensions
+  // per 16-byte vector, a plane of R + 1 rows (the odd stride spreads a row's
+  // vectors over the banks) per step and half; fast dimensions: transposed, eight
+  // channels of one dimension per vector.
+  const int low_bytes = (R + 1) * KS * 32;
+  uint8_t* low = frag;
+  uint8_t* high = low + low_bytes;
+  auto store_bk = [&](int r0) {
+    const int jj = 8 * (bk_vec % (VPR / 2)), up = bk_vec / (VPR / 2);   // pair, high half
+    const int ks = ((jj - J0) >> 4) + up * (KS / 2), kc = bk_vec & 1;
+    if (jj < J0) return;
+    uint8_t* plane = low + (ks * 2 + kc) * (R + 1) * 16;
+#pragma unroll
+    for (int k = 0; k < kBkBatch; ++k) {
+      const int rb = r0 + RPI * (tb + TB * k);
+      if (rb < R) {
+        const int ch = rb + bk_row, c = ch >> 3;
+        const int rr = 8 * (c >> 1 & 1) + chunk_element(chunk_order(QM, np, c), ch & 7);
+        const int row = 32 * (ch >> 5) + 8 * (rr >> 2) + 4 * (c & 1) + (rr & 3);
+        *reinterpret_cast<u4*>(plane + row * 16) = bkv[k];
+      }
+    }
+  };
+  auto store_fast = [&](int blk) {
+    if ((lane >> 2) < R / 8) {
+      uint8_t* dst = high + ((blk * np + (fc >> 1)) * 64 + 32 * (fc & 1) + 16 * (lane >> 1 & 1) + 8 * (lane & 1)) * 16;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {          // dimension i of the lane's eight
+        u4 v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          v[k] = perm(fast[2 * k + 1][i / 2], fast[2 * k][i / 2], i & 1 ? 0x07060302u : 0x05040100u);
+        *reinterpret_cast<u4*>(dst + i * 16) = v;
+      }
+    }
+  };
+  if (has) {
+    store_bk(0);
+    for (int r0 = RPI * TB * kBkBatch; r0 < R; r0 += RPI * TB * kBkBatch) {
+      load_bk(r0);
+      store_bk(r0);
+    }
+    // one block: both waves of a head write the same values; two blocks: one each, or
+    // both by the one wave
+    store_fast(NHB > 1 ? tb & (NHB - 1) : 0);
+    if (NHB > TB) {
+      load_fast(1);
+      store_fast(1);
+    }
+  }
+  uint32_t qr[QL];                           // (low, high) dimension of the lane's pair
+#pragma unroll
+  for (int k = 0; k < QL; ++k) qr[k] = q_lo[k] | ((uint32_t)q_hi[k] << 16);
+  // angles in turns, reduced in fp64
+  auto rotation = [&](double t) {
+    const double a = t * turn;
+    float sn, cn;
+    sincospif(2.0f * (float)(a - floor(a)), &sn, &cn);
+    return make_float2(cn, sn);
+  };
+  float2 rot = rotation((double)(t_begin + 64));
+  const float2 rot_step = rotation((double)kStepTokens);
 
   const PolyWave W = {frag, frag + low_bytes, qbase, zero, smem + LL.coef,
                       smem + LL.cs + tb * NS * 2048};
@@ -658,13 +762,23 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   };
   auto store_q = [&]() {
     wave_sync();
+    const float c = rot.x * p.score_scale, n = rot.y * p.score_scale;
 #pragma unroll
     for (int k = 0; k < QL; ++k) {
       const int i = qrow(k);
       if (i < G) {
+        float lo, hi;
+        if (p.q_bf16) {
+          lo = __uint_as_float(qr[k] << 16);
+          hi = __uint_as_float(qr[k] & 0xFFFF0000u);
+        } else {
+          const h2 v = as_h2(qr[k]);
+          lo = (float)v[0];
+          hi = (float)v[1];
+        }
         _Float16* d = reinterpret_cast<_Float16*>(qbase + i * QSB);
-        d[qpos] = (_Float16)__builtin_fmaf(ql[k], rot.x, qh[k] * rot.y);
-        d[HALF + qpos] = (_Float16)__builtin_fmaf(qh[k], rot.x, -(ql[k] * rot.y));
+        d[qpos] = (_Float16)__builtin_fmaf(lo, c, hi * n);
+        d[HALF + qpos] = (_Float16)__builtin_fmaf(hi, c, -(lo * n));
       }
     }
     wave_sync();
@@ -698,8 +812,6 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   const int row0 = has ? slot * G : 0;       // first probability row of the head
   const float x0 = (float)(token(0) - 64) * (1.0f / 64.0f);
 
-  __syncthreads();
-
   // ---------------------------------------------------------------- main loop
   // One copy of the loop per pair count (NP = 0: no head), so that the prefetched
   // codes are carried in registers of their own: merged over the counts they
@@ -718,6 +830,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     }
   };
   load_raw(0);
+  __syncthreads();   // operands, tables and zeroed probabilities visible
   for (int step = 0; step < n_steps; ++step) {
     const int t_step = t_begin + step * kStepTokens;
     const bool full = t_step + kStepTokens <= t_end;
@@ -753,44 +866,51 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
       // Probabilities against a reference maximum per query that is raised (with
       // a rescale of the accumulators) only when a score exceeds it by more than
       // kLazyMargin; the first step always sets it.
-      float mx[NQ];
-      bool over = false;
+      auto softmax = [&](auto all_tag) {
+        constexpr bool ALL = decltype(all_tag)::value;   // every lane row holds a query
+        float mx[NQ];
+        bool over = false;
 #pragma unroll
-      for (int iq = 0; iq < NQ; ++iq) {
-        mx[iq] = -INFINITY;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const float v = x[s][iq];
-          mx[iq] = fmaxf(mx[iq], v);
-          b2[s][iq] = fmaxf(b2[s][iq], fminf(b1[s][iq], v));
-          b1[s][iq] = fmaxf(b1[s][iq], v);
-        }
-        over |= hf + 2 * iq < G && mx[iq] > m_run[iq] + kLazyMargin;
-      }
-      any_over = __any(over);
-      if (any_over) {
-#pragma unroll
-        for (int iq = 0; iq < NQ; ++iq)
-          for (int o = 1; o < 32; o <<= 1) mx[iq] = fmaxf(mx[iq], __shfl_xor(mx[iq], o));
-      }
-#pragma unroll
-      for (int iq = 0; iq < NQ; ++iq) {
-        const int i = hf + 2 * iq;
-        if (i < G) {
-          if (cl == 0) red[(row0 + i) * 2 + tb] = any_over ? mx[iq] : -INFINITY;
-          uint8_t* pr = pb + (row0 + i) * 16;
-          float l = 0.0f;
+        for (int iq = 0; iq < NQ; ++iq) {
+          mx[iq] = -INFINITY;
 #pragma unroll
           for (int s = 0; s < NS; ++s) {
-            const float e = __builtin_amdgcn_exp2f(x[s][iq] - m_run[iq]);
-            l += e;
-            *reinterpret_cast<_Float16*>(pr + p_off(s)) = (_Float16)e;
+            const float v = x[s][iq];
+            mx[iq] = fmaxf(mx[iq], v);
+            b2[s][iq] = __builtin_amdgcn_fmed3f(b1[s][iq], b2[s][iq], v);   // b1 >= b2
+            b1[s][iq] = fmaxf(b1[s][iq], v);
+          }
+          over |= (ALL || hf + 2 * iq < G) && mx[iq] > m_run[iq] + kLazyMargin;
+        }
+        any_over = __any(over);
+        if (any_over) {
+#pragma unroll
+          for (int iq = 0; iq < NQ; ++iq) {
+            mx[iq] = reduce_lanes<32>(mx[iq], [](float u, float v) { return fmaxf(u, v); });
+            if (cl == 0 && (ALL || hf + 2 * iq < G)) red[(row0 + hf + 2 * iq) * 2 + tb] = mx[iq];
+          }
+        } else if (cl == 0) {
+#pragma unroll
+          for (int iq = 0; iq < NQ; ++iq)
+            if (ALL || hf + 2 * iq < G) red[(row0 + hf + 2 * iq) * 2 + tb] = -INFINITY;
+        }
+#pragma unroll
+        for (int iq = 0; iq < NQ; ++iq) {
+          float l = 0.0f;
+          if (ALL || hf + 2 * iq < G) {
+            uint8_t* pr = pb + (row0 + hf + 2 * iq) * 16;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+              const float e = __builtin_amdgcn_exp2f(x[s][iq] - m_run[iq]);
+              l += e;
+              *reinterpret_cast<_Float16*>(pr + p_off(s)) = (_Float16)e;
+            }
           }
           ls[iq] = l;
-        } else {
-          ls[iq] = 0.0f;
         }
-      }
+      };
+      if (G == MQ) softmax(std::true_type{});
+      else softmax(std::false_type{});
     }
     if (lane == 0) fl[w] = any_over ? 1 : 0;
     if (QM != STARKV_Q_F16) store_vmeta(step);
@@ -835,7 +955,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
 
     // ------------------------------------------ values: acc += P . V'
     // matrix step j: the four 32-token blocks' chunks j (block = lane quad)
-    const uint8_t* mbase = smem + LL.meta + (step & 1) * LL.meta_stride;
+    const uint8_t* mbase = smem + LL.meta + (step & 1) * vmeta_bytes;
     auto values = [&](auto vm_tag, auto full_tag) {
       constexpr int VM = decltype(vm_tag)::value;
       constexpr bool FULL = decltype(full_tag)::value;
@@ -915,16 +1035,18 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   }
 
   // ---------------------------------------------------------------- partials
+  // (the last step's readers of red are past a barrier)
 #pragma unroll
   for (int iq = 0; iq < NQ; ++iq)
-    for (int o = 1; o < 32; o <<= 1) l_part[iq] += __shfl_xor(l_part[iq], o);
-  __syncthreads();                           // red's last readers are done
-  if (has && cl == 0) {
+    l_part[iq] = reduce_lanes<32>(l_part[iq], [](float u, float v) { return u + v; });
+  if (TB > 1) {                              // the head's waves hold parts of the sum
+    if (has && cl == 0) {
 #pragma unroll
-    for (int iq = 0; iq < NQ; ++iq)
-      if (hf + 2 * iq < G) red[(row0 + hf + 2 * iq) * 2 + tb] = l_part[iq];
+      for (int iq = 0; iq < NQ; ++iq)
+        if (hf + 2 * iq < G) red[(row0 + hf + 2 * iq) * 2 + tb] = l_part[iq];
+    }
+    lds_barrier();
   }
-  __syncthreads();
   const int64_t pbase = (int64_t)item.pitem * p.n_q;
   // Candidates for the exact rescoring: the two largest scores of each of 32 token
   // slots per query, a slot being the tokens of a 16-token block (of every
@@ -942,8 +1064,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
       const int i = hf + 2 * iq;
       const bool ok = i < G;
       const int row = row0 + (ok ? i : 0);
-      float lt = red[row * 2];
-      if (TB == 2) lt += red[row * 2 + 1];
+      const float lt = TB > 1 ? red[row * 2] + red[row * 2 + 1] : l_part[iq];
       const float bar = 0.5f * kRescoreTau * lt;
       const float mr = m_run[iq];
       auto bound = [&](float v) {
@@ -951,27 +1072,36 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
       };
       float qb = 0.0f;
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const int o = k ? S2 : S1;
-          const float c1 = __shfl_xor(b1[s][iq], o), c2 = __shfl_xor(b2[s][iq], o);
-          b2[s][iq] = fmaxf(fmaxf(b2[s][iq], c2), fminf(b1[s][iq], c1));
-          b1[s][iq] = fmaxf(b1[s][iq], c1);
-        }
-        qb = fmaxf(qb, fmaxf(bound(b1[s][iq]), bound(b2[s][iq])));
-      }
-      for (int o = 1; o < 32 / NS; o <<= 1) qb = fmaxf(qb, __shfl_xor(qb, o));
+      for (int s = 0; s < NS; ++s) qb = fmaxf(qb, fmaxf(bound(b1[s][iq]), bound(b2[s][iq])));
+      qb = reduce_lanes<32 / NS>(qb, [](float u, float v) { return fmaxf(u, v); });
       const int u0 = token(0);
       const int tg = u0 >> 5;                // 32-token block of the lane
-      const bool any = qb >= bar;
-      const int64_t qrow_out = pbase + kh.head * G + i;
+      const bool any = ok && qb >= bar;
+      const int64_t qrow_out = pbase + info.head * G + i;
       if (ok && (cl & (32 / NS - 1)) == 0) {
         float* dst = p.part + qrow_out * p.part_stride + p.rv;
         reinterpret_cast<uint8_t*>(dst + 2)[tg] = any ? 1 : 0;
         dst[4 + tg] = qb;
       }
-      if (ok && any && ((u0 & 15) >> 2) == 0) {
+      if (any) {                             // (the same in all lanes of a slot)
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const int o = k ? S2 : S1;
+            float c1, c2;
+            if (NS == 4) {                   // within four lanes
+              c1 = k ? dpp<0x4E>(b1[s][iq]) : dpp<0xB1>(b1[s][iq]);
+              c2 = k ? dpp<0x4E>(b2[s][iq]) : dpp<0xB1>(b2[s][iq]);
+            } else {
+              c1 = __shfl_xor(b1[s][iq], o);
+              c2 = __shfl_xor(b2[s][iq], o);
+            }
+            b2[s][iq] = fmaxf(fmaxf(b2[s][iq], c2), fminf(b1[s][iq], c1));
+            b1[s][iq] = fmaxf(b1[s][iq], c1);
+          }
+      }
+      if (any && ((u0 & 15) >> 2) == 0) {
         float2* cd = p.cand + qrow_out * kCand + tg * 16;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
@@ -993,26 +1123,27 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
       }
     }
   }
+  uint8_t* part = reinterpret_cast<uint8_t*>(p.part + pbase * p.part_stride);
 #pragma unroll
   for (int c = 0; c < CT; ++c)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int il = c * 16 + 4 * quad + e;
       if (il < nql) {
-        const int64_t qrow_out = pbase + p.kh[g0 + il / G].head * G + il % G;
+        const uint32_t off = (uint32_t)(qmap[il] * p.part_stride + col) * 4u;
 #pragma unroll
         for (int t = 0; t < NTW; ++t) {
           const int nt = w * NTW + t;
-          if (nt < NT) p.part[qrow_out * p.part_stride + 16 * nt + col] = acc_v[c][t][e];
+          if (nt < NT) *reinterpret_cast<float*>(part + 64 * nt + off) = acc_v[c][t][e];
         }
       }
     }
 }
 
 // ------------------------------------------------------------------ launchers
-template <int D, int QM, int NHB, int M, int NS, int CT, int NTW>
+template <int D, int QM, int NHB, int M, int NS, int CT, int NTW, int MAXP>
 static int launch_poly_t(const PolyParams& p, size_t lds, hipStream_t st) {
-  auto k = decode_split_poly_kernel<D, QM, NHB, M, NS, CT, NTW>;
+  auto k = decode_split_poly_kernel<D, QM, NHB, M, NS, CT, NTW, MAXP>;
   static std::atomic<uint64_t> attr{0};
   if (const int e = allow_lds(reinterpret_cast<const void*>(k), attr)) return e;
   dim3 grid(p.dyn ? p.cap : p.n_split, p.dyn ? 1 : p.batch, p.n_hg);
@@ -1020,12 +1151,18 @@ static int launch_poly_t(const PolyParams& p, size_t lds, hipStream_t st) {
   return (int)hipGetLastError();
 }
 
+template <int D, int QM, int NHB, int M, int NS, int CT, int NTW>
+static int dispatch_maxp(const PolyParams& p, int maxp, size_t lds, hipStream_t st) {
+  if (maxp <= 4) return launch_poly_t<D, QM, NHB, M, NS, CT, NTW, 4>(p, lds, st);
+  if constexpr (D == 128 && QM != STARKV_Q_F16) return launch_poly_t<D, QM, NHB, M, NS, CT, NTW, 8>(p, lds, st);
+  return (int)hipErrorInvalidValue;
+}
+
 template <int D, int QM, int NHB, int M, int NS, int CT>
-static int dispatch_ntw(const PolyParams& p, int ntw, size_t lds, hipStream_t st) {
-  switch (ntw) {
-    case 2: return launch_poly_t<D, QM, NHB, M, NS, CT, 2>(p, lds, st);
-    case 3: if constexpr (QM != STARKV_Q_F16) return launch_poly_t<D, QM, NHB, M, NS, CT, 3>(p, lds, st); break;
-  }
+static int dispatch_ntw(const PolyParams& p, const PolyShape& s, size_t lds, hipStream_t st) {
+  if (s.ntw == 2) return dispatch_maxp<D, QM, NHB, M, NS, CT, 2>(p, s.maxp, lds, st);
+  if constexpr (QM != STARKV_Q_F16)
+    if (s.ntw == 3) return dispatch_maxp<D, QM, NHB, M, NS, CT, 3>(p, s.maxp, lds, st);
   return (int)hipErrorInvalidValue;
 }
 
@@ -1033,23 +1170,23 @@ static int dispatch_ntw(const PolyParams& p, int ntw, size_t lds, hipStream_t st
 #define SK_NAME(a, b) SK_CAT2(a, b)
 int SK_NAME(SK_D, SK_QM)(const PolyParams& p, const PolyShape& s, size_t lds, hipStream_t st) {
   if (s.m == 8 && s.nhb == 1) {
-    if (s.ns == 4 && s.ct == 2) return dispatch_ntw<SK_D, SK_QM, 1, 8, 4, 2>(p, s.ntw, lds, st);
-    if (s.ns == 2 && s.ct == 1) return dispatch_ntw<SK_D, SK_QM, 1, 8, 2, 1>(p, s.ntw, lds, st);
+    if (s.ns == 4 && s.ct == 2) return dispatch_ntw<SK_D, SK_QM, 1, 8, 4, 2>(p, s, lds, st);
+    if (s.ns == 2 && s.ct == 1) return dispatch_ntw<SK_D, SK_QM, 1, 8, 2, 1>(p, s, lds, st);
   }
 #if SK_D == 128
   if (s.m == 8 && s.nhb == 2) {
-    if (s.ns == 4 && s.ct == 2) return dispatch_ntw<SK_D, SK_QM, 2, 8, 4, 2>(p, s.ntw, lds, st);
-    if (s.ns == 2 && s.ct == 1) return dispatch_ntw<SK_D, SK_QM, 2, 8, 2, 1>(p, s.ntw, lds, st);
+    if (s.ns == 4 && s.ct == 2) return dispatch_ntw<SK_D, SK_QM, 2, 8, 4, 2>(p, s, lds, st);
+    if (s.ns == 2 && s.ct == 1) return dispatch_ntw<SK_D, SK_QM, 2, 8, 2, 1>(p, s, lds, st);
   }
   if (s.m == 4 && s.nhb == 2 && s.ns == 2 && s.ct == 2)
-    return dispatch_ntw<SK_D, SK_QM, 2, 4, 2, 2>(p, s.ntw, lds, st);
+    return dispatch_ntw<SK_D, SK_QM, 2, 4, 2, 2>(p, s, lds, st);
 #endif
   return (int)hipErrorInvalidValue;
 }
 #else
 
 int poly_lds_bytes(const PolyShape& s, int head_dim, int frag_bytes, int v_ng) {
-  return poly_lds(frag_bytes, head_dim, s.nhb, s.m, s.ct, v_ng).total;
+  return poly_lds(head_dim, s.nhb, s.m, s.ct).meta + 2 * poly_meta_bytes(v_ng) + frag_bytes;
 }
 
 #define SK_DECL(a, b) \

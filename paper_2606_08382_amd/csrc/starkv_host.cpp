@@ -84,52 +84,12 @@ struct starkv_plan {
   // polynomial-rotation split kernel, where it applies (see plan_poly)
   bool poly;
   PolyShape poly_shape;
-  int32_t poly_n_hg, poly_lds;
-  int32_t poly_first[STARKV_MAX_KV_HEADS + 1], poly_frag_bytes[STARKV_MAX_KV_HEADS];
-  int8_t poly_slot[STARKV_MAX_KV_HEADS][kWaves], poly_tb[STARKV_MAX_KV_HEADS][kWaves];
-  PolyHead poly_kh[STARKV_MAX_KV_HEADS];
-  uint16_t poly_coef[kPolyMaxDegree][48];
+  int32_t poly_n_hg, poly_lds, poly_frag_bytes;
+  int32_t poly_nql[kPolyMaxGroups];
+  PolyWaveInfo poly_wave[kPolyMaxGroups][kWaves];
 };
 
 namespace {
-
-uint16_t f16_bits(double v) {
-  const _Float16 h = (_Float16)v;
-  uint16_t u;
-  std::memcpy(&u, &h, 2);
-  return u;
-}
-
-// Coefficients c[j][i] of x^i, i < m, in polynomials of degree m - 1 for cos(a_j x) (i
-// even) and sin(a_j x) (i odd) on [-1, 1]: the Chebyshev series cut off there, by
-// discrete orthogonality over 16 nodes (a <= 2.44 leaves nothing beyond degree 24).
-void trig_polynomials(const double* a, int n, int m, double (*c)[kPolyMaxDegree]) {
-  constexpr int N = 16;
-  // node weights of x^i: sum over k of cos(k th) T_k's coefficient of x^i
-  double x[N], wt[N][kPolyMaxDegree] = {};
-  for (int s = 0; s < N; ++s) {
-    const double th = M_PI * (s + 0.5) / N;
-    x[s] = std::cos(th);
-    double tk[kPolyMaxDegree] = {1.0}, tn[kPolyMaxDegree] = {0.0, 1.0};   // T_k, T_{k+1}
-    for (int k = 0; k < m; ++k) {
-      const double f = (k ? 2.0 : 1.0) / N * std::cos(k * th);
-      double t2[kPolyMaxDegree];
-      for (int i = 0; i < m; ++i) {
-        wt[s][i] += f * tk[i];
-        t2[i] = (i ? 2.0 * tn[i - 1] : 0.0) - tk[i];
-      }
-      std::memcpy(tk, tn, sizeof(tk));
-      std::memcpy(tn, t2, sizeof(tn));
-    }
-  }
-  for (int j = 0; j < n; ++j) {
-    for (int i = 0; i < m; ++i) c[j][i] = 0.0;
-    for (int s = 0; s < N / 2; ++s) {          // nodes s and N - 1 - s are opposite
-      const double cs = std::cos(a[j] * x[s]), sn = std::sin(a[j] * x[s]);
-      for (int i = 0; i < m; ++i) c[j][i] += 2.0 * wt[s][i] * (i % 2 ? sn : cs);
-    }
-  }
-}
 
 // Chooses the polynomial-rotation split kernel (split_poly.hip) and its shape.
 //
@@ -161,11 +121,12 @@ bool plan_poly(starkv_plan* P) {
   s.ntw = std::max(tiles, 2);
   int rmax = 0;
   for (int g = 0; g < n_kv; ++g) rmax = std::max(rmax, P->key_rank[g]);
+  s.maxp = rmax / 16;
   if (s.ntw > (c.qmode == STARKV_Q_F16 ? 2 : 3) || (c.qmode == STARKV_Q_F16 && rmax > 64)) return false;
   // (value meta of a step: at most one 16-byte vector per thread)
   if (P->layout.value_groups * 512 > kThreads * 16) return false;
   const int ks = (D - 32 * s.nhb) / 16;
-  auto frag_of = [&](int g) { return P->key_rank[g] * (32 * ks + 64 * s.nhb); };
+  auto frag_of = [&](int g) { return P->key_rank[g] * (32 * ks + 64 * s.nhb) + 32 * ks; };
   auto cost_of = [&](int g) { return 4 + P->key_rank[g] / 16; };
   const int max_heads = s.m == 8 ? 8 : 4;
   int by_cost[STARKV_MAX_KV_HEADS];
@@ -198,42 +159,43 @@ bool plan_poly(starkv_plan* P) {
       break;
     }
   }
-  if (n_hg > n_kv || most < 3) return false;
+  if (n_hg > n_kv || n_hg > kPolyMaxGroups || most < 3) return false;
   P->poly_n_hg = n_hg;
+  P->poly_frag_bytes = 0;
   const int tb_n = 4 / s.ns;
-  int o = 0;
+  std::memset(P->poly_nql, 0, sizeof(P->poly_nql));
+  std::memset(P->poly_wave, 0, sizeof(P->poly_wave));
   for (int h = 0; h < n_hg; ++h) {
-    P->poly_first[h] = o;
-    int frag = 0, n_units = 0, unit_slot[kWaves], unit_tb[kWaves];
-    for (int i = 0; i < count[h]; ++i, ++o) {
+    P->poly_nql[h] = count[h] * G;
+    PolyWaveInfo unit[kWaves];
+    int frag = 0, n_units = 0;
+    for (int i = 0; i < count[h]; ++i) {
       const int g = members[h][i];            // costliest first
-      PolyHead& k = P->poly_kh[o];
-      k.code_off = P->layout.key_code_offset[g];
-      k.meta_off = P->layout.key_meta_offset[g];
-      k.head = g;
-      k.rank = P->key_rank[g];
-      k.row_bytes = P->layout.key_row_bytes[g];
-      k.ngroups = P->layout.key_groups[g];
-      k.bk_row = P->bk_row[g];
-      k.frag = frag;
+      if (((P->layout.key_code_offset[g] | P->layout.key_meta_offset[g]) >> 40) != 0) return false;
+      for (int t = 0; t < tb_n; ++t) {
+        PolyWaveInfo& k = unit[n_units++];
+        std::memset(&k, 0, sizeof(k));
+        k.code_off = (uint32_t)(P->layout.key_code_offset[g] >> 8);
+        k.meta_off = (uint32_t)(P->layout.key_meta_offset[g] >> 8);
+        k.frag = (uint32_t)frag;
+        k.bk_row = (uint16_t)P->bk_row[g];
+        k.head = (uint16_t)g;
+        k.rank = (uint16_t)P->key_rank[g];
+        k.row_bytes = (uint16_t)P->layout.key_row_bytes[g];
+        k.ngroups = (uint16_t)P->layout.key_groups[g];
+        k.has = 1;
+        k.slot = (uint16_t)i;
+        k.tb = (uint16_t)t;
+      }
       frag += frag_of(g);
-      for (int t = 0; t < tb_n; ++t, ++n_units) { unit_slot[n_units] = i; unit_tb[n_units] = t; }
     }
-    P->poly_frag_bytes[h] = frag;
+    P->poly_frag_bytes = std::max(P->poly_frag_bytes, frag);
     // waves w and w + 4 share a SIMD: the costliest unit is paired with the cheapest
     for (int w = 0; w < kWaves; ++w) {
       const int u = w < 4 ? w : 11 - w;
-      P->poly_slot[h][w] = (int8_t)(u < n_units ? unit_slot[u] : -1);
-      P->poly_tb[h][w] = (int8_t)(u < n_units ? unit_tb[u] : 0);
+      if (u < n_units) P->poly_wave[h][w] = unit[u];
     }
   }
-  P->poly_first[n_hg] = o;
-  const int j0 = 16 * s.nhb, nj = D / 2 - j0;
-  double a[48], coef[48][kPolyMaxDegree];
-  for (int j = 0; j < nj; ++j) a[j] = 64.0 * std::pow(c.rope_theta, -2.0 * (j0 + j) / D);
-  trig_polynomials(a, nj, s.m, coef);
-  for (int j = 0; j < nj; ++j)
-    for (int m = 0; m < s.m; ++m) P->poly_coef[m][j] = f16_bits(coef[j][m]);
   P->poly_shape = s;
   return true;
 }
@@ -781,7 +743,6 @@ starkv_status starkv_decode_split(const starkv_plan* P, const void* cache, const
     p.plan = reinterpret_cast<int32_t*>(static_cast<uint8_t*>(ws) + plan_offset(P, max_ctx, n_hg));
     p.batch = c.batch;
     p.n_q = c.n_q_heads;
-    p.n_kv = c.n_kv_heads;
     p.group_q = c.n_q_heads / c.n_kv_heads;
     p.rmap = P->rmap;
     p.max_ctx = max_ctx;
@@ -792,7 +753,6 @@ starkv_status starkv_decode_split(const starkv_plan* P, const void* cache, const
     p.cap = wp.cap;
     p.q_bf16 = c.q_dtype == STARKV_DT_BF16;
     p.score_scale = (float)(1.4426950408889634 / std::sqrt((double)c.head_dim));
-    p.log2_theta = std::log2(c.rope_theta);
     p.v_code_off = P->layout.value_code_offset;
     p.v_meta_off = P->layout.value_meta_offset;
     p.rv = c.value_rank;
@@ -805,19 +765,19 @@ starkv_status starkv_decode_split(const starkv_plan* P, const void* cache, const
   if (P->poly) {
     PolyParams p;
     common(p);
+    p.log2_theta = std::log2(c.rope_theta);
+    p.frag_bytes = P->poly_frag_bytes;
     p.n_hg = P->poly_n_hg;
-    std::memcpy(p.hg_first, P->poly_first, sizeof(p.hg_first));
-    std::memcpy(p.hg_frag_bytes, P->poly_frag_bytes, sizeof(p.hg_frag_bytes));
-    std::memcpy(p.wave_slot, P->poly_slot, sizeof(p.wave_slot));
-    std::memcpy(p.wave_tb, P->poly_tb, sizeof(p.wave_tb));
-    std::memcpy(p.kh, P->poly_kh, sizeof(p.kh));
-    std::memcpy(p.coef, P->poly_coef, sizeof(p.coef));
+    std::memcpy(p.nql, P->poly_nql, sizeof(p.nql));
+    std::memcpy(p.wave, P->poly_wave, sizeof(p.wave));
     const int e = launch_decode_split_poly(p, P->poly_shape, c.head_dim, c.qmode, P->poly_lds,
                                            static_cast<void*>(stream));
     return hip_status(e, "decode_split launch");
   }
   DecodeParams p;
   common(p);
+  p.n_kv = c.n_kv_heads;
+  p.log2_theta = std::log2(c.rope_theta);
   p.n_hg = P->n_hg;
   std::memcpy(p.hg_first, P->hg_first, sizeof(p.hg_first));
   std::memcpy(p.hg_frags, P->hg_frags, sizeof(p.hg_frags));

@@ -97,20 +97,26 @@ struct DecodeParams {
   uint32_t o_code[STARKV_MAX_KV_HEADS], o_meta[STARKV_MAX_KV_HEADS];
 };
 
-// One KV head as seen by the polynomial-rotation split kernel.
-struct PolyHead {
-  int64_t code_off, meta_off;  // key planes (bytes)
-  int32_t head;                // KV head (query heads head*G .. head*G + G - 1)
-  int32_t rank;
-  int32_t row_bytes, ngroups;
-  int32_t bk_row;              // first row of this head in B_k
-  int32_t frag;                // byte offset of its up-projection operands in LDS
+constexpr int kPolyMaxDegree = 8;   // polynomial coefficients per RoPE frequency
+constexpr int kPolyMaxGroups = 6;   // head groups of the polynomial-rotation split kernel
+
+// A wave's work in the polynomial-rotation split kernel: one KV head and a token
+// range of every step (one scalar load of 32 bytes).
+struct PolyWaveInfo {
+  uint32_t code_off, meta_off; // key planes of its head, bytes / 256
+  uint32_t frag;               // byte offset of the head's up-projection operands in LDS
+  uint16_t bk_row, head;       // first row in B_k; KV head (query heads head*G ..)
+  uint16_t rank, row_bytes;
+  uint16_t ngroups, has;       // has: 0 for a wave without a head
+  uint16_t slot, tb;           // head within the group; token range
+  uint32_t unused;
 };
 
-constexpr int kPolyMaxDegree = 8;   // polynomial coefficients per RoPE frequency
-
 // The polynomial-rotation split kernel (split_poly.hip).  Fields as in
-// DecodeParams where named alike.
+// DecodeParams where named alike.  Kernel arguments lie in host memory, where each
+// first touch of a line costs a workgroup a trip over the bus: the kernel reads the
+// scalars (the leading 192 bytes) at once at its start, plus one record per group and
+// wave, and computes its tables itself.
 struct PolyParams {
   const uint8_t* cache;
   const void* q;
@@ -119,25 +125,20 @@ struct PolyParams {
   float* part;
   float2* cand;
   int32_t* plan;
-  int32_t batch, n_q, n_kv, group_q;
+  int64_t v_code_off, v_meta_off;
+  double log2_theta;
   RowMap rmap;
+  float score_scale;
+  int32_t batch, n_q, group_q;
   int32_t max_ctx, split_len, n_split;
   int32_t dyn, k_lo, cap;
   int32_t q_bf16;
-  float score_scale;
-  double log2_theta;
-  int64_t v_code_off, v_meta_off;
   int32_t rv, v_ro, v_ng8, v_ng, v_row_bytes;
   int32_t part_stride;
+  int32_t frag_bytes;          // LDS bytes of the up-projection operands (largest group)
   int32_t n_hg;
-  int32_t hg_first[STARKV_MAX_KV_HEADS + 1];
-  int32_t hg_frag_bytes[STARKV_MAX_KV_HEADS];
-  // per head group, the work of every wave: slot within the group (-1: no key
-  // work) and token range of the step
-  int8_t wave_slot[STARKV_MAX_KV_HEADS][kWaves], wave_tb[STARKV_MAX_KV_HEADS][kWaves];
-  PolyHead kh[STARKV_MAX_KV_HEADS];
-  // fp16 coefficients [m][j - j0] of cos (m even) and sin (m odd) of 64 w_j x
-  uint16_t coef[kPolyMaxDegree][48];
+  int32_t nql[kPolyMaxGroups]; // query heads of each group
+  alignas(64) PolyWaveInfo wave[kPolyMaxGroups][kWaves];
 };
 
 constexpr int kCand = 64;      // rescoring candidates per (sequence, split, query head):
@@ -230,9 +231,10 @@ int launch_decode_split_ntw(const DecodeParams& p, int head_dim, int qmode, int 
                             size_t lds_bytes, void* stream);
 // Shape of a polynomial-rotation instance: high frequency blocks (16 RoPE pairs
 // each, rebuilt and rotated per token), polynomial terms of the others, tokens
-// per lane of a 128-token step, 16-query tiles, value tiles per wave.
+// per lane of a 128-token step, 16-query tiles, value tiles per wave, most pairs of
+// 8-channel chunks of a key head.
 struct PolyShape {
-  int32_t nhb, m, ns, ct, ntw;
+  int32_t nhb, m, ns, ct, ntw, maxp;
 };
 int poly_lds_bytes(const PolyShape& s, int head_dim, int frag_bytes, int v_ng);
 int launch_decode_split_poly(const PolyParams& p, const PolyShape& s, int head_dim, int qmode,
