@@ -7,9 +7,11 @@
 //   (Sec. 4.4: an outlier block and an inlier block at b_out > b_in bits: 8/4,
 //   4/4, or the paper's 4/3).  The scale is
 //   the smallest fp16 not below (max - min)/(2^b - 1) and the codes round half
-//   to even; both are evaluated in fp64, which is exact for fp16 operands, so
-//   the codes do not depend on evaluation order.
+//   to even; both are decided on exact fp32 residuals (fp64 for values that are
+//   not finite), so the codes do not depend on evaluation order.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "starkv_internal.h"
 
@@ -40,55 +42,34 @@ __device__ uint16_t f16_ceil_pos(double q) {
   return (uint16_t)(((E + 15) << 10) | ((int)m - 1024));
 }
 
-struct GroupQ {
-  uint16_t s, z;
-  double sv, zv, levels;
-};
-
-__device__ __forceinline__ GroupQ group_params(const uint16_t* x, int n, int bits) {
-  double lo = h2d(x[0]), hi = lo;
-  for (int i = 1; i < n; ++i) {
-    const double v = h2d(x[i]);
-    lo = v < lo ? v : lo;
-    hi = v > hi ? v : hi;
-  }
-  GroupQ g;
-  g.levels = (double)((1 << bits) - 1);
-  g.z = __builtin_bit_cast(uint16_t, (_Float16)lo);   // lo is an fp16 value
-  g.s = (hi > lo) ? f16_ceil_pos((hi - lo) / g.levels) : (uint16_t)0;
-  g.sv = h2d(g.s);
-  g.zv = lo;
-  return g;
-}
-
-__device__ __forceinline__ uint32_t group_code(const GroupQ& g, uint16_t x) {
-  if (g.sv == 0.0) return 0;
-  double c = rint((h2d(x) - g.zv) / g.sv);
-  c = c < 0.0 ? 0.0 : (c > g.levels ? g.levels : c);
-  return (uint32_t)c;
-}
-
 // ------------------------------------------------------------------ pack kernels
 // Lanes 32h .. 32h + 31 of a wave hold the channels c0 .. c0 + 31 of one token
 // and one quantization group (lanes at or beyond the group's width are off).
 // The group's min and max come from reductions within those 32 lanes, the scale
-// and the codes from fp64 arithmetic per lane, and a token's key codes are
-// packed into its cache words with shuffles.
+// and the codes from each lane's arithmetic, and a token's key codes are packed
+// into its cache words across lanes.
 //
-// Two kernels.  Decode-sized appends (one token per wave) first sum the
-// down-projection's split-k partials (fixed order) and store the fp16 latent;
-// a token then writes its value nibbles into words that hold eight tokens four
-// apart, with an atomic AND/OR pair unless each word has one writer.  Appends
-// given as fp16 latents take one wave per 32-row block of a sequence and
-// group, with lane (h, c) on channel c0 + c of the block's tokens 2i + h: every
-// value word of the block is then assembled in one lane and stored once.
+// Decode-sized appends (one token per wave) first sum the down-projection's
+// split-k partials (fixed order) and store the fp16 latent; a token then writes its
+// value nibbles into words that hold eight tokens four apart, with an atomic
+// AND/OR pair unless each word has one writer.  Appends given as fp16 latents (the
+// prefill, cache fills) take a lane per token, see pack_tokens_kernel.
 
-__device__ __forceinline__ float wave_min32(float v) {
-  for (int o = 16; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o));
-  return v;
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
-__device__ __forceinline__ float wave_max32(float v) {
-  for (int o = 16; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+// op over the lane's neighbours in its quad, eight and 32 lanes, to all of them
+template <int N, class T, class Op>
+__device__ __forceinline__ T reduce_lanes(T v, Op op) {
+  auto at = [](T x, auto c) { return __builtin_bit_cast(T, dpp<decltype(c)::value>(__builtin_bit_cast(uint32_t, x))); };
+  v = op(v, at(v, std::integral_constant<int, 0xB1>{}));                 // quad_perm 1,0,3,2
+  v = op(v, at(v, std::integral_constant<int, 0x4E>{}));                 // quad_perm 2,3,0,1
+  if (N > 4) v = op(v, at(v, std::integral_constant<int, 0x141>{}));     // row_half_mirror
+  if (N > 8) {
+    v = op(v, at(v, std::integral_constant<int, 0x140>{}));              // row_mirror
+    v = op(v, __shfl_xor(v, 16));
+  }
   return v;
 }
 
@@ -129,14 +110,19 @@ struct QCode {
   uint32_t code;
 };
 
-__device__ __forceinline__ QCode quantize_lane(uint16_t xb, bool on, int bits) {
-  // the fp16 values compare exactly in fp32
-  const float xf = (float)__builtin_bit_cast(_Float16, xb);
-  const float lo = wave_min32(on ? xf : INFINITY);
-  const float hi = wave_max32(on ? xf : -INFINITY);
+// a - b = hi + lo exactly, hi the rounded difference (finite operands)
+__device__ __forceinline__ void exact_diff(float a, float b, float* hi, float* lo) {
+  const float d = a - b, t = d - a;
+  *hi = d;
+  *lo = (a - (d - t)) - (b + t);
+}
+
+// Scale, zero and code of a group whose values span lo .. hi; fp64, for groups that
+// are not finite.
+__device__ QCode quantize_wide(float xf, float lo, float hi, int bits) {
   const double levels = (double)((1 << bits) - 1);
   QCode q;
-  q.s16 = (hi > lo) ? f16_ceil_pos(((double)hi - (double)lo) / levels) : (uint16_t)0;
+  q.s16 = f16_ceil_pos(((double)hi - (double)lo) / levels);
   q.z16 = __builtin_bit_cast(uint16_t, (_Float16)lo);
   const double sv = h2d(q.s16);
   q.code = 0;
@@ -144,6 +130,57 @@ __device__ __forceinline__ QCode quantize_lane(uint16_t xb, bool on, int bits) {
     double c = rint(((double)xf - (double)lo) / sv);
     c = c < 0.0 ? 0.0 : (c > levels ? levels : c);
     q.code = (uint32_t)c;
+  }
+  return q;
+}
+
+// The fp16 values and their differences are multiples of 2^-24 below 2^17, up to 41
+// bits: a difference is held as an exact pair of fp32.  A guess of the scale or of
+// the code is off by one unit at most, and is settled by residuals that fp32 holds
+// exactly: level counts and codes (8 bits) times a scale (11 bits) fit in 24, and what
+// is left of a difference near half a unit loses no bits.
+
+// The smallest fp16 s with s levels >= hi - lo (hi > lo, finite difference).
+__device__ __forceinline__ uint16_t group_scale(float lo, float hi, float levels, float inv_levels) {
+  float dh, dl;
+  exact_diff(hi, lo, &dh, &dl);
+  uint32_t s = __builtin_bit_cast(uint16_t, (_Float16)(dh * inv_levels));
+  auto short_of = [&](uint32_t u) {
+    const float sv = (float)__builtin_bit_cast(_Float16, (uint16_t)u);
+    return __builtin_fmaf(sv, levels, -dh) - dl < 0.0f;
+  };
+  if (short_of(s)) ++s;
+  else if (s > 0 && !short_of(s - 1)) --s;
+  return (uint16_t)s;
+}
+
+// round-half-even((x - lo) / s) in [0, levels]; rs: 1/s within an ulp.  (A NaN x: 0.)
+__device__ __forceinline__ uint32_t group_code(float x, float lo, float s, float rs, float levels) {
+  float xh, xl;
+  exact_diff(x, lo, &xh, &xl);
+  float n = rintf(xh * rs);
+  const float r = __builtin_fmaf(-n, s, xh), half = 0.5f * s;
+  const float up = (r - half) + xl, down = (r + half) + xl;   // exact signs
+  const bool odd = (int)n & 1;
+  if (up > 0.0f || (up == 0.0f && odd)) n += 1.0f;
+  else if (down < 0.0f || (down == 0.0f && odd)) n -= 1.0f;
+  return (uint32_t)fminf(fmaxf(n, 0.0f), levels);
+}
+
+__device__ __forceinline__ QCode quantize_lane(uint16_t xb, bool on, int bits) {
+  const float xf = (float)__builtin_bit_cast(_Float16, xb);
+  const float lo = reduce_lanes<32>(on ? xf : INFINITY, [](float a, float b) { return fminf(a, b); });
+  const float hi = reduce_lanes<32>(on ? xf : -INFINITY, [](float a, float b) { return fmaxf(a, b); });
+  QCode q = {0, __builtin_bit_cast(uint16_t, (_Float16)lo), 0};
+  if (hi > lo) {
+    const float levels = (float)((1 << bits) - 1);
+    if (hi - lo < INFINITY) {
+      q.s16 = group_scale(lo, hi, levels, 1.0f / levels);
+      const float sv = (float)__builtin_bit_cast(_Float16, q.s16);
+      q.code = group_code(xf, lo, sv, __builtin_amdgcn_rcpf(sv), levels);
+    } else {
+      q = quantize_wide(xf, lo, hi, bits);
+    }
   }
   if (!on) q.code = 0;
   return q;
@@ -163,17 +200,14 @@ __device__ __forceinline__ void store_key_token(const AppendParams& p, const Pac
   uint8_t* chunk = ch < nhi ? kb + ch * 16 * hb : kb + nhi * 16 * hb + (ch - nhi) * 16 * lb;
   if (bits == 8) {          // 4 codes per 32-bit word, lanes 4k..4k+3
     uint32_t wv = q.code << (8 * (cl & 3));
-    wv |= __shfl_xor(wv, 1);
-    wv |= __shfl_xor(wv, 2);
+    wv = reduce_lanes<4>(wv, [](uint32_t a, uint32_t b) { return a | b; });
     if (on && (cl & 3) == 0)
       *reinterpret_cast<uint32_t*>(chunk + tau * 8 + (c % 8)) = wv;
   } else {                  // a token's 8 codes of a chunk, lanes 8k..8k+7: channel
     // w at bits bits*w (4-bit: one 32-bit word; 3-bit: 3 bytes, stored bytewise
     // since neighbouring tokens share 32-bit words)
     uint32_t wv = q.code << (bits * (cl & 7));
-    wv |= __shfl_xor(wv, 1);
-    wv |= __shfl_xor(wv, 2);
-    wv |= __shfl_xor(wv, 4);
+    wv = reduce_lanes<8>(wv, [](uint32_t a, uint32_t b) { return a | b; });
     if (on && (cl & 7) == 0) {
       if (bits == 4) {
         *reinterpret_cast<uint32_t*>(chunk + tau * 4) = wv;
@@ -313,12 +347,10 @@ __global__ __launch_bounds__(256) void pack_kernel(AppendParams p) {
   pack_token(p, G, lane, b, pos + j, xb);
 }
 
-// Appends given as fp16 latents: one wave per (sequence, 32-row block that the
-// rows pos .. pos + n_new - 1 touch, group).  A 3- or 4-bit value word of the
-// block (eight tokens of one channel, four apart) belongs to one lane, which
-// assembles the new fields and stores the word once, reading it first only
-// when the append covers part of it; no other wave of the launch writes it.
-__global__ __launch_bounds__(256) void pack_block_kernel(AppendParams p) {
+// Appends given as fp16 latents, fp16 cache: one wave per (sequence, 32-row block that
+// the rows pos .. pos + n_new - 1 touch, group of 32 channels), lane (h, c) on channel
+// c of the block's tokens 2i + h.
+__global__ __launch_bounds__(256) void pack_f16_kernel(AppendParams p) {
   const int lane = threadIdx.x & 63;
   const int wid = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
   const int nblk = (p.n_new + 31) / 32 + 1;     // blocks a run of n_new rows can touch
@@ -338,79 +370,243 @@ __global__ __launch_bounds__(256) void pack_block_kernel(AppendParams p) {
   }
   const PackGroup G = make_group(p, item);
   const int h = lane >> 5, cl = lane & 31;
-  const bool on = cl < G.n;
   const int c = G.c0 + cl;
-  const int bits = G.bits;
   const int64_t row0 = cache_row(p.rmap, b, 32 * a);   // 32-aligned: pages hold >= 128 rows
-  // the lane's 16 latents (tokens u = 2 i + h of the block), loaded together
-  uint16_t xb[16];
+  uint8_t* code_plane = p.cache + p.code_off[G.bl];
+  uint8_t* vb = code_plane + (row0 / 32) * 32 * G.rb;
+  if (cl >= G.n) return;
+  uint16_t xb[16];                              // loaded together
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    const int t = 32 * a + 2 * i + h;
-    xb[i] = 0;
-    if (on && t >= t_lo && t < t_hi)
-      xb[i] = p.lat[((int64_t)b * p.n_new + (t - t0)) * p.width + p.lat_off[G.bl] + c];
+    const int t = min(max(32 * a + 2 * i + h, t_lo), t_hi - 1);
+    xb[i] = p.lat[((int64_t)b * p.n_new + (t - t0)) * p.width + p.lat_off[G.bl] + c];
   }
-  uint8_t* code_plane = p.cache + p.code_off[G.bl];
-  uint8_t* meta_plane = p.cache + p.meta_off[G.bl];
-  uint8_t* vb = code_plane + (row0 / 32) * 32 * G.rb;
-  // value words of chunks kq = h and kq = h + 2 (3- and 4-bit): new fields, and
-  // the bits they cover
-  uint32_t acc[2] = {0u, 0u}, cov[2] = {0u, 0u};
-  const uint32_t fmask = bits < 16 ? (1u << bits) - 1 : 0u;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int u = 2 * i + h, t = 32 * a + u;
-    const bool live = t >= t_lo && t < t_hi;    // uniform in the lane's half
-    const int64_t kblk = (row0 + u) / 16;
+    if (t < t_lo || t >= t_hi) continue;
     const int tau = u % 16, kq = u % 4, slot = 4 * (u / 16) + (u % 16) / 4;
-    if (bits == 16) {
-      if (on && live) {
-        if (!G.is_v)
-          *reinterpret_cast<uint16_t*>(code_plane + kblk * 16 * G.rb + (c / 8) * 256 + tau * 16 + (c % 8) * 2) = xb[i];
-        else
-          *reinterpret_cast<uint16_t*>(vb + ((int64_t)c * 4 + kq) * 16 + slot * 2) = xb[i];
-      }
-      continue;
-    }
-    const QCode q = quantize_lane(xb[i], on, bits);
-    if (!G.is_v) {
-      store_key_token(p, G, cl, kblk, tau, q, on && live, live && cl == 0);
-      continue;
-    }
-    if (on && live) {
-      if (bits == 8) {
-        vb[value_word(G, c, kq) + slot] = (uint8_t)q.code;
-      } else {
-        const int sh = value_shift(bits, slot);
-        acc[i & 1] |= q.code << sh;
-        cov[i & 1] |= fmask << sh;
-      }
-    }
-    if (live && cl == 0) {
-      uint16_t* m = reinterpret_cast<uint16_t*>(meta_plane + ((row0 / 32) * G.ngr + G.gi) * 128 +
-                                                kq * 32 + slot * 2);
-      m[0] = q.s16;
-      m[8] = q.z16;
+    if (!G.is_v)
+      *reinterpret_cast<uint16_t*>(code_plane + (row0 + u) / 16 * 16 * G.rb + (c / 8) * 256 + tau * 16 + (c % 8) * 2) = xb[i];
+    else
+      *reinterpret_cast<uint16_t*>(vb + ((int64_t)c * 4 + kq) * 16 + slot * 2) = xb[i];
+  }
+}
+
+// Values of lane ^ 1, ^ 2 and ^ 4.
+__device__ __forceinline__ uint32_t lane_x1(uint32_t v) { return dpp<0xB1>(v); }
+__device__ __forceinline__ uint32_t lane_x2(uint32_t v) { return dpp<0x4E>(v); }
+__device__ __forceinline__ uint32_t lane_x4(uint32_t v) { return dpp<0x141>(dpp<0x1B>(v)); }   // ^ 3, then ^ 7
+
+// Eight 3-bit fields at bits 4k moved to bits 3k.
+__device__ __forceinline__ uint32_t squeeze3(uint32_t x) {
+  x = (x & 0x07070707u) | ((x >> 1) & 0x38383838u);
+  x = (x & 0x003F003Fu) | ((x >> 2) & 0x0FC00FC0u);
+  return (x & 0xFFFu) | ((x >> 4) & 0xFFF000u);
+}
+
+// Appends given as fp16 latents, quantized caches: one wave per (sequence, 64-row
+// block that the rows touch, quantization group); a lane quantizes one token's group.
+//
+// The group's extremes, scale and codes are then in one lane: nothing is reduced over
+// lanes and the scale is formed once per token (with a lane per channel it was formed in
+// all 32, and every token took its own reductions and fp64 divisions: 8192 tokens of the
+// 70B layer 64 us, now 13; 4503 of the 8B layer 31 us, now 8).  Codes come from a reciprocal, and from the exact test
+// (group_code) only where some lane is within 2^-12 of a tie (the reciprocal's quotient
+// is off by at most 255 x 2^-21.5).
+// Lane (half h, chunk q, i) holds row 32 h + u of the block, u the token of chunk q in
+// field i of a value word (slots 0,2,4,6,1,3,5,7).  A key word is a lane's own eight codes;
+// value words hold one channel of the eight lanes of a chunk, so the codes are
+// transposed within eight lanes first.  Value words that the append covers in
+// part are merged with what they hold; no other wave of the launch writes them.
+typedef uint32_t u4_2 __attribute__((ext_vector_type(4), aligned(2)));   // latents: 2-byte aligned
+typedef _Float16 h2v __attribute__((ext_vector_type(2)));
+
+__global__ __launch_bounds__(256) void pack_tokens_kernel(AppendParams p) {
+  const int lane = threadIdx.x & 63;
+  const int wid = blockIdx.x * (blockDim.x / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nblk = (p.n_new + 62) / 64 + 1;     // blocks a run of n_new rows can touch
+  const int per_seq = nblk * p.n_items;
+  if (wid >= p.batch * per_seq) return;
+  const int b = wid / per_seq, rem = wid % per_seq;
+  const int bi = rem / p.n_items, item = rem % p.n_items;
+  const int t0 = p.pos[b];
+  const int a = (t0 >> 6) + bi;                 // rows 64 a .. 64 a + 63 of the sequence
+  // rows outside the cache are dropped
+  const int t_lo = max(max(t0, 64 * a), 0);
+  const int t_hi = min(min(t0 + p.n_new, 64 * a + 64), p.capacity);
+  if (t_lo >= t_hi) return;
+  if (p.rmap.table) {                           // and rows on pages outside the pool
+    const int pg = p.rmap.table[(int64_t)b * p.rmap.per_seq + ((64 * a) >> p.rmap.shift)];
+    if (pg < 0 || pg >= p.rmap.n_pages) return;
+  }
+  const PackGroup G = make_group(p, item);
+  const int bits = G.bits, nc = G.n / 8;        // 8-channel chunks of the group
+  const int q = (lane >> 3) & 3, i = lane & 7;
+  const int slot = i < 4 ? 2 * i : 2 * i - 7;
+  const int u = 32 * (lane >> 5) + 16 * (slot >> 2) + 4 * (slot & 3) + q;   // row of the block
+  const int t = 64 * a + u;
+  const bool live = t >= t_lo && t < t_hi;
+  const int64_t row = cache_row(p.rmap, b, 64 * a) + u;   // pages hold a multiple of 128 rows
+  // the token's channels (lanes outside the append repeat its first row)
+  uint32_t x[16];
+  {
+    const uint16_t* src = p.lat + ((int64_t)b * p.n_new + (live ? t : t_lo) - t0) * p.width +
+                          p.lat_off[G.bl] + G.c0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const u4_2 v = *reinterpret_cast<const u4_2*>(src + 8 * (k < nc ? k : 0));
+      x[4 * k] = v.x; x[4 * k + 1] = v.y; x[4 * k + 2] = v.z; x[4 * k + 3] = v.w;
     }
   }
-  if (G.is_v && on && (bits == 4 || bits == 3)) {
+  // chunks past the group repeat chunk 0: the extremes need no masks
+  h2v mn = __builtin_bit_cast(h2v, x[0]), mx = mn;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {               // chunk kq = 2 k + h
-      if (cov[k] == 0u) continue;
-      uint8_t* wd = vb + value_word(G, c, 2 * k + h);
-      if (bits == 4) {
-        uint32_t* w32 = reinterpret_cast<uint32_t*>(wd);
-        *w32 = cov[k] == 0xFFFFFFFFu ? acc[k] : ((*w32 & ~cov[k]) | acc[k]);
-      } else {                                  // 24-bit word, bytewise (not aligned)
-        uint32_t old = 0u;
-        if (cov[k] != 0xFFFFFFu) old = (uint32_t)wd[0] | ((uint32_t)wd[1] << 8) | ((uint32_t)wd[2] << 16);
-        const uint32_t v = (old & ~cov[k]) | acc[k];
-        wd[0] = (uint8_t)v;
-        wd[1] = (uint8_t)(v >> 8);
-        wd[2] = (uint8_t)(v >> 16);
+  for (int k = 1; k < 16; ++k) {
+    mn = __builtin_elementwise_min(mn, __builtin_bit_cast(h2v, x[k]));
+    mx = __builtin_elementwise_max(mx, __builtin_bit_cast(h2v, x[k]));
+  }
+  float lo = fminf((float)mn[0], (float)mn[1]), hi = fmaxf((float)mx[0], (float)mx[1]);
+  if (lo != lo && nc < 4) { lo = INFINITY; hi = -INFINITY; }   // every channel a NaN
+  const float levels = (float)((1 << bits) - 1), inv_levels = 1.0f / levels;
+  const uint16_t z16 = __builtin_bit_cast(uint16_t, (_Float16)lo);
+  uint16_t s16 = 0;
+  uint32_t w0[4], w1[4];                        // per chunk: nibbles, or bytes 0..3 and 4..7
+  const bool finite = hi - lo < INFINITY;       // (also of an empty span, lo = inf)
+  if (__ballot(!finite && hi > lo) == 0) {
+    const bool span = hi > lo;
+    if (span) s16 = group_scale(lo, hi, levels, inv_levels);
+    const float s = (float)__builtin_bit_cast(_Float16, s16);
+    const float rs = span ? __builtin_amdgcn_rcpf(s) : 0.0f;
+    auto codes = [&](auto wide_tag) {
+      constexpr bool WIDE = decltype(wide_tag)::value;   // 8-bit codes
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        w0[k] = w1[k] = 0;
+        if (k >= nc) continue;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float xf = (float)__builtin_bit_cast(h2v, x[4 * k + e / 2])[e % 2];
+          const float qv = (xf - lo) * rs;
+          const float n = rintf(qv);
+          uint32_t c = (uint32_t)n;
+          if (__ballot(fabsf(qv - n) > 0.5f - 0x1p-12f) != 0) c = span ? group_code(xf, lo, s, rs, levels) : 0u;
+          if (!WIDE) w0[k] |= c << (4 * e);
+          else if (e < 4) w0[k] |= c << (8 * e);
+          else w1[k] |= c << (8 * (e - 4));
+        }
+      }
+    };
+    if (bits == 8) codes(std::true_type{});
+    else codes(std::false_type{});
+  } else {                                      // infinities: fp64, channel by channel
+    for (int k = 0; k < 4; ++k) {
+      w0[k] = w1[k] = 0;
+      for (int e = 0; e < 8; ++e) {
+        const float xf = (float)__builtin_bit_cast(h2v, x[4 * k + e / 2])[e % 2];
+        QCode qc = {0, z16, 0};
+        if (hi > lo) qc = quantize_wide(xf, lo, hi, bits);
+        s16 = qc.s16;
+        if (bits != 8) w0[k] |= qc.code << (4 * e);
+        else if (e < 4) w0[k] |= qc.code << (8 * e);
+        else w1[k] |= qc.code << (8 * (e - 4));
       }
     }
+  }
+  uint8_t* code_plane = p.cache + p.code_off[G.bl];
+  uint8_t* meta_plane = p.cache + p.meta_off[G.bl];
+  const int ch0 = G.c0 / 8, nhi = G.ro / 8;     // first chunk of the group; outlier chunks
+  if (!G.is_v) {
+    if (!live) return;
+    const int64_t kblk = row / 16;
+    const int tau = (int)(row % 16);
+    uint8_t* kb = code_plane + kblk * 16 * G.rb +
+                  (ch0 < nhi ? ch0 * 16 * G.hb : nhi * 16 * G.hb + (ch0 - nhi) * 16 * G.lb) + tau * bits;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k >= nc) break;
+      uint8_t* d = kb + k * 16 * bits;
+      if (bits == 8) {
+        *reinterpret_cast<uint2*>(d) = make_uint2(w0[k], w1[k]);
+      } else if (bits == 4) {
+        *reinterpret_cast<uint32_t*>(d) = w0[k];
+      } else {
+        const uint32_t v = squeeze3(w0[k]);
+        d[0] = (uint8_t)v;
+        d[1] = (uint8_t)(v >> 8);
+        d[2] = (uint8_t)(v >> 16);
+      }
+    }
+    *reinterpret_cast<uint32_t*>(meta_plane + (kblk * G.ngr + G.gi) * 64 + tau * 4) =
+        (uint32_t)s16 | ((uint32_t)z16 << 16);
+    return;
+  }
+  const int64_t vblk = row / 32;
+  uint8_t* vb = code_plane + vblk * 32 * G.rb;
+  // rows of this lane's chunk (fields of its value words) that the append covers
+  const uint32_t cov = (uint32_t)(__ballot(live) >> (lane & 56)) & 0xFFu;
+  const bool b0 = i & 1, b1 = i & 2, b2 = i & 4;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (k >= nc) break;
+    if (bits == 8) {
+      // 8 x 8 bytes over eight lanes
+      uint32_t A = w0[k], B = w1[k];
+      const uint32_t r4 = lane_x4(b2 ? A : B);
+      if (b2) A = r4; else B = r4;
+      const uint32_t sel2 = b1 ? 0x03020706u : 0x05040100u;   // (partner, own) halves
+      A = __builtin_amdgcn_perm(lane_x2(A), A, sel2);
+      B = __builtin_amdgcn_perm(lane_x2(B), B, sel2);
+      const uint32_t sel1 = b0 ? 0x03070105u : 0x06020400u;   // bytes
+      A = __builtin_amdgcn_perm(lane_x1(A), A, sel1);
+      B = __builtin_amdgcn_perm(lane_x1(B), B, sel1);
+      // fields (lanes) 0..7 to slots 0,2,4,6,1,3,5,7
+      const uint32_t v0 = __builtin_amdgcn_perm(B, A, 0x05010400u);
+      const uint32_t v1 = __builtin_amdgcn_perm(B, A, 0x07030602u);
+      uint8_t* d = vb + value_word(G, G.c0 + 8 * k + i, q);
+      if (cov == 0xFFu) {
+        *reinterpret_cast<uint2*>(d) = make_uint2(v0, v1);
+      } else {
+#pragma unroll
+        for (int f = 0; f < 8; ++f) {
+          const int sl = f < 4 ? 2 * f : 2 * f - 7;
+          if ((cov >> f) & 1) d[sl] = (uint8_t)((sl < 4 ? v0 : v1) >> (8 * (sl & 3)));
+        }
+      }
+    } else {
+      // 8 x 8 nibbles over eight lanes
+      uint32_t v = w0[k];
+      v = __builtin_amdgcn_perm(lane_x4(v), v, b2 ? 0x03020706u : 0x05040100u);
+      v = __builtin_amdgcn_perm(lane_x2(v), v, b1 ? 0x03070105u : 0x06020400u);
+      const uint32_t o = lane_x1(v);
+      const uint32_t m = b0 ? 0xF0F0F0F0u : 0x0F0F0F0Fu;
+      v = (v & m) | (__builtin_amdgcn_alignbit(o, o, b0 ? 4 : 28) & ~m);
+      if (cov == 0) continue;
+      uint32_t cm = (cov | (cov << 12)) & 0x000F000Fu;        // a nibble per covered field
+      cm = (cm | (cm << 6)) & 0x03030303u;
+      cm = (cm | (cm << 3)) & 0x11111111u;
+      cm *= 15u;
+      uint8_t* d = vb + value_word(G, G.c0 + 8 * k + i, q);
+      if (bits == 4) {
+        uint32_t* w32 = reinterpret_cast<uint32_t*>(d);
+        *w32 = cov == 0xFFu ? v : ((*w32 & ~cm) | (v & cm));
+      } else {                                  // 24-bit word, bytewise (not aligned)
+        uint32_t nv = squeeze3(v);
+        if (cov != 0xFFu) {
+          const uint32_t old = (uint32_t)d[0] | ((uint32_t)d[1] << 8) | ((uint32_t)d[2] << 16);
+          const uint32_t c3 = squeeze3(cm & 0x77777777u);
+          nv = (old & ~c3) | (nv & c3);
+        }
+        d[0] = (uint8_t)nv;
+        d[1] = (uint8_t)(nv >> 8);
+        d[2] = (uint8_t)(nv >> 16);
+      }
+    }
+  }
+  if (live) {
+    uint16_t* m = reinterpret_cast<uint16_t*>(meta_plane + (vblk * G.ngr + G.gi) * 128 + q * 32 + slot * 2);
+    m[0] = s16;
+    m[8] = z16;
   }
 }
 
@@ -794,9 +990,12 @@ int launch_append_pack(const AppendParams& p, void* stream) {
   if (p.partial) {
     waves = (int64_t)p.batch * p.n_new * p.n_items;
     hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, p);
-  } else {
+  } else if (p.qmode == STARKV_Q_F16) {
     waves = (int64_t)p.batch * ((p.n_new + 31) / 32 + 1) * p.n_items;
-    hipLaunchKernelGGL(pack_block_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, p);
+    hipLaunchKernelGGL(pack_f16_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, p);
+  } else {
+    waves = (int64_t)p.batch * ((p.n_new + 62) / 64 + 1) * p.n_items;
+    hipLaunchKernelGGL(pack_tokens_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, p);
   }
   return (int)hipGetLastError();
 }
