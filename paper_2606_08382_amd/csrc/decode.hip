@@ -1352,27 +1352,18 @@ __device__ __forceinline__ float h2f(uint16_t u) { return (float)__builtin_bit_c
 __device__ __forceinline__ int region_hi_bits(int qmode) { return qmode == STARKV_Q_MIX8_4 ? 8 : 4; }
 __device__ __forceinline__ int region_lo_bits(int qmode) { return qmode == STARKV_Q_MIX4_3 ? 3 : 4; }
 
-// `bits`-wide field at bit `sh` of the little-endian word starting at w (the
-// word's bytes are read one at a time: 3-bit words are not aligned)
-__device__ __forceinline__ int code_field(const uint8_t* w, int sh, int bits) {
-  const int b0 = sh / 8;
-  uint32_t v = w[b0];
-  if (sh % 8 + bits > 8) v |= (uint32_t)w[b0 + 1] << 8;
-  return (int)((v >> (sh % 8)) & ((1u << bits) - 1));
-}
-
-// Dequantized key latent channels 8c .. 8c + 7 of head g, of token tau of the
+// Dequantized key latent channels 8c .. 8c + 7 of a head, of token tau of the
 // 16-token block blk: one code load (three bytes at 3 bits) and one (s, z) load.
-__device__ __forceinline__ void key_chunk(const CombineParams& p, int g, int64_t blk, int tau, int c,
-                                          float (&x)[8]) {
-  const uint8_t* code = p.cache + p.k_code_off[g] + blk * 16 * p.k_rb[g];
+__device__ __forceinline__ void key_chunk(const CombineParams& p, const CombineHead& kh, int64_t blk,
+                                          int tau, int c, float (&x)[8]) {
+  const uint8_t* code = p.cache + kh.code_off + blk * 16 * kh.rb;
   if (p.qmode == STARKV_Q_F16) {
     const u4 v = *reinterpret_cast<const u4*>(code + c * 256 + tau * 16);
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[e] = h2f((uint16_t)(v[e / 2] >> (16 * (e % 2))));
     return;
   }
-  const int ro = p.k_ro[g], nhi = ro / 8;
+  const int ro = kh.ro, nhi = ro / 8;
   const int hb = region_hi_bits(p.qmode), lb = region_lo_bits(p.qmode);
   const bool hi = c < nhi;
   const int bits = hi ? hb : lb;
@@ -1380,7 +1371,7 @@ __device__ __forceinline__ void key_chunk(const CombineParams& p, int g, int64_t
   const uint8_t* tok = code + (hi ? c * 16 * hb : nhi * 16 * hb + (c - nhi) * 16 * lb) + tau * bits;
   const int grp = hi ? c / 4 : (ro + 31) / 32 + (c - nhi) / 4;
   const uint32_t m = *reinterpret_cast<const uint32_t*>(
-      p.cache + p.k_meta_off[g] + (blk * p.k_ng[g] + grp) * 64 + tau * 4);
+      p.cache + kh.meta_off + (blk * kh.ng + grp) * 64 + tau * 4);
   uint64_t w;
   if (bits == 8) {
     const u2 d = *reinterpret_cast<const u2*>(tok);
@@ -1396,42 +1387,17 @@ __device__ __forceinline__ void key_chunk(const CombineParams& p, int g, int64_t
   for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf((float)((uint32_t)(w >> (bits * e)) & mask), s, z);
 }
 
-// Dequantized value latent channel r of token u of the 32-token block blk.
-__device__ __forceinline__ float value_latent(const CombineParams& p, int64_t blk, int u, int r) {
-  const int kq = u % 4, slot = 4 * (u / 16) + (u % 16) / 4;
-  const uint8_t* code = p.cache + p.v_code_off + blk * 32 * p.v_rb;
-  if (p.qmode == STARKV_Q_F16)
-    return h2f(*reinterpret_cast<const uint16_t*>(code + (r * 4 + kq) * 16 + slot * 2));
-  const int hb = region_hi_bits(p.qmode), lb = region_lo_bits(p.qmode);
-  const bool hi = r < p.v_ro;
-  const int bits = hi ? hb : lb;
-  // (channel, chunk) words of `bits` bytes, the outlier region first
-  const uint8_t* wd = code + (hi ? (r * 4 + kq) * hb : 4 * p.v_ro * hb + ((r - p.v_ro) * 4 + kq) * lb);
-  int q;
-  if (bits == 8) {
-    q = wd[slot];
-  } else {
-    // slot 2k / 2k+1 at fields k / k+4 of the word (4 bits: 4 bits apiece and the
-    // second half at bit 16; 3 bits: 3 bits apiece and the second half at bit 12)
-    const int sh = bits == 4 ? ((slot & 1) ? 16 + 4 * (slot / 2) : 4 * (slot / 2))
-                             : ((slot & 1) ? 12 + 3 * (slot / 2) : 3 * (slot / 2));
-    q = code_field(wd, sh, bits);
-  }
-  const int grp = hi ? r / 32 : (p.v_ro + 31) / 32 + (r - p.v_ro) / 32;
-  const uint8_t* m = p.cache + p.v_meta_off + blk * p.v_ng * 128 + (grp * 4 + kq) * 32;
-  return __builtin_fmaf((float)q, h2f(reinterpret_cast<const uint16_t*>(m)[slot]),
-                        h2f(reinterpret_cast<const uint16_t*>(m + 16)[slot]));
-}
-
 // LDS of the combine kernel in floats: a fixed head, then one region that in
 // turn holds the waves' split sums [NW][rv], the rescoring's key latents
-// [rmax][8 NW] and B_k block (fp16 [rmax][D]), its value sums [groups][rv] and
-// the up-projection's partial sums [NW][Dc].
+// [rmax][8 NW] with the B_k block behind them ([rmax][D/2] fp16 pairs j, j + D/2), its value
+// sums [NW][rv] and the up-projection's partial sums [NW][Dc].
 __host__ __device__ constexpr int combine_head_floats(int rv, int nw) {
   return (rv + 2 * kCombineMaxSplits + 4 * kRescoreMax + kCandChunk + 4 * nw + 4 + 3 * nw + 3) / 4 * 4;
 }
-__host__ __device__ constexpr int combine_value_groups(int rv, int nw) {
-  return 64 * nw / rv > 1 ? 64 * nw / rv : 1;
+// B_k's place in the region: behind the split sums (it is loaded before they are read) and
+// the latents.  At the largest ranks (1024, 128) and sixteen waves the kernel holds 107 KB.
+__host__ __device__ constexpr int combine_bk_at(int rv, int rmax, int nw) {
+  return nw * rv > 8 * nw * rmax ? nw * rv : 8 * nw * rmax;
 }
 
 // NW: waves of the workgroup.
@@ -1452,6 +1418,16 @@ __host__ __device__ constexpr int combine_value_groups(int rv, int nw) {
 // Measured against the one-candidate-and-pair-per-item form on four waves: decode
 // calls of 4 x 128K tokens with about 100 candidates a head 276 -> 191 us, of 4 x 32K
 // 108 -> 83 us, of 6 short contexts 81 -> 52 us, of 8 x 4K 70 -> 50 us.
+//
+// What remained were memory round trips in a chain (arguments of the head's record, the
+// candidates, B_k) with sixteen waves, and vector-ALU issue with four: B_k, the query and the
+// first candidates are loaded before the merge, the fp64 angle is kept in turns (no range
+// reduction in the sine), the dot products of a wave's eight candidates are reduced
+// together (10 lane exchanges instead of 48), and the value sums take their token from
+// scalars instead of decoding block, chunk and slot per channel.  In traces: four waves
+// (32 ragged sequences, 1024 workgroups) 95.9 -> 38.1 us, sixteen waves 26.9 -> 19.8 (six
+// short contexts), 32.9 -> 21.4 (4 x 8K, absorbed), 40.0 -> 28.1 (4 x 128K, peaked),
+// 17.0 -> 14.2 (1 x 1K); without candidates 8.9 -> 9.3.
 template <int NW, int D>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
 void decode_combine_kernel(CombineParams p) {
@@ -1480,7 +1456,16 @@ void decode_combine_kernel(CombineParams p) {
   // rescoring are repeated by each of the col_split workgroups of the head)
   const int Dc = D / p.col_split, c_0 = blockIdx.z * Dc;
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = (int)(((int64_t)i * p.n_kv) / p.n_q);
+  // All kernel arguments at once (see CombineParams).
+#define SK_TOUCH(k) "s"(p.head[k].rank), "s"(p.head[(k) + 1].rank), "s"(p.head[(k) + 2].rank), "s"(p.head[(k) + 3].rank)
+  static_assert(STARKV_MAX_KV_HEADS == 16 && sizeof(CombineHead) <= 64, "a word of every line");
+  asm volatile("" :: SK_TOUCH(0), SK_TOUCH(4), SK_TOUCH(8), SK_TOUCH(12), "s"(p.part), "s"(p.bk),
+               "s"(p.q), "s"(p.ctx_len), "s"(p.lat), "s"(p.log2_theta), "s"(p.rmap.table),
+               "s"(p.n_q), "s"(p.part_stride), "s"(p.qmode), "s"(p.score_scale));
+#undef SK_TOUCH
+  const int g = i / p.group_q;
+  const CombineHead kh = p.head[g];
+  asm volatile("" :: "s"(kh.code_off), "s"(kh.rank), "s"(kh.bkrow));
   // this sequence's splits: under the work plan, items first .. first + ns - 1
   // (the split pass wrote the plan), else the fixed split grid
   int L, ns, first;
@@ -1596,6 +1581,53 @@ void decode_combine_kernel(CombineParams p) {
     Lsum = ls;
     any_cand = (wfl[0] | wfl[1] | wfl[2] | wfl[3]) != 0;
   }
+  // The KV head's up-projection block B_k goes to LDS as fp16 pairs (j, j + D/2) before
+  // the merge, behind the split sums, so that its latency passes there.
+  const int r_g = kh.rank;
+  uint32_t* bks = reinterpret_cast<uint32_t*>(uni + combine_bk_at(p.rv, p.rmax, NW));        // [r_g][HALF]
+  auto load_bk = [&]() {
+    const uint16_t* src = p.bk + (int64_t)kh.bkrow * D;
+    constexpr int VH = HALF / 8;
+    for (int v = tid; v < r_g * VH; v += NTH) {
+      const uint16_t* row = src + (v / VH) * D + 8 * (v % VH);
+      const u4 lo = *reinterpret_cast<const u4*>(row), hi = *reinterpret_cast<const u4*>(row + HALF);
+      u4 o[2];
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        o[e / 4][e % 4] = __builtin_amdgcn_perm(hi[e / 2], lo[e / 2], e & 1 ? 0x07060302u : 0x05040100u);
+      u4* dst = reinterpret_cast<u4*>(bks) + 2 * v;
+      dst[0] = o[0];
+      dst[1] = o[1];
+    }
+  };
+  // candidate entries: see the selection
+  static_assert(kCand == 64, "one slot per lane");
+  const float2* cand = p.cand + ((int64_t)first * p.n_q + i) * kCand;
+  float2 ce[KC];
+  auto load_entries = [&](int c) {
+    const float2* cl = cand + (int64_t)(kCandChunk * c + w) * p.n_q * kCand + lane;
+    const int64_t cstep = (int64_t)NW * p.n_q * kCand;
+#pragma unroll
+    for (int k = 0; k < KC; ++k) {
+      const int s = kCandChunk * c + NW * k + w;
+      ce[k] = make_float2(-INFINITY, 0.0f);
+      if (s < ns && ((sfl[s] >> (8 * (lane >> 4))) & 0xFFu) != 0u) ce[k] = cl[k * cstep];
+    }
+  };
+  // lane of the rescoring: RoPE pair l (its query and frequency in turns per token),
+  // candidates cj .. cj + NCL - 1 of the wave's eight
+  constexpr int NCL = HALF / 8;          // 8 with 64 pairs, 4 with 32
+  const int l = lane % HALF, cj = 8 * w + (lane / HALF) * NCL;
+  float q_lo = 0.0f, q_hi = 0.0f;
+  double turn = 0.0;
+  if (any_cand) {
+    load_entries(0);
+    const uint16_t* qs = static_cast<const uint16_t*>(p.q) + ((int64_t)b * p.n_q + i) * D;
+    q_lo = load_qf(qs, l, p.q_bf16);
+    q_hi = load_qf(qs, l + HALF, p.q_bf16);
+    load_bk();
+    turn = 0.15915494309189533576888376337251 * exp2(-(2.0 * l / D) * p.log2_theta);
+  }
   // weighted sums of this wave's splits, per channel, into red4[w][r]
   float* red4 = uni;
   auto add_batch = [&](int h, const f4 (&pv)[kSplitBatch], f4& acc) {
@@ -1639,18 +1671,9 @@ void decode_combine_kernel(CombineParams p) {
     // Candidate entries of the splits.  Thread tid takes slot `lane` of splits
     // 64 c + NW k + w of chunk c (entry order: split, then slot); a slot's block of
     // 16 entries holds data only when the split set its flag byte, and the rest
-    // read as -inf scores (never selected).
-    static_assert(kCand == 64, "one slot per lane");
-    const float2* cand = p.cand + ((int64_t)first * p.n_q + i) * kCand;
-    auto load_cand = [&](int c, float2 (&ce)[KC], float (&prio)[KC]) {
-      const float2* cl = cand + (int64_t)(kCandChunk * c + w) * p.n_q * kCand + lane;
-      const int64_t cstep = (int64_t)NW * p.n_q * kCand;
-#pragma unroll
-      for (int k = 0; k < KC; ++k) {
-        const int s = kCandChunk * c + NW * k + w;
-        ce[k] = make_float2(-INFINITY, 0.0f);
-        if (s < ns && ((sfl[s] >> (8 * (lane >> 4))) & 0xFFu) != 0u) ce[k] = cl[k * cstep];
-      }
+    // read as -inf scores (never selected).  Chunk 0 was loaded before the merge.
+    float prio[KC];
+    auto weigh = [&]() {
 #pragma unroll
       for (int k = 0; k < KC; ++k) {
         const float x = ce[k].x;
@@ -1725,12 +1748,10 @@ void decode_combine_kernel(CombineParams p) {
       return n;
     };
     const int n_cchunk = (ns + kCandChunk - 1) / kCandChunk;
-    float2 ce[KC];
-    float prio[KC];
     float tau = kRescoreTau;
     int n_sel = 0;
     if (n_cchunk == 1) {
-      load_cand(0, ce, prio);
+      weigh();
       int excl = scan(prio, tau, &n_sel);
       if (n_sel > kRescoreMax) {
         uint32_t lv[kLevels / 2] = {};
@@ -1744,7 +1765,8 @@ void decode_combine_kernel(CombineParams p) {
     } else {
       uint32_t lv[kLevels / 2] = {};
       for (int c = 0; c < n_cchunk; ++c) {
-        load_cand(c, ce, prio);
+        if (c > 0) load_entries(c);
+        weigh();
         count_levels(prio, lv);
       }
       n_sel = pick_level(lv, &tau);
@@ -1752,7 +1774,8 @@ void decode_combine_kernel(CombineParams p) {
         int base = 0;
         for (int c = 0; c < n_cchunk; ++c) {
           int n;
-          load_cand(c, ce, prio);
+          load_entries(c);
+          weigh();
           const int excl = scan(prio, tau, &n);
           scatter(ce, prio, tau, base, excl);
           base += n;
@@ -1761,22 +1784,10 @@ void decode_combine_kernel(CombineParams p) {
     }
     n_sel = min(n_sel, kRescoreMax);
     if (n_sel > 0) {
-      // the KV head's up-projection block B_k (r_g x D fp16) in LDS; the region's
-      // split sums were read before the barriers of the selection
-      const int r_g = p.k_rank[g], nch = r_g / 8;
-      float* lat = uni;                                              // [r_g][NB]
-      uint16_t* bks = reinterpret_cast<uint16_t*>(uni + p.rmax * NB);  // [r_g][D]
-      {
-        const u4* src = reinterpret_cast<const u4*>(p.bk + (int64_t)p.k_bkrow[g] * D);
-        for (int v = tid; v < r_g * D / 8; v += NTH) reinterpret_cast<u4*>(bks)[v] = src[v];
-      }
+      const int nch = r_g / 8;
+      float* lat = uni;                  // [r_g][NB]: the split sums were read before the
+                                         // barriers of the selection
       __syncthreads();                   // the candidates are visible
-      const uint16_t* qs = static_cast<const uint16_t*>(p.q) + ((int64_t)b * p.n_q + i) * D;
-      // lane: RoPE pair l, candidates cj .. cj + NCL - 1 of the wave's eight
-      constexpr int NCL = HALF / 8;      // 8 with 64 pairs, 4 with 32
-      const int l = lane % HALF, cj = 8 * w + (lane / HALF) * NCL;
-      const float q_lo = load_qf(qs, l, p.q_bf16), q_hi = load_qf(qs, l + HALF, p.q_bf16);
-      const double om = exp2(-(2.0 * l / D) * p.log2_theta);
       for (int j0 = 0; j0 < n_sel; j0 += NB) {
         const int nb = min(NB, n_sel - j0);
         if (j0 > 0) __syncthreads();     // the previous batch's latents are read
@@ -1784,7 +1795,7 @@ void decode_combine_kernel(CombineParams p) {
           const int j = it % NB, c = it / NB;
           if (j < nb) {
             float x[8];
-            key_chunk(p, g, c_b[j0 + j], c_t[j0 + j] % 16, c, x);
+            key_chunk(p, kh, c_b[j0 + j], c_t[j0 + j] % 16, c, x);
 #pragma unroll
             for (int e = 0; e < 8; ++e) lat[(8 * c + e) * NB + j] = x[e];
           }
@@ -1796,7 +1807,8 @@ void decode_combine_kernel(CombineParams p) {
           for (int e = 0; e < NCL; ++e) klo[e] = khi[e] = 0.0f;
 #pragma unroll 4
           for (int ch = 0; ch < r_g; ++ch) {
-            const float blo = h2f(bks[ch * D + l]), bhi = h2f(bks[ch * D + l + HALF]);
+            const h2 bp = as_h2(bks[ch * HALF + l]);
+            const float blo = (float)bp[0], bhi = (float)bp[1];
             const f4* x = reinterpret_cast<const f4*>(lat + ch * NB + cj);
 #pragma unroll
             for (int e = 0; e < NCL; e += 4) {
@@ -1808,20 +1820,33 @@ void decode_combine_kernel(CombineParams p) {
               }
             }
           }
+          float dot[NCL];
 #pragma unroll
           for (int e = 0; e < NCL; ++e) {
             const int j = min(cj + e, nb - 1);
-            // angle t * theta^(-2l/D), reduced modulo 2 pi in fp64
-            double ph = (double)c_t[j0 + j] * om;
-            ph -= 6.283185307179586476925286766559 * floor(ph * 0.15915494309189533576888376337251);
+            // angle in turns, reduced in fp64
+            const double ph = (double)c_t[j0 + j] * turn;
             float sf, cf;
-            sincosf((float)ph, &sf, &cf);
-            float dot = q_lo * (klo[e] * cf - khi[e] * sf) + q_hi * (khi[e] * cf + klo[e] * sf);
-            for (int o = HALF / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
-            if (l == 0 && cj + e < nb)
-              c_d[j0 + j] = __builtin_amdgcn_exp2f(dot * p.score_scale - M) -
-                            __builtin_amdgcn_exp2f(c_x[j0 + j] - M);
+            sincospif(2.0f * (float)(ph - floor(ph)), &sf, &cf);
+            dot[e] = q_lo * (klo[e] * cf - khi[e] * sf) + q_hi * (khi[e] * cf + klo[e] * sf);
           }
+          // sums over the pairs' lanes, halving the candidates per lane with the
+          // lanes: candidate l / 8 ends in lanes 8 (l / 8) ..+7
+#pragma unroll
+          for (int n = NCL / 2, o = HALF / 2; n >= 1; n /= 2, o /= 2) {
+            const bool up = (l & o) != 0;
+#pragma unroll
+            for (int e = 0; e < n; ++e) {
+              const float give = up ? dot[e] : dot[e + n];
+              dot[e] = (up ? dot[e + n] : dot[e]) + __shfl_xor(give, o);
+            }
+          }
+          float ds = dot[0];
+          for (int o = 4; o > 0; o >>= 1) ds += __shfl_xor(ds, o);
+          const int j = cj + l / 8;
+          if (l % 8 == 0 && j < nb)
+            c_d[j0 + j] = __builtin_amdgcn_exp2f(ds * p.score_scale - M) -
+                          __builtin_amdgcn_exp2f(c_x[j0 + j] - M);
         }
       }
       __syncthreads();
@@ -1829,30 +1854,95 @@ void decode_combine_kernel(CombineParams p) {
       float dl = (lane < n_sel ? c_d[lane] : 0.0f) + (lane + 64 < n_sel ? c_d[lane + 64] : 0.0f);
       for (int o = 32; o > 0; o >>= 1) dl += __shfl_xor(dl, o);
       inv_l = 1.0f / (Lsum + dl);
-      // value latents of the rescored tokens: thread (group, channel), a group
-      // taking every n_vg-th candidate, eight candidates' loads in flight
-      const int n_vg = combine_value_groups(p.rv, NW);
-      float* vred = uni;                 // [n_vg][rv]: key latents and B_k are read
-      for (int it = tid; it < n_vg * p.rv; it += NTH) {
-        const int r = it % p.rv, vg = it / p.rv;
-        float acc = 0.0f;
-        for (int j0 = vg; j0 < n_sel; j0 += 8 * n_vg) {
-          float vl[8];
+      // Value latents of the rescored tokens: wave w takes every NW-th candidate, a
+      // lane four channels, so that a token's block, chunk and slot are scalars; four
+      // tokens' loads are in flight.
+      float* vred = uni;                 // [NW][rv]: key latents and B_k are read
+      const int hb = region_hi_bits(p.qmode), lb = region_lo_bits(p.qmode);
+      auto value_sums = [&](auto qm_tag) {
+        constexpr int QM = decltype(qm_tag)::value;
+        constexpr bool F16 = QM == STARKV_Q_F16, B3 = QM == STARKV_Q_MIX4_3;
+        constexpr int U = 4;
+        for (int r0 = 0; r0 < p.rv; r0 += 256) {
+          uint32_t co[4], mo[4];         // code word of chunk 0, (s, z) row of its group
+          bool hi[4];
+          float acc[4] = {0, 0, 0, 0};
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int j = min(j0 + u * n_vg, n_sel - 1);
-            vl[u] = value_latent(p, c_b[j] >> 1, c_t[j] % 32, r);
+          for (int k = 0; k < 4; ++k) {
+            const int r = min(r0 + 64 * k + lane, p.rv - 1);
+            hi[k] = r < p.v_ro;
+            co[k] = F16 ? r * 64 : hi[k] ? r * 4 * hb : 4 * p.v_ro * hb + (r - p.v_ro) * 4 * lb;
+            mo[k] = (hi[k] ? r / 32 : (p.v_ro + 31) / 32 + (r - p.v_ro) / 32) * 128;
+          }
+          for (int j0 = w; j0 < n_sel; j0 += U * NW) {
+            uint32_t c0[U][4], c1[U][4], sv[U][4], zv[U][4];
+            int shh[U], shl[U];
+            float wt[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const int j = min(j0 + u * NW, n_sel - 1);
+              const int t = __builtin_amdgcn_readfirstlane(c_t[j]) & 31;
+              const int64_t blk = __builtin_amdgcn_readfirstlane(c_b[j]) >> 1;
+              wt[u] = c_d[j];
+              const int kq = t & 3, slot = 4 * (t >> 4) + ((t & 15) >> 2);
+              const uint8_t* code = p.cache + p.v_code_off + blk * 32 * p.v_rb;
+              const uint8_t* m = p.cache + p.v_meta_off + blk * p.v_ng * 128 + kq * 32 + slot * 2;
+              // slot 2k / 2k+1 at fields k / k+4 of the word (8 bits: byte `slot`; 4 bits:
+              // 4 bits apiece and the second half at bit 16; 3 bits: 3 bits apiece and the
+              // second half at bit 12)
+              const int s4 = (slot & 1) * 16 + 4 * (slot / 2);
+              shh[u] = QM == STARKV_Q_MIX8_4 ? 8 * slot : s4;
+              shl[u] = B3 ? (slot & 1) * 12 + 3 * (slot / 2) : s4;
+#pragma unroll
+              for (int k = 0; k < 4; ++k) {
+                if (r0 + 64 * k >= p.rv) continue;
+                if (F16) {
+                  c0[u][k] = *reinterpret_cast<const uint16_t*>(code + (kq * 16 + slot * 2) + co[k]);
+                } else {
+                  const uint8_t* wd = code + (co[k] + (hi[k] ? kq * hb + (shh[u] >> 3) : kq * lb + (shl[u] >> 3)));
+                  c0[u][k] = wd[0];
+                  // a 3-bit field may end in the word's next byte
+                  if (B3) c1[u][k] = wd[!hi[k] && (shl[u] >> 3) < 2 ? 1 : 0];
+                  sv[u][k] = *reinterpret_cast<const uint16_t*>(m + mo[k]);
+                  zv[u][k] = *reinterpret_cast<const uint16_t*>(m + 16 + mo[k]);
+                }
+              }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+              for (int k = 0; k < 4; ++k) {
+                if (r0 + 64 * k >= p.rv) continue;
+                float x;
+                if (F16) {
+                  x = h2f((uint16_t)c0[u][k]);
+                } else {
+                  const uint32_t c = B3 ? c0[u][k] | c1[u][k] << 8 : c0[u][k];
+                  const uint32_t q = hi[k] ? c >> (shh[u] & 7) & ((1u << hb) - 1)
+                                           : c >> (shl[u] & 7) & ((1u << lb) - 1);
+                  x = __builtin_fmaf((float)q, h2f((uint16_t)sv[u][k]), h2f((uint16_t)zv[u][k]));
+                }
+                if (j0 + u * NW < n_sel) acc[k] = __builtin_fmaf(wt[u], x, acc[k]);
+              }
           }
 #pragma unroll
-          for (int u = 0; u < 8; ++u)
-            if (j0 + u * n_vg < n_sel) acc = __builtin_fmaf(c_d[j0 + u * n_vg], vl[u], acc);
+          for (int k = 0; k < 4; ++k) {
+            const int r = r0 + 64 * k + lane;
+            if (r < p.rv) vred[w * p.rv + r] = acc[k];
+          }
         }
-        vred[vg * p.rv + r] = acc;
+      };
+      switch (p.qmode) {
+        case STARKV_Q_F16: value_sums(std::integral_constant<int, STARKV_Q_F16>{}); break;
+        case STARKV_Q_INT4: value_sums(std::integral_constant<int, STARKV_Q_INT4>{}); break;
+        case STARKV_Q_MIX8_4: value_sums(std::integral_constant<int, STARKV_Q_MIX8_4>{}); break;
+        default: value_sums(std::integral_constant<int, STARKV_Q_MIX4_3>{}); break;
       }
       __syncthreads();
       for (int r = tid; r < p.rv; r += NTH) {
         float acc = a[r];
-        for (int vg = 0; vg < n_vg; ++vg) acc += vred[vg * p.rv + r];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) acc += vred[k * p.rv + r];
         a[r] = acc;
       }
     }
@@ -2021,11 +2111,9 @@ static int launch_combine_t(const CombineParams& p, hipStream_t st) {
   // the shared region: the split sums, the rescoring's key latents and B_k
   // block, its value sums, or the up-projection's partial sums
   const size_t dc = (size_t)D / p.col_split;
-  size_t region = (size_t)NW * p.rv;
-  region = std::max(region, (size_t)8 * NW * p.rmax + (size_t)p.rmax * D / 2);
-  region = std::max(region, (size_t)combine_value_groups(p.rv, NW) * p.rv);
-  region = std::max(region, (size_t)NW * dc);
-  const size_t lds = ((size_t)combine_head_floats(p.rv, NW) + region) * sizeof(float);
+  const size_t bk = (size_t)p.rmax * D / 2;
+  const size_t head = combine_head_floats(p.rv, NW);
+  const size_t lds = (head + std::max(combine_bk_at(p.rv, p.rmax, NW) + bk, NW * dc)) * sizeof(float);
   auto k = decode_combine_kernel<NW, D>;
   static std::atomic<uint64_t> attr{0};
   if (const int e = allow_lds(reinterpret_cast<const void*>(k), attr)) return e;

@@ -830,6 +830,7 @@ static void combine_params(const starkv_plan* P, const void* cache, const void* 
   p.batch = c.batch;
   p.n_q = c.n_q_heads;
   p.n_kv = c.n_kv_heads;
+  p.group_q = c.n_q_heads / c.n_kv_heads;
   p.head_dim = c.head_dim;
   p.rv = c.value_rank;
   p.max_ctx = max_ctx;
@@ -853,13 +854,14 @@ static void combine_params(const starkv_plan* P, const void* cache, const void* 
   p.score_scale = (float)(1.4426950408889634 / std::sqrt((double)c.head_dim));
   p.log2_theta = std::log2(c.rope_theta);
   for (int g = 0; g < c.n_kv_heads; ++g) {
-    p.k_code_off[g] = L.key_code_offset[g];
-    p.k_meta_off[g] = L.key_meta_offset[g];
-    p.k_rank[g] = P->key_rank[g];
-    p.k_ro[g] = L.key_outlier_channels[g];
-    p.k_ng[g] = L.key_groups[g];
-    p.k_rb[g] = L.key_row_bytes[g];
-    p.k_bkrow[g] = P->bk_row[g];
+    CombineHead& h = p.head[g];
+    h.code_off = L.key_code_offset[g];
+    h.meta_off = L.key_meta_offset[g];
+    h.rank = P->key_rank[g];
+    h.ro = L.key_outlier_channels[g];
+    h.ng = L.key_groups[g];
+    h.rb = L.key_row_bytes[g];
+    h.bkrow = P->bk_row[g];
     p.rmax = std::max(p.rmax, P->key_rank[g]);
   }
   p.v_code_off = L.value_code_offset;

@@ -147,6 +147,15 @@ constexpr int kCand = 64;      // rescoring candidates per (sequence, split, que
 // reaches this
 constexpr float kRescoreTau = 1.0f / 64.0f;
 
+// A KV head's planes in the cache and its rows of B_k.
+struct CombineHead {
+  int64_t code_off, meta_off;
+  int32_t rank, ro, ng, rb, bkrow, unused;
+};
+
+// Kernel arguments lie in host memory (see PolyParams): the combine kernel reads the
+// scalars and a word of every line of the head records at once at its start, then its
+// head's record.
 struct CombineParams {
   const float* part;
   const float2* cand;
@@ -160,23 +169,20 @@ struct CombineParams {
   // up-projected output, as fp16 parts [2][B][H_q * r_v] (hi = fp16(x), then
   // lo = fp16(x - hi)); bv and out are unused
   uint16_t* lat;
-  int32_t batch, n_q, n_kv, head_dim, rv;
+  const int32_t* plan;         // dyn: the split pass's per-sequence plan (DecodeParams::plan)
+  double log2_theta;
+  int64_t v_code_off, v_meta_off;
+  RowMap rmap;
+  int32_t batch, n_q, n_kv, group_q, head_dim, rv;
   int32_t max_ctx, split_len, n_split, part_stride;
   int32_t dyn, k_lo, cap;      // as in DecodeParams
-  const int32_t* plan;         // dyn: the split pass's per-sequence plan (DecodeParams::plan)
   int32_t out_dtype, q_bf16, qmode;
   int32_t rmax;                // largest key rank (sizes the rescoring buffers)
   int32_t col_split;           // workgroups per (sequence, query head), each taking
                                // head_dim / col_split output columns (1 or 2; 1 with lat)
-  RowMap rmap;
-  float score_scale;
-  double log2_theta;
-  // key head of this query head's group and the value latent (cache layout)
-  int64_t k_code_off[STARKV_MAX_KV_HEADS], k_meta_off[STARKV_MAX_KV_HEADS];
-  int32_t k_rank[STARKV_MAX_KV_HEADS], k_ro[STARKV_MAX_KV_HEADS], k_ng[STARKV_MAX_KV_HEADS];
-  int32_t k_rb[STARKV_MAX_KV_HEADS], k_bkrow[STARKV_MAX_KV_HEADS];
-  int64_t v_code_off, v_meta_off;
   int32_t v_ro, v_ng, v_rb;
+  float score_scale;
+  CombineHead head[STARKV_MAX_KV_HEADS];
 };
 
 // y [B][n_out] = lat [B][k] . w^T, w [n_out][k] fp16, lat as two fp16 parts
