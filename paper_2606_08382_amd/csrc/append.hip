@@ -11,6 +11,7 @@
 //   not finite), so the codes do not depend on evaluation order.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "starkv_internal.h"
@@ -774,25 +775,35 @@ __global__ __launch_bounds__(256) void downproj_small_kernel(DownprojParams p) {
 // (64 WMW) x (TN WNW) tile, each wave 64 x TN; k steps of 64 are staged in LDS
 // with a padded row (conflict-free 16-byte reads), double buffered: the next
 // step's global loads are in flight while the current step's MFMAs run.  Large
-// problems take 256 x 192 tiles of eight 64 x 96 waves (LDS traffic per flop a
-// third lower than with 64 x 48 waves), smaller ones 128 x 96 tiles of four
-// waves.
+// problems take the kernel below, smaller ones 128 x 96 tiles of four waves.
 constexpr int GK = 64, GKP = GK + 8;
 
+// A_all [K][N] -> [N][K], 64 x 64 tiles.  Bound by memory: sixteen-byte loads and stores
+// (K a multiple of 64, N of 8, both pointers aligned), eight lanes on 128 bytes of a row; the
+// odd pitch of 33 words leaves two-way bank conflicts on the gathers.
 __global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* a, uint16_t* at,
                                                              int K, int N) {
-  __shared__ uint16_t t[64][66];
+  __shared__ uint32_t t[64][33];
   const int k0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-    const int r = i / 64, c = i % 64;             // r: k, c: n (coalesced reads)
-    const int k = k0 + r, n = n0 + c;
-    t[r][c] = (k < K && n < N) ? a[(int64_t)k * N + n] : (uint16_t)0;
-  }
+  const int row = threadIdx.x / 8, vec = threadIdx.x % 8;
+  u4 v[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    v[i] = *reinterpret_cast<const u4*>(a + (int64_t)(k0 + row + 32 * i) * N + min(n0 + 8 * vec, N - 8));
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[row + 32 * i][4 * vec + e] = v[i][e];
   __syncthreads();
-  for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-    const int r = i / 64, c = i % 64;             // r: n, c: k (coalesced writes)
-    const int n = n0 + r, k = k0 + c;
-    if (n < N && k < K) at[(int64_t)n * K + k] = t[c][r];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int n = row + 32 * i;
+    u4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      o[e] = __builtin_amdgcn_perm(t[8 * vec + 2 * e + 1][n / 2], t[8 * vec + 2 * e][n / 2],
+                                   n & 1 ? 0x07060302u : 0x05040100u);
+    if (n0 + n < N) *reinterpret_cast<u4*>(at + (int64_t)(n0 + n) * K + k0 + 8 * vec) = o;
   }
 }
 
@@ -891,46 +902,66 @@ __global__ __launch_bounds__(64 * WMW * WNW) void gemm_bf16_nt_kernel(DownprojPa
       }
 }
 
-// The large-problem tile (256 x 192) with its operands copied from global
-// memory straight into LDS (global_load_lds, 16 bytes per lane) instead of
-// through registers, which leaves registers for sixteen waves of 64 x 48 (four
-// per SIMD: the other waves hide each one's fragment reads and the step's
-// barrier, worth a third of the GEMM time against two per SIMD): unpadded
-// 128-byte rows of 64 k whose
+// Large problems: the operands are copied from global memory straight into LDS
+// (global_load_lds, 16 bytes per lane) instead of through registers, which leaves
+// registers for three or four waves per SIMD (the other waves hide each one's
+// fragment reads and the step's barrier): unpadded 128-byte rows of 64 k whose
 // 16-byte chunk c sits in slot c ^ (row % 8), each lane of a copy fetching the
 // chunk that lands where the swizzle wants it, so that a fragment read (one
-// chunk of 16 rows) covers eight distinct slots per eight lanes.  Two stages;
-// the next step's copies are issued at the start of a step.
-constexpr int GDM = 256, GDN = 192, GDWN = 4;   // 16 waves of 64 x 48: four per SIMD
-constexpr int GDA = GDM / 8, GDB = GDN / 8;       // 1 KiB copies per k step (A, B)
-constexpr int GDSTAGE = (GDM + GDN) * 128;
+// chunk of 16 rows) covers eight distinct slots per eight lanes.  One workgroup of
+// 4 x WN waves per compute unit computes 256 x (16 NT WN); ST stages (three where LDS
+// holds them), the copies of ST - 1 steps in flight, one barrier a step.  It is bound by the
+// copies' latency and by compute units without a tile: 8192 x 1072 x 8192 in 192 tiles of
+// 192 columns and two stages took 155 us, in 256 tiles of 144 and three stages 141 (two
+// stages 159), 1.02 PFLOP/s.  The transpose before it 17.0 -> 8.6 us with 16-byte accesses.
+constexpr int GDM = 256, GDA = GDM / 8;          // rows; 1 KiB copies of A per k step
 
-// WN waves across the 192 columns (tiles of 192 / WN), four across the rows.
-template <int WN>
+// 1 KiB: lane l's 16 bytes from its src to dst + 16 l
+__device__ __forceinline__ void copy_to_lds(const uint16_t* src, uint8_t* dst) {
+  __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
+}
+
+template <int N>
+__device__ __forceinline__ void wait_copies_barrier() {   // all but the wave's N youngest copies
+  static_assert(N < 16, "low bits of vmcnt");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | N);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+template <int WN, int NT, int ST>
 __global__ __launch_bounds__(256 * WN) void gemm_bf16_nt_dma_kernel(DownprojParams p) {
-  constexpr int NW = 4 * WN, TN = GDN / WN, NT = TN / 16;
-  __shared__ __align__(16) uint8_t sm[2 * GDSTAGE];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  constexpr int NW = 4 * WN, TN = 16 * NT, GN = TN * WN;
+  constexpr int COPIES = GDA + GN / 8, CPW = (COPIES + NW - 1) / NW;
+  constexpr int STAGE = (GDM + GN) * 128;
+  __shared__ __align__(16) uint8_t sm[ST * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = p.m, N = p.n, K = p.k;            // K is a multiple of GK (checked by the host)
   // tiles row-major, a contiguous run per XCD (workgroup i on XCD i % 8)
-  const int n_ct = (N + GDN - 1) / GDN, n_t = n_ct * ((M + GDM - 1) / GDM);
+  const int n_ct = (N + GN - 1) / GN, n_t = n_ct * ((M + GDM - 1) / GDM);
   const int per_xcd = (n_t + 7) / 8;
   const int t = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (t >= n_t) return;
-  const int n0 = (t % n_ct) * GDN, m0 = (t / n_ct) * GDM;
+  const int n0 = (t % n_ct) * GN, m0 = (t / n_ct) * GDM;
   const int wm = (w / WN) * 64, wn = (w % WN) * TN;
   // copy j of a k step: rows 8 j' .. 8 j' + 7 of the A tile (j < GDA) or of the
   // B tile (j' = j - GDA); lane l fills slot l % 8 of row l / 8 with the global
-  // chunk (l % 8) ^ (l / 8)
+  // chunk (l % 8) ^ (l / 8).  Wave w takes copies w, w + NW, ..
   const int crow = lane >> 3, cchunk = (lane & 7) ^ crow;
+  const uint16_t* src[CPW];
+#pragma unroll
+  for (int i = 0; i < CPW; ++i) {
+    const int j = w + NW * i;
+    src[i] = (j < GDA ? p.x + (int64_t)min(m0 + 8 * j + crow, M - 1) * K
+                      : p.at + (int64_t)min(n0 + 8 * (j - GDA) + crow, N - 1) * K) + 8 * cchunk;
+  }
+  const bool all = w + NW * (CPW - 1) < COPIES;   // CPW copies a step, else CPW - 1
   auto issue = [&](int k0, int buf) {
-    uint8_t* st = sm + buf * GDSTAGE;
-    for (int j = w; j < GDA + GDB; j += NW) {
-      const uint16_t* src;
-      if (j < GDA) src = p.x + (int64_t)min(m0 + 8 * j + crow, M - 1) * K;
-      else src = p.at + (int64_t)min(n0 + 8 * (j - GDA) + crow, N - 1) * K;
-      __builtin_amdgcn_global_load_lds(src + k0 + 8 * cchunk, st + j * 1024, 16, 0, 0);
-    }
+    uint8_t* st = sm + buf * STAGE;
+#pragma unroll
+    for (int i = 0; i < CPW; ++i)
+      if (i < CPW - 1 || all)
+        copy_to_lds(src[i] + k0, st + (w + NW * i) * 1024);
   };
   const int fr = lane & 15, kq = lane >> 4;
   f4 acc[4][NT];
@@ -940,12 +971,16 @@ __global__ __launch_bounds__(256 * WN) void gemm_bf16_nt_dma_kernel(DownprojPara
     for (int j = 0; j < NT; ++j) acc[i][j] = (f4){0, 0, 0, 0};
   const int nk = K / GK;
   issue(0, 0);
-  __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
-  __syncthreads();
+  if (ST == 3 && nk > 1) issue(GK, 1);
+  int buf = 0;
   for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) issue((kt + 1) * GK, buf ^ 1);
-    const uint8_t* sa = sm + buf * GDSTAGE;
+    // this step's copies of every wave have landed, and the buffer of the step before
+    // is free: its fragment reads are past
+    if (ST == 2 || kt + 1 == nk) wait_copies_barrier<0>();
+    else if (all) wait_copies_barrier<CPW>();
+    else wait_copies_barrier<CPW - 1>();
+    if (kt + ST - 1 < nk) issue((kt + ST - 1) * GK, buf == 0 ? ST - 1 : buf - 1);
+    const uint8_t* sa = sm + buf * STAGE;
     const uint8_t* sb = sa + GDM * 128;
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {                 // 32 k each: chunks 4 kk + kq
@@ -967,8 +1002,7 @@ __global__ __launch_bounds__(256 * WN) void gemm_bf16_nt_dma_kernel(DownprojPara
         for (int j = 0; j < NT; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);             // this wave's copies of the next step
-    __syncthreads();                                 // every wave's; buf is free
+    buf = buf == ST - 1 ? 0 : buf + 1;
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -1006,16 +1040,27 @@ int launch_downproj(const DownprojParams& p, void* stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(transpose_bf16_kernel, dim3((p.n + 63) / 64, (p.k + 63) / 64), dim3(256), 0,
                        st, p.a, p.at, p.k, p.n);
-    // 256 x 192 tiles when they give at least 96 workgroups (one per CU),
-    // else 128 x 96 tiles (then at most 4 x 96 of them: a single round at two
-    // workgroups per CU)
-    if (((p.m + 255) / 256) * ((p.n + 191) / 192) >= 96)
-      hipLaunchKernelGGL((gemm_bf16_nt_dma_kernel<GDWN>),
-                         dim3(8 * ((((p.n + 191) / 192) * ((p.m + 255) / 256) + 7) / 8)), dim3(256 * GDWN), 0, st, p);
-    else
+    const int rows = (p.m + GDM - 1) / GDM;
+    auto tiles = [&](int gn) { return rows * ((p.n + gn - 1) / gn); };
+    auto cost = [&](int gn) { return (int64_t)((tiles(gn) + 255) / 256) * (gn + 115); };
+    // 256-row tiles when those of 192 columns give at least 96 workgroups (one per CU),
+    // else 128 x 96 tiles (then at most 4 x 96 of them: a single round at two workgroups
+    // per CU).  Their width: a round of at most one workgroup per CU takes a time in
+    // proportion to width + 115 (fit of single rounds, K = 4096 and 8192), so the width
+    // with the least sum over the rounds.  Whole appends with 192 / 144 / 128 columns, us:
+    // 8192 x 1072 x 8192 188 / 160 / 238, 4096 x 1072 x 8192 141 / 123 / 116,
+    // 8192 x 512 x 4096 77 / 68 / 64, 16384 x 688 x 4096 102 / 137 / 126.
+    if (tiles(192) >= 96) {
+      const int gn = cost(128) < std::min(cost(144), cost(192)) ? 128 : cost(144) < cost(192) ? 144 : 192;
+      const dim3 grid(8 * ((tiles(gn) + 7) / 8));
+      if (gn == 128) hipLaunchKernelGGL((gemm_bf16_nt_dma_kernel<4, 2, 3>), grid, dim3(1024), 0, st, p);
+      else if (gn == 144) hipLaunchKernelGGL((gemm_bf16_nt_dma_kernel<3, 3, 3>), grid, dim3(768), 0, st, p);
+      else hipLaunchKernelGGL((gemm_bf16_nt_dma_kernel<4, 3, 2>), grid, dim3(1024), 0, st, p);
+    } else {
       hipLaunchKernelGGL((gemm_bf16_nt_kernel<2, 2, 48>),
                          dim3(8 * ((((p.n + 95) / 96) * ((p.m + 127) / 128) + 7) / 8)),
                          dim3(256), 0, st, p);
+    }
     return (int)hipGetLastError();
   }
   if (p.m <= kSmallM) {
