@@ -7,7 +7,7 @@
 // d = -64 .. 63 the token's offset from it.  Only the first frequencies turn
 // far inside a step.  For the others cos and sin of w_j d are polynomials of
 // degree M - 1 in x = d/64 to fp16 accuracy (Chebyshev series, |w_j d| <= 2.4
-// for M = 8, <= 0.46 for M = 4), so their part of the score is
+// for M = 8), so their part of the score is
 //     sum_m x^m (W_m . c),   W_m = sum_j coef_mj (B_k rows of j applied to q'),
 // with c the token's dequantized latent: the key is never rebuilt nor rotated
 // in those dimensions.  W_m (r channels) is formed once per step, head and query
@@ -323,8 +323,9 @@ __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, 
   const uint8_t *qsrc_lo, *qsrc_hi, *qop, *coef, *cs;
   {
     // row (query i, term m) of the products with W_m
-    const int m = M == 8 ? 4 * ((cl >> 3) & 1) + (cl & 3) : cl & 3;
-    const int i = ((cl >> 2) & 1) + 2 * (M == 8 ? cl >> 4 : cl >> 3);
+    static_assert(M == 8, "four queries of eight terms per tile");
+    const int m = 4 * ((cl >> 3) & 1) + (cl & 3);
+    const int i = ((cl >> 2) & 1) + 2 * (cl >> 4);
     const uint8_t* row = (i < G ? W.q + i * ((D + 8) * 2) : W.zero) + 16 * hf;
     const bool odd = m & 1;
     qsrc_lo = row + (odd ? D : 0) + 32 * NHB;
@@ -455,12 +456,6 @@ __device__ constexpr float kWeights8[5][8] = {
     {-0.2f, -2.2627417f, 3.2f, 20.3646753f, -3.2f, -36.2038672f, 0.0f, 18.1019336f},
     {-0.0689153034f, 2.34301927f, 7.3662331f, -3.73302358f, -19.2491395f, -2.48278063f, 12.1735234f, 4.00472231f},
     {1.13914351f, 4.51639422f, -7.58175341f, -26.3417852f, 13.8743312f, 44.4425757f, -7.52365123f, -22.809767f}};
-__device__ constexpr float kWeights4[5][4] = {
-    {-0.180422607f, -0.674132493f, 0.760845213f, 1.42561044f},
-    {-0.0351141009f, 0.168681252f, 0.470228202f, 0.250295144f},
-    {0.2f, 1.13137085f, 0.0f, -1.13137085f},
-    {0.435114101f, 1.36682221f, -0.470228202f, -1.58030134f},
-    {0.580422607f, 0.607362386f, -0.760845213f, -0.7263848f}};
 
 // NHB: fast blocks of 16 RoPE pairs; M: polynomial terms; NS: tokens per lane;
 // CT: 16-query tiles; NTW: 16-channel value tiles per wave; MAXP: most pairs (of 8
@@ -650,7 +645,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     float c = 0.0f;
 #pragma unroll
     for (int k = 0; k < 5; ++k)
-      c += (M == 8 ? kWeights8[k][w] : kWeights4[k][w & 3]) *
+      c += kWeights8[k][w] *
            (w & 1 ? sinf(a * kNodes[k]) : cosf(a * kNodes[k]));
     const int j = lane - J0;
     _Float16* dst = reinterpret_cast<_Float16*>(smem + LL.coef) + ((j >> 3) * M + w) * 8 + (j & 7);
@@ -1178,8 +1173,6 @@ int SK_NAME(SK_D, SK_QM)(const PolyParams& p, const PolyShape& s, size_t lds, hi
     if (s.ns == 4 && s.ct == 2) return dispatch_ntw<SK_D, SK_QM, 2, 8, 4, 2>(p, s, lds, st);
     if (s.ns == 2 && s.ct == 1) return dispatch_ntw<SK_D, SK_QM, 2, 8, 2, 1>(p, s, lds, st);
   }
-  if (s.m == 4 && s.nhb == 2 && s.ns == 2 && s.ct == 2)
-    return dispatch_ntw<SK_D, SK_QM, 2, 4, 2, 2>(p, s, lds, st);
 #endif
   return (int)hipErrorInvalidValue;
 }

@@ -93,13 +93,13 @@ namespace {
 
 // Chooses the polynomial-rotation split kernel (split_poly.hip) and its shape.
 //
-// Terms and fast blocks: eight terms serve four query heads per 32-row matrix tile,
-// four terms eight; the first dropped Chebyshev term of the fastest frequency left
-// to the polynomial, 2 J_M(64 w_j), must stay below 2^-12, fp16's rounding of a
-// value below one: 64 w_j <= 2.44 with eight terms, <= 0.46 with four (w_j =
-// theta^(-2j/d); at theta = 5e5, d = 128: one fast block of 16 pairs with eight
-// terms, two with four).  The general kernel stays for more than eight query
-// heads per KV head, rope bases whose frequencies are all fast, value ranks above
+// Terms and fast blocks: eight terms serve four query heads per 32-row matrix tile; the
+// first dropped Chebyshev term of the fastest frequency left to the polynomial,
+// 2 J_8(64 w_j), must stay below 2^-12, fp16's rounding of a value below one:
+// 64 w_j <= 2.44 (w_j = theta^(-2j/d); at theta = 5e5, d = 128: one fast block of 16
+// pairs).  The general kernel stays for more than four query heads per KV head (four
+// terms and two fast blocks would serve eight; measured at 64 query and 8 KV heads,
+// 2 x 64K tokens: first calls 164 us against 149, repeated ones no faster), rope bases whose frequencies are all fast, value ranks above
 // 512 (accumulators beyond the register file), fp16 caches of ranks above 64 or 256
 // (a lane's prefetched codes), and at most two KV heads per workgroup, where a
 // wave per head leaves waves without key work (measured, one KV head: 4 of 8).
@@ -111,11 +111,9 @@ bool plan_poly(starkv_plan* P) {
   const int D = c.head_dim, G = c.n_q_heads / c.n_kv_heads, n_kv = c.n_kv_heads;
   if (G > 4) return false;
   PolyShape s;
-  s.m = G <= 4 ? 8 : 4;
-  const double a_max = s.m == 8 ? 2.44 : 0.46;
+  s.m = 8;
   for (s.nhb = 1; s.nhb <= 2; ++s.nhb)
-    if (64.0 * std::pow(c.rope_theta, -2.0 * 16 * s.nhb / D) <= a_max) break;
-  if (s.m == 4) s.nhb = std::max(s.nhb, 2);
+    if (64.0 * std::pow(c.rope_theta, -2.0 * 16 * s.nhb / D) <= 2.44) break;
   if (s.nhb > 2 || 32 * s.nhb >= D) return false;
   const int tiles = (c.value_rank / 16 + kWaves - 1) / kWaves;
   s.ntw = std::max(tiles, 2);
@@ -128,7 +126,7 @@ bool plan_poly(starkv_plan* P) {
   const int ks = (D - 32 * s.nhb) / 16;
   auto frag_of = [&](int g) { return P->key_rank[g] * (32 * ks + 64 * s.nhb) + 32 * ks; };
   auto cost_of = [&](int g) { return 4 + P->key_rank[g] / 16; };
-  const int max_heads = s.m == 8 ? 8 : 4;
+  const int max_heads = 8;
   int by_cost[STARKV_MAX_KV_HEADS];
   for (int g = 0; g < n_kv; ++g) by_cost[g] = g;
   std::stable_sort(by_cost, by_cost + n_kv, [&](int x, int y) { return cost_of(x) > cost_of(y); });
@@ -153,7 +151,7 @@ bool plan_poly(starkv_plan* P) {
       worst = std::max(worst, bytes[h]);
     }
     s.ns = most > 4 ? 4 : 2;
-    s.ct = s.ns == 4 || s.m == 4 ? 2 : 1;
+    s.ct = s.ns == 4 ? 2 : 1;
     if (poly_lds_bytes(s, D, worst, P->layout.value_groups) <= kLdsLimit) {
       P->poly_lds = poly_lds_bytes(s, D, worst, P->layout.value_groups);
       break;
