@@ -1465,7 +1465,6 @@ void decode_combine_kernel(CombineParams p) {
 #undef SK_TOUCH
   const int g = i / p.group_q;
   const CombineHead kh = p.head[g];
-  asm volatile("" :: "s"(kh.code_off), "s"(kh.rank), "s"(kh.bkrow));
   // this sequence's splits: under the work plan, items first .. first + ns - 1
   // (the split pass wrote the plan), else the fixed split grid
   int L, ns, first;
