@@ -310,7 +310,8 @@ struct PolyWave {
 // Scores of the wave's tokens: x[s][iq] for the lane's token s and query hf + 2 iq.
 template <int D, int QM, int NHB, int M, int NS, int NP>
 __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, NS, NP>& raw, int lane,
-                                            int G, float x0, float (&sc)[NS][16 / M]) {
+                                            int G, float x0, float s_scale,
+                                            float (&sc)[NS][16 / M]) {
   constexpr int KS = (D - 32 * NHB) / 16;    // 16-dimension steps of the slow dimensions
   constexpr int NT2 = (NP + 1) / 2;
   constexpr int R = 16 * NP;
@@ -418,7 +419,7 @@ __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, 
       float v = d[iq * M + M - 1];
 #pragma unroll
       for (int m = M - 2; m >= 0; --m) v = __builtin_fmaf(v, x, d[iq * M + m]);
-      sc[s][iq] = v;
+      sc[s][iq] = v * s_scale;
     }
   }
   // the scores are evaluated here (not after the next step's key loads, where they
@@ -443,6 +444,14 @@ __device__ __forceinline__ float reduce_lanes(float v, Op op) {
   if (N > 8) v = op(v, dpp<0x140>(v));           // row_mirror
   if (N > 16) v = op(v, __shfl_xor(v, 16));
   return v;
+}
+
+// the same over the wave, from the sums of its rows of 16
+__device__ __forceinline__ float wave_sum(float v) {
+  v = reduce_lanes<16>(v, [](float a, float b) { return a + b; });
+  auto row = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+  const float sum = (row(0) + row(16)) + (row(32) + row(48));
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(sum)));
 }
 
 // Chebyshev nodes cos(pi (k + 1/2) / 10), k < 5, and the weights of a function's values
@@ -507,6 +516,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   const int bk_row = lane / VPR, bk_vec = lane % VPR;
   const uint16_t* bk = p.bk + (int)info.bk_row * D;
   u4 bkv[kBkBatch];
+  float b_norm = 0.0f;                       // squares of the rows this wave loads
   auto load_bk = [&](int r0) {
 #pragma unroll
     for (int k = 0; k < kBkBatch; ++k) {
@@ -691,6 +701,11 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   uint8_t* low = frag;
   uint8_t* high = low + low_bytes;
   auto store_bk = [&](int r0) {
+#pragma unroll
+    for (int k = 0; k < kBkBatch; ++k)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        b_norm = __builtin_amdgcn_fdot2(as_h2(bkv[k][e]), as_h2(bkv[k][e]), b_norm, false);
     const int jj = 8 * (bk_vec % (VPR / 2)), up = bk_vec / (VPR / 2);   // pair, high half
     const int ks = ((jj - J0) >> 4) + up * (KS / 2), kc = bk_vec & 1;
     if (jj < J0) return;
@@ -755,22 +770,56 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
+  auto query = [&](int k, float* lo, float* hi) {   // the lane's pair of its query k
+    if (p.q_bf16) {
+      *lo = __uint_as_float(qr[k] << 16);
+      *hi = __uint_as_float(qr[k] & 0xFFFF0000u);
+    } else {
+      const h2 v = as_h2(qr[k]);
+      *lo = (float)v[0];
+      *hi = (float)v[1];
+    }
+  };
+  // A query row is scaled by a power of two that keeps its products within fp16: an
+  // element of W_m is at most 3 |q'| |B_k| (coefficients are below 2.98;
+  // the norms are those of the head's queries and of its B_k, whole), and an operand
+  // coef * q' at most 3 |q'|.  With the larger of the two at 2^13 .. 2^15, W_m neither
+  // overflows nor loses bits to subnormals wherever the key itself stays in fp16.  The
+  // scores are scaled back, which is exact.  (alpha_s is free until the loop's first
+  // barrier.)
+  float q_norm = 0.0f;
+  float* alpha_s = reinterpret_cast<float*>(smem + LL.alpha);
+  if (has) {
+#pragma unroll
+    for (int k = 0; k < QL; ++k) {
+      float lo, hi;
+      query(k, &lo, &hi);
+      q_norm = __builtin_fmaf(lo, lo, __builtin_fmaf(hi, hi, q_norm));
+    }
+    q_norm = wave_sum(q_norm);
+    b_norm = wave_sum(b_norm);
+    if (lane == 0) alpha_s[slot * TB + tb] = b_norm;
+  }
+  float q_scale = p.score_scale, s_scale = 1.0f;
+  auto set_scale = [&]() {
+    float bn = alpha_s[slot * TB];
+    if (TB > 1) bn += alpha_s[slot * TB + 1];
+    const float u2 = 9.0f * p.score_scale * p.score_scale * q_norm * fmaxf(bn, 1.0f);
+    // u2 < 2^(2x), at least a quarter of it; norms that are not finite scale nothing
+    const int e = u2 < INFINITY ? __builtin_amdgcn_frexp_expf(u2) : 30;
+    const int x = __builtin_amdgcn_readfirstlane(min(max((e + 1) >> 1, -60), 60));
+    q_scale = __int_as_float(__float_as_int(p.score_scale) + ((15 - x) << 23));   // times 2^(15 - x)
+    s_scale = __int_as_float((127 - 15 + x) << 23);
+  };
   auto store_q = [&]() {
     wave_sync();
-    const float c = rot.x * p.score_scale, n = rot.y * p.score_scale;
+    const float c = rot.x * q_scale, n = rot.y * q_scale;
 #pragma unroll
     for (int k = 0; k < QL; ++k) {
       const int i = qrow(k);
       if (i < G) {
         float lo, hi;
-        if (p.q_bf16) {
-          lo = __uint_as_float(qr[k] << 16);
-          hi = __uint_as_float(qr[k] & 0xFFFF0000u);
-        } else {
-          const h2 v = as_h2(qr[k]);
-          lo = (float)v[0];
-          hi = (float)v[1];
-        }
+        query(k, &lo, &hi);
         _Float16* d = reinterpret_cast<_Float16*>(qbase + i * QSB);
         d[qpos] = (_Float16)__builtin_fmaf(lo, c, hi * n);
         d[HALF + qpos] = (_Float16)__builtin_fmaf(hi, c, -(lo * n));
@@ -795,7 +844,6 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
 #pragma unroll
     for (int t = 0; t < NTW; ++t) acc_v[c][t] = (f4){0, 0, 0, 0};
   float* red = reinterpret_cast<float*>(smem + LL.red);       // [CT * 16][2]
-  float* alpha_s = reinterpret_cast<float*>(smem + LL.alpha);
   int* flag_s = reinterpret_cast<int*>(smem + LL.flag);       // [2][kWaves]
   // token u of the step held by the lane as its token s, and its place in the
   // probability operand: 32-token block u / 32, chunk u % 4, slot
@@ -825,7 +873,8 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     }
   };
   load_raw(0);
-  __syncthreads();   // operands, tables and zeroed probabilities visible
+  __syncthreads();   // operands, tables, norms and zeroed probabilities visible
+  if constexpr (has) set_scale();
   for (int step = 0; step < n_steps; ++step) {
     const int t_step = t_begin + step * kStepTokens;
     const bool full = t_step + kStepTokens <= t_end;
@@ -837,7 +886,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     bool any_over = false;
     if constexpr (has) {
       store_q();
-      poly_scores<D, QM, NHB, M, NS, NP>(W, raw, lane, G, x0, x);
+      poly_scores<D, QM, NHB, M, NS, NP>(W, raw, lane, G, x0, s_scale, x);
       load_raw(next);
       // a score's token (step and, below, its place among the lanes of a slot)
       // replaces the low 8 of its 24 significand bits, far below the score's
