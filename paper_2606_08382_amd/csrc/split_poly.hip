@@ -5,13 +5,24 @@
 //     cos(w_j d) (q'_j k_j + q'_j+h k_j+h) + sin(w_j d) (q'_j+h k_j - q'_j k_j+h),
 // with h = D/2, q' the query rotated back to the middle of the 128-token step and
 // d = -64 .. 63 the token's offset from it.  Only the first frequencies turn
-// far inside a step.  For the others cos and sin of w_j d are polynomials of
-// degree M - 1 in x = d/64 to fp16 accuracy (Chebyshev series, |w_j d| <= 2.4
-// for M = 8), so their part of the score is
-//     sum_m x^m (W_m . c),   W_m = sum_j coef_mj (B_k rows of j applied to q'),
+// far inside a step.  For the others cos and sin of w_j d are Chebyshev series of
+// degree M - 1 in x = d/64 (|w_j d| <= 2.44 for M = 8; what is cut off stays below
+// 2^-12), so their part of the score is
+//     sum_m T_m(x) (W_m . c),   W_m = sum_j coef_mj (B_k rows of j applied to q'),
 // with c the token's dequantized latent: the key is never rebuilt nor rotated
 // in those dimensions.  W_m (r channels) is formed once per step, head and query
-// with MFMA and serves 128 tokens.  The 16 NHB fastest pairs are rebuilt,
+// with MFMA and serves 128 tokens.
+//
+// Rounding: q', a coefficient, their product and W_m are fp16.  In the basis T_m a
+// coefficient is at most 1.17, so that the eight terms weigh no more than the one key of
+// the general kernel (in powers of x they reach 3 and cancel), and the largest one of a
+// pair is moved into q' before that is rounded, which leaves it exactly one.  Root mean
+// square error of scores against float64, relative to the general kernel's: 0.90 at
+// (d, theta) = (64, 700), (128, 700), 0.86 at (128, 5e5), 0.91 at (128, 1e4), at most 0.98
+// over any 16 tokens of a step; in powers of x, coefficients rounded as they are, 1.02 at
+// (64, 700) and up to 1.18 over the first tokens.
+//
+// The 16 NHB fastest pairs are rebuilt,
 // rotated and scored per token as the paper describes.
 //
 // Per 32 tokens and 16 channels this takes 1 + NHB matrix instructions
@@ -303,7 +314,7 @@ struct PolyWave {
   const uint8_t* high;     // B_k of the fast dimensions, [block][pair][half][row][8 channels]
   const uint8_t* q;        // the wave's query rows
   const uint8_t* zero;     // a row of zeros
-  const uint8_t* coef;     // polynomial coefficients
+  const uint8_t* coef;     // series coefficients
   const uint8_t* cs;       // rotations of the wave's tokens
 };
 
@@ -413,12 +424,19 @@ __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, 
       d = mfma32(qlo[b], __builtin_bit_cast(h8, kl), d);
       d = mfma32(qhi[b], __builtin_bit_cast(h8, kh), d);
     }
-    const float x = x0 + (float)s * (1.0f / 64.0f);
+    // T_m(x), formed for every token: kept across the step loop they would be spilled
+    float x = x0 + (float)s * (1.0f / 64.0f);
+    asm volatile("" : "+v"(x));
+    float T[M];
+    T[0] = 1.0f;
+    T[1] = x;
+#pragma unroll
+    for (int m = 2; m < M; ++m) T[m] = __builtin_fmaf(x + x, T[m - 1], -T[m - 2]);
 #pragma unroll
     for (int iq = 0; iq < 16 / M; ++iq) {
-      float v = d[iq * M + M - 1];
+      float v = d[iq * M];
 #pragma unroll
-      for (int m = M - 2; m >= 0; --m) v = __builtin_fmaf(v, x, d[iq * M + m]);
+      for (int m = 1; m < M; ++m) v = __builtin_fmaf(d[iq * M + m], T[m], v);
       sc[s][iq] = v * s_scale;
     }
   }
@@ -454,17 +472,16 @@ __device__ __forceinline__ float wave_sum(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(sum)));
 }
 
-// Chebyshev nodes cos(pi (k + 1/2) / 10), k < 5, and the weights of a function's values
-// there in the monomial coefficients of its series: 2 (2 - [i = 0]) / 10 sum_i cos(i th_k)
-// T_i's coefficient of x^m, i < M.
+// Chebyshev nodes cos th_k = cos(pi (k + 1/2) / 10), k < 5, and the weights of a function's
+// values there in its series: 2 (2 - [m = 0]) / 10 cos(m th_k) for T_m, m < M.
 __device__ constexpr float kNodes[5] = {0.987688341f, 0.891006524f, 0.707106781f, 0.4539905f,
                                         0.156434465f};
 __device__ constexpr float kWeights8[5][8] = {
-    {-0.0919299097f, -0.53109233f, 2.40404465f, 5.93814338f, -8.69662246f, -15.813291f, 7.52365123f, 11.6221568f},
-    {0.221701708f, 1.51999504f, -5.38852433f, -16.2170694f, 17.2714307f, 39.7229543f, -12.1735234f, -25.2848215f},
-    {-0.2f, -2.2627417f, 3.2f, 20.3646753f, -3.2f, -36.2038672f, 0.0f, 18.1019336f},
-    {-0.0689153034f, 2.34301927f, 7.3662331f, -3.73302358f, -19.2491395f, -2.48278063f, 12.1735234f, 4.00472231f},
-    {1.13914351f, 4.51639422f, -7.58175341f, -26.3417852f, 13.8743312f, 44.4425757f, -7.52365123f, -22.809767f}};
+    {0.2f, 0.395075336f, 0.380422607f, 0.35640261f, 0.323606798f, 0.282842712f, 0.235114101f, 0.1815962f},
+    {0.2f, 0.35640261f, 0.235114101f, 0.062573786f, -0.123606798f, -0.282842712f, -0.380422607f, -0.395075336f},
+    {0.2f, 0.282842712f, 2.4492936e-17f, -0.282842712f, -0.4f, -0.282842712f, -7.34788079e-17f, 0.282842712f},
+    {0.2f, 0.1815962f, -0.235114101f, -0.395075336f, -0.123606798f, 0.282842712f, 0.380422607f, 0.062573786f},
+    {0.2f, 0.062573786f, -0.380422607f, -0.1815962f, 0.323606798f, 0.282842712f, -0.235114101f, -0.35640261f}};
 
 // NHB: fast blocks of 16 RoPE pairs; M: polynomial terms; NS: tokens per lane;
 // CT: 16-query tiles; NTW: 16-channel value tiles per wave; MAXP: most pairs (of 8
@@ -644,23 +661,34 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   int* qmap = reinterpret_cast<int*>(smem + LL.qmap);         // query head of a probability row
   // turns per token of the lane's RoPE pair, theta^(-2j/D) / (2 pi)
   const double turn = 0.15915494309189533576888376337251 * exp2(-(2.0 * qj / D) * p.log2_theta);
-  // Polynomial coefficients of the slow pairs, [slow step][half of it][m][8 dims]: the
+  // Series coefficients of the slow pairs, [slow step][half of it][m][8 dims]: the
   // low dimensions of the pairs, then the high ones, whose odd terms are negated
-  // (q'_j k_j+h is subtracted).  Wave m forms x^m's: the Chebyshev series of cos (m
+  // (q'_j k_j+h is subtracted).  Wave m forms T_m's: the Chebyshev series of cos (m
   // even) or sin (m odd) of 64 w_j x, cut off at degree M - 1, by discrete
   // orthogonality over ten nodes (five of either sign: the weights are doubled;
-  // 64 w_j <= 2.44 leaves nothing the nodes cannot tell apart).
-  if (w < M && lane >= J0 && lane < HALF) {
-    const float a = 64.0f * (float)(6.283185307179586476925286766559 * turn);
-    float c = 0.0f;
+  // 64 w_j <= 2.44 leaves nothing the nodes cannot tell apart).  The largest, T_0's or
+  // T_1's there, scales the lane's pair of q' and divides the others.
+  float q_coef = 1.0f;
+  if (qj >= J0) {
+    const float a = (float)(128.0 * turn);   // 64 w_j in half turns
+    float c0 = 0.0f, c1 = 0.0f, c = 0.0f;
 #pragma unroll
-    for (int k = 0; k < 5; ++k)
-      c += kWeights8[k][w] *
-           (w & 1 ? sinf(a * kNodes[k]) : cosf(a * kNodes[k]));
-    const int j = lane - J0;
-    _Float16* dst = reinterpret_cast<_Float16*>(smem + LL.coef) + ((j >> 3) * M + w) * 8 + (j & 7);
-    dst[0] = (_Float16)c;
-    dst[KS / 2 * 2 * M * 8] = (_Float16)(w & 1 ? -c : c);
+    for (int k = 0; k < 5; ++k) {
+      float sn, cn;
+      sincospif(a * kNodes[k], &sn, &cn);
+      c0 += kWeights8[k][0] * cn;
+      c1 += kWeights8[k][1] * sn;
+      c += kWeights8[k][w] * (w & 1 ? sn : cn);
+    }
+    const int top = c1 > c0 ? 1 : 0;
+    q_coef = top ? c1 : c0;
+    c = w == top ? 1.0f : c / q_coef;
+    if (lane < HALF) {
+      const int j = lane - J0;
+      _Float16* dst = reinterpret_cast<_Float16*>(smem + LL.coef) + ((j >> 3) * M + w) * 8 + (j & 7);
+      dst[0] = (_Float16)c;
+      dst[KS / 2 * 2 * M * 8] = (_Float16)(w & 1 ? -c : c);
+    }
   }
   for (int i = tid; i < QSB / 2; i += kThreads) reinterpret_cast<uint16_t*>(zero)[i] = 0;
   // probability rows that no wave writes stay zero
@@ -759,6 +787,8 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     return make_float2(cn, sn);
   };
   float2 rot = rotation((double)(t_begin + 64));
+  rot.x *= q_coef;
+  rot.y *= q_coef;
   const float2 rot_step = rotation((double)kStepTokens);
 
   const PolyWave W = {frag, frag + low_bytes, qbase, zero, smem + LL.coef,
@@ -781,9 +811,10 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     }
   };
   // A query row is scaled by a power of two that keeps its products within fp16: an
-  // element of W_m is at most 3 |q'| |B_k| (coefficients are below 2.98;
+  // element of W_m is at most 1.2 |q'| |B_k| (the coefficients moved into q' are below 1.17,
+  // the others at most one;
   // the norms are those of the head's queries and of its B_k, whole), and an operand
-  // coef * q' at most 3 |q'|.  With the larger of the two at 2^13 .. 2^15, W_m neither
+  // coef * q' at most 1.2 |q'|.  With the larger of the two at 2^13 .. 2^15, W_m neither
   // overflows nor loses bits to subnormals wherever the key itself stays in fp16.  The
   // scores are scaled back, which is exact.  (alpha_s is free until the loop's first
   // barrier.)
@@ -804,7 +835,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   auto set_scale = [&]() {
     float bn = alpha_s[slot * TB];
     if (TB > 1) bn += alpha_s[slot * TB + 1];
-    const float u2 = 9.0f * p.score_scale * p.score_scale * q_norm * fmaxf(bn, 1.0f);
+    const float u2 = 1.44f * p.score_scale * p.score_scale * q_norm * fmaxf(bn, 1.0f);
     // u2 < 2^(2x), at least a quarter of it; norms that are not finite scale nothing
     const int e = u2 < INFINITY ? __builtin_amdgcn_frexp_expf(u2) : 30;
     const int x = __builtin_amdgcn_readfirstlane(min(max((e + 1) >> 1, -60), 60));
