@@ -696,10 +696,13 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     reinterpret_cast<u4*>(smem + LL.pbuf)[i] = (u4){0, 0, 0, 0};
   if (has && tb == 0 && lane < G) qmap[slot * G + lane] = info.head * G + lane;
   // Rotations of the fast pairs for the 128 token offsets of a step: vector
-  // (block, token range, s, cos | sin, half, lane), 8 frequencies each
+  // (block, token range, s, cos | sin, half, lane), 8 frequencies each.  With the angle
+  // reduced in fp64, what is left is the hardware sine's own error: 7e-8 root mean square
+  // at (d, theta) = (128, 5e5) and (64, 1e4), where the general kernel's tables have
+  // 4e-7 and 2.6e-7.
   if (w < NHB * 4) {
     const int s = w % NS, tr = w / NS % TB, blk = w / 4;
-    const float u = (float)(32 * NS * tr + NS * cl + s - 64);
+    const double u = (double)(32 * NS * tr + NS * cl + s - 64);
     u4 cv, sv;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -707,11 +710,10 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
         const int r = 2 * k + e;             // lane j holds pair j's turns
-        const float tj = __shfl((float)turn, 16 * blk + 8 * (r >> 2) + 4 * hf + (r & 3));
-        // at most 11 turns, known to 2^-20 of a turn: far below the fp16 rounding
-        const float a = __builtin_amdgcn_fractf(u * tj);
-        ss[e] = __builtin_amdgcn_sinf(a);
-        cc[e] = __builtin_amdgcn_cosf(a);
+        const double a = u * __shfl(turn, 16 * blk + 8 * (r >> 2) + 4 * hf + (r & 3));
+        const float f = (float)(a - floor(a));
+        ss[e] = __builtin_amdgcn_sinf(f);
+        cc[e] = __builtin_amdgcn_cosf(f);
       }
       cv[k] = as_u32(__builtin_convertvector((f2){cc[0], cc[1]}, h2));
       sv[k] = as_u32(__builtin_convertvector((f2){ss[0], ss[1]}, h2));
@@ -779,17 +781,20 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   uint32_t qr[QL];                           // (low, high) dimension of the lane's pair
 #pragma unroll
   for (int k = 0; k < QL; ++k) qr[k] = q_lo[k] | ((uint32_t)q_hi[k] << 16);
-  // angles in turns, reduced in fp64
-  auto rotation = [&](double t) {
+  // angles in turns, reduced in fp64; the base position's rotation is evaluated there, too
+  auto turns = [&](double t) {
     const double a = t * turn;
-    float sn, cn;
-    sincospif(2.0f * (float)(a - floor(a)), &sn, &cn);
-    return make_float2(cn, sn);
+    return 2.0 * (a - floor(a));
   };
-  float2 rot = rotation((double)(t_begin + 64));
+  float2 rot, rot_step;
+  {
+    double sn, cn;
+    sincospi(turns((double)(t_begin + 64)), &sn, &cn);
+    rot = make_float2((float)cn, (float)sn);
+    sincospif((float)turns((double)kStepTokens), &rot_step.y, &rot_step.x);
+  }
   rot.x *= q_coef;
   rot.y *= q_coef;
-  const float2 rot_step = rotation((double)kStepTokens);
 
   const PolyWave W = {frag, frag + low_bytes, qbase, zero, smem + LL.coef,
                       smem + LL.cs + tb * NS * 2048};
