@@ -189,7 +189,7 @@ starkv_status starkv_cache_layout(const starkv_plan* plan, starkv_layout* out);
  * partials and rescoring candidates for contexts up to max_ctx, the normalized
  * value latents that the absorbed output reads (the same size serves both
  * decode entry points), and the per-sequence work plan the split pass leaves
- * for the combine pass. */
+ * for the combine pass.  The size for max_ctx serves every call with a smaller one. */
 size_t        starkv_append_workspace_bytes(const starkv_plan* plan, int32_t n_new);
 size_t        starkv_decode_workspace_bytes(const starkv_plan* plan, int32_t max_ctx);
 
@@ -252,8 +252,8 @@ starkv_status starkv_decode_attn(const starkv_plan* plan, const void* cache, con
  * All calls on one device share that array and leave their partial results in
  * it: calls that overlap on one device (other streams, other threads) race and
  * must be ordered by the caller.
- * Errors: as starkv_decode_attn; WORKSPACE when starkv_decode_workspace_bytes(plan,
- * max_ctx) exceeds 32 MiB (the C3 layer shape needs 12.4 MiB at 4 x 131072 tokens
+ * Errors: as starkv_decode_attn; WORKSPACE when the call needs more than 32 MiB (at most
+ * starkv_decode_workspace_bytes(plan, max_ctx); the C3 layer shape needs 12.4 MiB at 4 x 131072 tokens
  * and 51.0 MiB at 64 x 131072). */
 starkv_status starkv_decode_attn_noalloc(const starkv_plan* plan, const void* cache,
                                          const void* q, const void* B_k, const void* B_v,

@@ -573,6 +573,16 @@ static WorkPlan work_plan(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
   return w;
 }
 
+// Splits per sequence of the equal split grid (batches the work plan does not serve):
+// enough to give every compute unit a workgroup and that none exceeds
+// kMaxSplitTokens, at most kMaxSplits (the combine pass merges up to that many)
+static int64_t grid_splits(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
+  const int64_t wgs_per_split = (int64_t)P->cfg.batch * n_hg;
+  const int64_t splits = std::max<int64_t>((kComputeUnits + wgs_per_split - 1) / wgs_per_split,
+                                           ((int64_t)max_ctx + kMaxSplitTokens - 1) / kMaxSplitTokens);
+  return std::min<int64_t>(splits, kMaxSplits);
+}
+
 static int32_t split_tokens(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
   const WorkPlan wp = work_plan(P, max_ctx, n_hg);
   if (wp.dyn) {
@@ -582,13 +592,7 @@ static int32_t split_tokens(const starkv_plan* P, int32_t max_ctx, int32_t n_hg)
       if (P->cfg.batch * ((steps + k - 1) / k) <= wp.cap) return k * kStepTokens;
     return kMaxSplitTokens;
   }
-  // enough splits to give every compute unit a workgroup, at most kMaxSplits
-  // per sequence (the combine pass merges up to that many)
-  const int64_t wgs_per_split = (int64_t)P->cfg.batch * n_hg;
-  int64_t splits = (kComputeUnits + wgs_per_split - 1) / wgs_per_split;
-  // and enough that no split exceeds kMaxSplitTokens
-  splits = std::max<int64_t>(splits, ((int64_t)max_ctx + kMaxSplitTokens - 1) / kMaxSplitTokens);
-  if (splits > kMaxSplits) splits = kMaxSplits;
+  const int64_t splits = grid_splits(P, max_ctx, n_hg);
   int64_t len = ((int64_t)max_ctx + splits - 1) / splits;
   len = (len + kStepTokens - 1) / kStepTokens * kStepTokens;
   if (len < kStepTokens) len = kStepTokens;
@@ -606,28 +610,40 @@ static int64_t part_slots(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
   return wp.dyn ? wp.cap : (int64_t)P->cfg.batch * ((max_ctx + (int64_t)len - 1) / len);
 }
 
-// Workspace: the split partials [items][H_q][part_stride] fp32, then the
-// rescoring candidates [items][H_q][kCand] (score, token) pairs.
-static int64_t cand_offset(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
-  return align256(part_slots(P, max_ctx, n_hg) * P->cfg.n_q_heads * part_stride(P) * 4);
+// Offsets in a workspace of that many slots.  The split partials [items][H_q][part_stride]
+// fp32, then the rescoring candidates [items][H_q][kCand] (score, token) pairs.
+static int64_t cand_bytes(const starkv_plan* P, int64_t slots) {
+  return align256(slots * P->cfg.n_q_heads * part_stride(P) * 4);
 }
 
 // Then, for the absorbed output, the normalized value latents as two fp16 parts
 // [2][B][H_q * r_v].
-static int64_t lat_offset(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
-  return cand_offset(P, max_ctx, n_hg) +
-         align256(part_slots(P, max_ctx, n_hg) * P->cfg.n_q_heads * kCand * 8);
+static int64_t lat_bytes(const starkv_plan* P, int64_t slots) {
+  return cand_bytes(P, slots) + align256(slots * P->cfg.n_q_heads * kCand * 8);
 }
 
 // Then the per-sequence work plan the split pass writes for the merge pass
 // [B] (first item, splits, length, 0).
-static int64_t plan_offset(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
-  return lat_offset(P, max_ctx, n_hg) +
+static int64_t plan_bytes(const starkv_plan* P, int64_t slots) {
+  return lat_bytes(P, slots) +
          align256((int64_t)2 * P->cfg.batch * P->cfg.n_q_heads * P->cfg.value_rank * 2);
 }
 
+static int64_t end_bytes(const starkv_plan* P, int64_t slots) {
+  return plan_bytes(P, slots) + align256((int64_t)16 * P->cfg.batch);
+}
+
+static int64_t cand_offset(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
+  return cand_bytes(P, part_slots(P, max_ctx, n_hg));
+}
+static int64_t lat_offset(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
+  return lat_bytes(P, part_slots(P, max_ctx, n_hg));
+}
+static int64_t plan_offset(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
+  return plan_bytes(P, part_slots(P, max_ctx, n_hg));
+}
 static int64_t workspace_bytes(const starkv_plan* P, int32_t max_ctx, int32_t n_hg) {
-  return plan_offset(P, max_ctx, n_hg) + align256((int64_t)16 * P->cfg.batch);
+  return end_bytes(P, part_slots(P, max_ctx, n_hg));
 }
 
 // Workgroups per work item that the work plan counts with: the split kernel's head
@@ -674,9 +690,20 @@ starkv_status starkv_decode_describe(const starkv_plan* P, int32_t max_ctx,
   return STARKV_OK;
 }
 
+// What a call with max_ctx needs, at most what starkv_decode_workspace_bytes reports.
+static size_t workspace_needed(const starkv_plan* P, int32_t max_ctx) {
+  return (size_t)workspace_bytes(P, max_ctx, plan_groups(P, max_ctx));
+}
+
+// Enough for every context up to max_ctx.  The equal split grid needs fewer slots for
+// some longer contexts (640 tokens in four splits: 256 tokens each, three splits; 512: four),
+// hence the splits it asks for, or one per step.
 size_t starkv_decode_workspace_bytes(const starkv_plan* P, int32_t max_ctx) {
   if (!P || max_ctx < 1) return 0;
-  return (size_t)workspace_bytes(P, max_ctx, plan_groups(P, max_ctx));
+  const int32_t n_hg = plan_groups(P, max_ctx);
+  if (work_plan(P, max_ctx, n_hg).dyn) return workspace_needed(P, max_ctx);
+  const int64_t steps = ((int64_t)max_ctx + kStepTokens - 1) / kStepTokens;
+  return (size_t)end_bytes(P, P->cfg.batch * std::min(grid_splits(P, max_ctx, n_hg), steps));
 }
 
 static starkv_status check_common(const starkv_plan* P, int32_t max_ctx, size_t ws_bytes,
@@ -687,7 +714,7 @@ static starkv_status check_common(const starkv_plan* P, int32_t max_ctx, size_t 
     return fail(STARKV_ERR_CAPACITY, "max_ctx %d > capacity %d", max_ctx, P->cfg.capacity);
   if (starkv_decode_split_tokens(P, max_ctx) > kMaxSplitTokens || max_ctx > kMaxCtx)
     return fail(STARKV_ERR_UNSUPPORTED, "max_ctx %d > %d", max_ctx, kMaxCtx);
-  const size_t need = starkv_decode_workspace_bytes(P, max_ctx);
+  const size_t need = workspace_needed(P, max_ctx);
   if (!ws || ws_bytes < need)
     return fail(STARKV_ERR_WORKSPACE, "decode workspace %zu bytes < %zu", ws_bytes, need);
   if (reinterpret_cast<uintptr_t>(ws) % 256) return fail(STARKV_ERR_ALIGNMENT, "ws not 256-byte aligned");
@@ -888,7 +915,7 @@ starkv_status starkv_decode_attn_noalloc(const starkv_plan* P, const void* cache
                                          starkv_stream_t stream) {
   if (!P) return fail(STARKV_ERR_INVALID_ARG, "plan is NULL");
   if (max_ctx < 1) return fail(STARKV_ERR_INVALID_ARG, "max_ctx %d < 1", max_ctx);
-  const size_t need = starkv_decode_workspace_bytes(P, max_ctx);
+  const size_t need = workspace_needed(P, max_ctx);
   if (need > kScratchBytes)
     return fail(STARKV_ERR_WORKSPACE, "decode needs %zu workspace bytes, more than the %zu of "
                 "the fixed scratch array", need, kScratchBytes);
