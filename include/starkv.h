@@ -319,9 +319,9 @@ int32_t       starkv_decode_splits(const starkv_plan* plan, int32_t max_ctx);
 int32_t       starkv_decode_split_tokens(const starkv_plan* plan, int32_t max_ctx);
 
 /* Shape of the decode launch a plan makes for max_ctx (informative, for tests and
- * measurement; no device work).  The split pass is one kernel instance per
- * (head_dim, qmode, score_tiles, value_tiles) and runs a grid of work items x
- * head_groups workgroups.  With device_plan != 0 (batches of up to 64 sequences)
+ * measurement; no device work).  The split pass is one of two kernels (see
+ * starkv_decode_fast_blocks) in an instance for the head_dim, qmode, score_tiles and
+ * value_tiles, and runs a grid of work items x head_groups workgroups.  With device_plan != 0 (batches of up to 64 sequences)
  * the kernels take the split length S = 128 k from the actual lengths L_b: the
  * smallest k >= k_lo with sum_b ceil(L_b / S) <= items; otherwise every sequence
  * has `items / batch` splits of split_tokens tokens.
@@ -338,6 +338,11 @@ typedef struct {
 } starkv_decode_info;
 starkv_status starkv_decode_describe(const starkv_plan* plan, int32_t max_ctx,
                                      starkv_decode_info* out);
+/* Which split kernel that launch is: 0 for the general one, which rebuilds and rotates
+ * every key whole, else the number of blocks of 16 RoPE pairs that the
+ * polynomial-rotation kernel rebuilds per token (1 or 2).  -1 for a NULL plan or
+ * max_ctx < 1. */
+int32_t       starkv_decode_fast_blocks(const starkv_plan* plan, int32_t max_ctx);
 
 /* starkv_read_stream -- a measurement aid, not part of the method: reads `bytes`
  * at src once with 16-byte loads (every lane keeps sixteen in flight, grid-stride

@@ -690,6 +690,11 @@ starkv_status starkv_decode_describe(const starkv_plan* P, int32_t max_ctx,
   return STARKV_OK;
 }
 
+int32_t starkv_decode_fast_blocks(const starkv_plan* P, int32_t max_ctx) {
+  if (!P || max_ctx < 1) return -1;
+  return P->poly ? P->poly_shape.nhb : 0;
+}
+
 // What a call with max_ctx needs, at most what starkv_decode_workspace_bytes reports.
 static size_t workspace_needed(const starkv_plan* P, int32_t max_ctx) {
   return (size_t)workspace_bytes(P, max_ctx, plan_groups(P, max_ctx));

@@ -65,7 +65,8 @@ EXPORTS = ["starkv_plan_create", "starkv_plan_destroy", "starkv_cache_bytes",
            "starkv_decode_split", "starkv_decode_combine", "starkv_decode_splits",
            "starkv_decode_split_tokens", "starkv_status_string", "starkv_last_error",
            "starkv_decode_attn_absorbed", "starkv_decode_combine_absorbed",
-           "starkv_decode_describe", "starkv_decode_attn_noalloc", "starkv_read_stream"]
+           "starkv_decode_describe", "starkv_decode_fast_blocks", "starkv_decode_attn_noalloc",
+           "starkv_read_stream"]
 
 _lib = None
 
@@ -112,6 +113,8 @@ def lib():
         L.starkv_decode_attn_noalloc.restype = C.c_int
         L.starkv_decode_describe.argtypes = [P, C.c_int32, C.POINTER(starkv_decode_info)]
         L.starkv_decode_describe.restype = C.c_int
+        L.starkv_decode_fast_blocks.argtypes = [P, C.c_int32]
+        L.starkv_decode_fast_blocks.restype = C.c_int32
         L.starkv_read_stream.argtypes = [P, S, C.c_int32, P, S, P]
         L.starkv_read_stream.restype = C.c_int
         L.starkv_status_string.argtypes = [C.c_int]
@@ -208,7 +211,13 @@ def starkv_decode_split_tokens(plan: Plan, max_ctx: int) -> int:
 def starkv_decode_describe(plan: Plan, max_ctx: int) -> dict:
     d = starkv_decode_info()
     _check(lib().starkv_decode_describe(plan.handle, max_ctx, C.byref(d)))
-    return {k: getattr(d, k) for k, _ in starkv_decode_info._fields_}
+    info = {k: getattr(d, k) for k, _ in starkv_decode_info._fields_}
+    info["fast_blocks"] = starkv_decode_fast_blocks(plan, max_ctx)
+    return info
+
+
+def starkv_decode_fast_blocks(plan: Plan, max_ctx: int) -> int:
+    return lib().starkv_decode_fast_blocks(plan.handle, max_ctx)
 
 
 def split_plan(info: dict, ctx_len) -> dict:
@@ -228,7 +237,9 @@ def split_plan(info: dict, ctx_len) -> dict:
         S = info["split_tokens"]
     items = sum(-(-L // S) for L in lens)
     return {"split_tokens": S, "steps_per_split": S // 128, "items": items,
-            "instance": f"<{info['head_dim']},{info['qmode']},{info['score_tiles']},"
+            "instance": ("general" if info["fast_blocks"] == 0 else
+                         f"polynomial, {info['fast_blocks']} fast blocks") +
+                        f" <{info['head_dim']},{info['qmode']},{info['score_tiles']},"
                         f"{info['value_tiles']}> x {info['head_groups']} head groups"}
 
 

@@ -21,6 +21,7 @@ def _decode(w, inp):
     from paper_2606_08382_amd.device import Layer, to_dev
     layer = Layer(w.batch, w.n_q_heads, w.n_kv_heads, w.head_dim, w.ctx, inp.key_rank, w.value_rank,
                   w.qmode, w.rope_theta, w.q_dtype, w.out_dtype)
+    assert S.starkv_decode_fast_blocks(layer.plan, w.ctx) == (1 if w.rope_theta >= 5e5 else 2)
     layer.append(to_dev(inp.latents), torch.zeros(w.batch, dtype=torch.int32, device="cuda"))
     layer.decode(*[to_dev(x) for x in (inp.q, inp.Bk, inp.Bv, inp.ctx_len)])
     torch.cuda.synchronize()
@@ -79,6 +80,7 @@ def _score_errors(d, theta, ranks, heads, q, Bk, lat, exact):
     qh = [g * G + i for g in heads for i in range(G)]
     layer = Layer(batch, len(qh), len(heads), d, n, [ranks[g] for g in heads], rv, F16, theta,
                   synth.DT_F16, synth.DT_F32)
+    assert (S.starkv_decode_fast_blocks(layer.plan, n) > 0) == (len(heads) > 2)
     z = np.concatenate([lat[..., cols], np.zeros((batch, n, rv))], axis=-1)
     layer.append(to_dev(synth.to_bits(z, synth.DT_F16)),
                  torch.zeros(batch, dtype=torch.int32, device="cuda"))
