@@ -62,6 +62,16 @@ constexpr int kMaxCtx = 64 * kMaxSplitTokens;   // longest context (524288 token
 
 }  // namespace
 
+// The polynomial-rotation split kernel for a plan's heads (ok: whether it applies).
+struct PolyPlan {
+  bool ok;
+  PolyShape shape;
+  int32_t n_hg, lds, frag_bytes;
+  int32_t most;                            // KV heads of the largest group
+  int32_t nql[kPolyMaxGroups];
+  PolyWaveInfo wave[kPolyMaxGroups][kWaves];
+};
+
 struct starkv_plan {
   starkv_config cfg;
   int32_t key_rank[STARKV_MAX_KV_HEADS];
@@ -81,12 +91,9 @@ struct starkv_plan {
   uint32_t o_code[STARKV_MAX_KV_HEADS], o_meta[STARKV_MAX_KV_HEADS];
   int32_t lds_bytes;
   RowMap rmap;            // cache rows (contiguous or paged)
-  // polynomial-rotation split kernel, where it applies (see plan_poly)
-  bool poly;
-  PolyShape poly_shape;
-  int32_t poly_n_hg, poly_lds, poly_frag_bytes;
-  int32_t poly_nql[kPolyMaxGroups];
-  PolyWaveInfo poly_wave[kPolyMaxGroups][kWaves];
+  // polynomial-rotation split kernel, where it applies (see plan_poly): head groups of up
+  // to eight KV heads, and of up to four where those are others (see poly_at)
+  PolyPlan poly, poly_short;
 };
 
 namespace {
@@ -104,11 +111,13 @@ namespace {
 // (a lane's prefetched codes), and at most two KV heads per workgroup, where a
 // wave per head leaves waves without key work (measured, one KV head: 4 of 8).
 //
-// Head groups: as few as fit the LDS, balanced by cost; a group of up to four heads
-// gives a head two waves of 64 tokens a step, a larger one a wave of 128.
-bool plan_poly(starkv_plan* P) {
+// Head groups: as few of at most max_heads heads as fit the LDS, balanced by cost; a group
+// of up to four heads gives a head two waves of 64 tokens a step, a larger one a wave of
+// 128.
+bool plan_poly(const starkv_plan* P, int max_heads, PolyPlan* R) {
   const starkv_config& c = P->cfg;
   const int D = c.head_dim, G = c.n_q_heads / c.n_kv_heads, n_kv = c.n_kv_heads;
+  R->ok = false;
   if (G > 4) return false;
   PolyShape s;
   s.m = 8;
@@ -126,7 +135,6 @@ bool plan_poly(starkv_plan* P) {
   const int ks = (D - 32 * s.nhb) / 16;
   auto frag_of = [&](int g) { return P->key_rank[g] * (32 * ks + 64 * s.nhb) + 32 * ks; };
   auto cost_of = [&](int g) { return 4 + P->key_rank[g] / 16; };
-  const int max_heads = 8;
   int by_cost[STARKV_MAX_KV_HEADS];
   for (int g = 0; g < n_kv; ++g) by_cost[g] = g;
   std::stable_sort(by_cost, by_cost + n_kv, [&](int x, int y) { return cost_of(x) > cost_of(y); });
@@ -153,18 +161,19 @@ bool plan_poly(starkv_plan* P) {
     s.ns = most > 4 ? 4 : 2;
     s.ct = s.ns == 4 ? 2 : 1;
     if (poly_lds_bytes(s, D, worst, P->layout.value_groups) <= kLdsLimit) {
-      P->poly_lds = poly_lds_bytes(s, D, worst, P->layout.value_groups);
+      R->lds = poly_lds_bytes(s, D, worst, P->layout.value_groups);
       break;
     }
   }
   if (n_hg > n_kv || n_hg > kPolyMaxGroups || most < 3) return false;
-  P->poly_n_hg = n_hg;
-  P->poly_frag_bytes = 0;
+  R->n_hg = n_hg;
+  R->most = most;
+  R->frag_bytes = 0;
   const int tb_n = 4 / s.ns;
-  std::memset(P->poly_nql, 0, sizeof(P->poly_nql));
-  std::memset(P->poly_wave, 0, sizeof(P->poly_wave));
+  std::memset(R->nql, 0, sizeof(R->nql));
+  std::memset(R->wave, 0, sizeof(R->wave));
   for (int h = 0; h < n_hg; ++h) {
-    P->poly_nql[h] = count[h] * G;
+    R->nql[h] = count[h] * G;
     PolyWaveInfo unit[kWaves];
     int frag = 0, n_units = 0;
     for (int i = 0; i < count[h]; ++i) {
@@ -187,15 +196,40 @@ bool plan_poly(starkv_plan* P) {
       }
       frag += frag_of(g);
     }
-    P->poly_frag_bytes = std::max(P->poly_frag_bytes, frag);
+    R->frag_bytes = std::max(R->frag_bytes, frag);
     // waves w and w + 4 share a SIMD: the costliest unit is paired with the cheapest
     for (int w = 0; w < kWaves; ++w) {
       const int u = w < 4 ? w : 11 - w;
-      if (u < n_units) P->poly_wave[h][w] = unit[u];
+      if (u < n_units) R->wave[h][w] = unit[u];
     }
   }
-  P->poly_shape = s;
+  R->shape = s;
+  R->ok = true;
   return true;
+}
+
+// The split kernel for contexts up to max_ctx: a form of the polynomial kernel, or the
+// general one (null).
+//
+// Groups of eight heads read the values once and leave half the workgroups of groups of
+// four, whose waves have half of a head's tokens.  With few steps the work items do not
+// fill the compute units, and a step's time counts: split pass at 8 heads, value rank
+// 256, 4/4 against 8 heads a group, 1 x 2K tokens 12.3 against 15.2 us (4-bit), 4 x 8K 16.8
+// against 17.5 (18.2 / 18.4 with 4/3 bits), 4 x 16K 22.5 / 21.7, 4 x 32K 33.0 / 29.3.  The line
+// is at one workgroup of eight heads per compute unit.  Two kinds of instance of the larger
+// groups are short of registers and have theirs elsewhere: 8/4-bit with two fast blocks
+// or ranks above 64 (4 x 16K 25.4 / 28.7 and 30.1 / 37.9, 4 x 32K 41.9 / 41.1) and fp16 with
+// two fast blocks (4 x 128K 132 / 150, 32 x 8K 65 / 81).
+const PolyPlan* poly_at(const starkv_plan* P, int32_t max_ctx) {
+  if (!P->poly.ok) return nullptr;
+  const starkv_config& c = P->cfg;
+  const PolyShape& s = P->poly.shape;
+  const int64_t steps = (int64_t)c.batch * (((int64_t)max_ctx + kStepTokens - 1) / kStepTokens);
+  if (P->poly_short.ok) {
+    const int64_t line = c.qmode == STARKV_Q_MIX8_4 && (s.nhb == 2 || s.maxp > 4) ? 2 * kComputeUnits : kComputeUnits;
+    if (steps * P->poly.n_hg <= line || (c.qmode == STARKV_Q_F16 && s.nhb == 2)) return &P->poly_short;
+  }
+  return &P->poly;
 }
 
 }  // namespace
@@ -530,7 +564,8 @@ starkv_status starkv_plan_create(const starkv_config* c, starkv_plan** out) {
     if (lds > P->lds_bytes) P->lds_bytes = lds;
   }
   for (int g = 0; g < c->n_kv_heads; ++g) P->bk_row[g] = info[g].bk_row;
-  P->poly = plan_poly(P);
+  P->poly_short.ok = false;
+  if (plan_poly(P, 8, &P->poly) && P->poly.most > 4) plan_poly(P, 4, &P->poly_short);
   *out = P;
   g_last_error.clear();
   return STARKV_OK;
@@ -652,11 +687,13 @@ static int64_t workspace_bytes(const starkv_plan* P, int32_t max_ctx, int32_t n_
 // of the no-allocation entry point and the general kernel's plan does not, the
 // items stay those of the general kernel's plan.
 static int32_t plan_groups(const starkv_plan* P, int32_t max_ctx) {
-  if (!P->poly || P->poly_n_hg >= P->n_hg) return P->poly ? P->poly_n_hg : P->n_hg;
+  const PolyPlan* poly = poly_at(P, max_ctx);
+  if (!poly) return P->n_hg;
+  if (poly->n_hg >= P->n_hg) return poly->n_hg;
   const int64_t limit = (int64_t)kScratchBytes;
-  if (workspace_bytes(P, max_ctx, P->poly_n_hg) > limit && workspace_bytes(P, max_ctx, P->n_hg) <= limit)
+  if (workspace_bytes(P, max_ctx, poly->n_hg) > limit && workspace_bytes(P, max_ctx, P->n_hg) <= limit)
     return P->n_hg;
-  return P->poly_n_hg;
+  return poly->n_hg;
 }
 
 int32_t starkv_decode_split_tokens(const starkv_plan* P, int32_t max_ctx) {
@@ -678,21 +715,23 @@ starkv_status starkv_decode_describe(const starkv_plan* P, int32_t max_ctx,
   starkv_decode_info d;
   d.head_dim = P->cfg.head_dim;
   d.qmode = P->cfg.qmode;
-  d.score_tiles = P->poly ? P->poly_shape.ct : P->ct;
-  d.value_tiles = P->poly ? P->poly_shape.ntw : P->ntw;
-  d.head_groups = P->poly ? P->poly_n_hg : P->n_hg;
+  const PolyPlan* poly = poly_at(P, max_ctx);
+  d.score_tiles = poly ? poly->shape.ct : P->ct;
+  d.value_tiles = poly ? poly->shape.ntw : P->ntw;
+  d.head_groups = poly ? poly->n_hg : P->n_hg;
   d.device_plan = wp.dyn ? 1 : 0;
   d.k_lo = wp.dyn ? wp.k_lo : 0;
   d.split_tokens = starkv_decode_split_tokens(P, max_ctx);
   d.items = wp.dyn ? wp.cap : P->cfg.batch * starkv_decode_splits(P, max_ctx);
-  d.lds_bytes = P->poly ? P->poly_lds : P->lds_bytes;
+  d.lds_bytes = poly ? poly->lds : P->lds_bytes;
   *out = d;
   return STARKV_OK;
 }
 
 int32_t starkv_decode_fast_blocks(const starkv_plan* P, int32_t max_ctx) {
   if (!P || max_ctx < 1) return -1;
-  return P->poly ? P->poly_shape.nhb : 0;
+  const PolyPlan* poly = poly_at(P, max_ctx);
+  return poly ? poly->shape.nhb : 0;
 }
 
 // What a call with max_ctx needs, at most what starkv_decode_workspace_bytes reports.
@@ -792,15 +831,15 @@ starkv_status starkv_decode_split(const starkv_plan* P, const void* cache, const
     p.v_row_bytes = P->layout.value_row_bytes;
     p.part_stride = part_stride(P);
   };
-  if (P->poly) {
+  if (const PolyPlan* poly = poly_at(P, max_ctx)) {
     PolyParams p;
     common(p);
     p.log2_theta = std::log2(c.rope_theta);
-    p.frag_bytes = P->poly_frag_bytes;
-    p.n_hg = P->poly_n_hg;
-    std::memcpy(p.nql, P->poly_nql, sizeof(p.nql));
-    std::memcpy(p.wave, P->poly_wave, sizeof(p.wave));
-    const int e = launch_decode_split_poly(p, P->poly_shape, c.head_dim, c.qmode, P->poly_lds,
+    p.frag_bytes = poly->frag_bytes;
+    p.n_hg = poly->n_hg;
+    std::memcpy(p.nql, poly->nql, sizeof(p.nql));
+    std::memcpy(p.wave, poly->wave, sizeof(p.wave));
+    const int e = launch_decode_split_poly(p, poly->shape, c.head_dim, c.qmode, poly->lds,
                                            static_cast<void*>(stream));
     return hip_status(e, "decode_split launch");
   }
