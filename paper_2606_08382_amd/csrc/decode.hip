@@ -1424,10 +1424,15 @@ __host__ __device__ constexpr int combine_bk_at(int rv, int rmax, int nw) {
 // first candidates are loaded before the merge, the fp64 angle is kept in turns (no range
 // reduction in the sine), the dot products of a wave's eight candidates are reduced
 // together (10 lane exchanges instead of 48), and the value sums take their token from
-// scalars instead of decoding block, chunk and slot per channel.  In traces: four waves
-// (32 ragged sequences, 1024 workgroups) 95.9 -> 38.1 us, sixteen waves 26.9 -> 19.8 (six
-// short contexts), 32.9 -> 21.4 (4 x 8K, absorbed), 40.0 -> 28.1 (4 x 128K, peaked),
-// 17.0 -> 14.2 (1 x 1K); without candidates 8.9 -> 9.3.
+// scalars instead of decoding block, chunk and slot per channel.
+//
+// Without candidates a call is a chain of short dependent steps, in which lane exchanges
+// through LDS (about 130 cycles each) and barriers count: the reductions of the split weights
+// and of the up-projection stay in the vector registers (DPP and row swaps), and up to
+// 64 splits, which are all in wave 0, take one barrier instead of three.  In traces, without
+// candidates: 4 x 128K tokens 9.7 -> 7.3 us, 1 x 2K 8.8 -> 6.9, 4 x 16K at value rank 384 8.7 -> 6.8;
+// with candidates 1 x 1K 12.4 -> 10.5, 8 x 4K 15.9 -> 12.4, 4 x 128K (peaked) 28.3 -> 26.6, 32 x 8K
+// (four waves, 1024 workgroups) 18.3 -> 17.8.
 template <int NW, int D>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
 void decode_combine_kernel(CombineParams p) {
@@ -1456,13 +1461,9 @@ void decode_combine_kernel(CombineParams p) {
   // rescoring are repeated by each of the col_split workgroups of the head)
   const int Dc = D / p.col_split, c_0 = blockIdx.z * Dc;
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // All kernel arguments at once (see CombineParams).
-#define SK_TOUCH(k) "s"(p.head[k].rank), "s"(p.head[(k) + 1].rank), "s"(p.head[(k) + 2].rank), "s"(p.head[(k) + 3].rank)
-  static_assert(STARKV_MAX_KV_HEADS == 16 && sizeof(CombineHead) <= 64, "a word of every line");
-  asm volatile("" :: SK_TOUCH(0), SK_TOUCH(4), SK_TOUCH(8), SK_TOUCH(12), "s"(p.part), "s"(p.bk),
-               "s"(p.q), "s"(p.ctx_len), "s"(p.lat), "s"(p.log2_theta), "s"(p.rmap.table),
-               "s"(p.n_q), "s"(p.part_stride), "s"(p.qmode), "s"(p.score_scale));
-#undef SK_TOUCH
+  // The scalar arguments at once (see CombineParams).
+  asm volatile("" :: "s"(p.part), "s"(p.bk), "s"(p.q), "s"(p.ctx_len), "s"(p.lat), "s"(p.log2_theta),
+               "s"(p.rmap.table), "s"(p.n_q), "s"(p.part_stride), "s"(p.qmode), "s"(p.score_scale));
   const int g = i / p.group_q;
   const CombineHead kh = p.head[g];
   // this sequence's splits: under the work plan, items first .. first + ns - 1
@@ -1551,20 +1552,24 @@ void decode_combine_kernel(CombineParams p) {
   float M, Lsum;
   bool any_cand;
   {                               // split weights: one split per thread (ns <= 256 <= NTH)
-    float m = mv0;
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    // up to 64 splits are all in wave 0, which then needs no other wave's maximum or sum
+    const bool one = ns <= 64;
+    float m = wave_max(mv0);
     if (lane == 0) wmax[w] = m;
-    __syncthreads();
-    m = wmax[0];
+    if (!one) {
+      __syncthreads();
+      m = wmax[0];
 #pragma unroll
-    for (int k = 1; k < 4; ++k) m = fmaxf(m, wmax[k]);   // splits live in the first four waves
+      for (int k = 1; k < 4; ++k) m = fmaxf(m, wmax[k]);   // splits live in the first four waves
+    }
     const float wv = tid < ns ? __builtin_amdgcn_exp2f(mv0 - m) : 0.0f;
     if (tid < kCombineMaxSplits) wts[tid] = wv;
-    float l = tid < ns ? wv * lv0 : 0.0f;
-    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
-    if (lane == 0) wsum[w] = l;
-    __syncthreads();
-    const float ls = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
+    float ls = wave_sum(tid < ns ? wv * lv0 : 0.0f);
+    if (lane == 0) wsum[w] = ls;
+    if (!one) {
+      __syncthreads();
+      ls = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
+    }
     // the candidate blocks of this split that may hold a token to rescore:
     // written by the split and bounded by 2^(m_s - M) q / L >= tau / 2
     uint32_t fl = 0;
@@ -1576,8 +1581,8 @@ void decode_combine_kernel(CombineParams p) {
     const bool fw = __ballot(fl != 0u) != 0;
     if (lane == 0) wfl[w] = fw ? 1 : 0;
     __syncthreads();
-    M = m;
-    Lsum = ls;
+    M = one ? wmax[0] : m;
+    Lsum = one ? wsum[0] : ls;
     any_cand = (wfl[0] | wfl[1] | wfl[2] | wfl[3]) != 0;
   }
   // The KV head's up-projection block B_k goes to LDS as fp16 pairs (j, j + D/2) before
@@ -1983,7 +1988,9 @@ void decode_combine_kernel(CombineParams p) {
   float* red = uni;                      // [NW][Dc]
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    for (int k = D8; k < 64; k <<= 1) o[e] += __shfl_xor(o[e], k);
+    if (D8 <= 4) o[e] += dpp<0x141>(dpp<0x1B>(o[e]));   // lane ^ 3, ^ 7
+    if (D8 <= 8) o[e] += dpp<0x128>(o[e]);              // row_ror:8
+    o[e] = sum_rows32(sum_rows16(o[e]));
     if (lane < D8) red[w * Dc + 8 * j8 + e] = o[e];
   }
   __syncthreads();

@@ -174,6 +174,47 @@ __device__ __forceinline__ uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel)
   return __builtin_amdgcn_perm(hi, lo, sel);
 }
 
+// Lane exchanges in the vector registers (__shfl goes through LDS, some 130 cycles).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
+                                                               0xF, 0xF, true));
+}
+// reductions over the lane's 8, 16 or 32 neighbours (a power-of-two group), to all of them
+template <int N, class Op>
+__device__ __forceinline__ float reduce_lanes(float v, Op op) {
+  v = op(v, dpp<0xB1>(v));                       // quad_perm 1,0,3,2
+  v = op(v, dpp<0x4E>(v));                       // quad_perm 2,3,0,1
+  v = op(v, dpp<0x141>(v));                      // row_half_mirror
+  if (N > 8) v = op(v, dpp<0x140>(v));           // row_mirror
+  if (N > 16) v = op(v, __shfl_xor(v, 16));
+  return v;
+}
+// the same over the wave, from the results of its rows of 16 (wave-uniform)
+template <class Op>
+__device__ __forceinline__ float reduce_wave(float v, Op op) {
+  v = reduce_lanes<16>(v, op);
+  auto row = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+  const float r = op(op(row(0), row(16)), op(row(32), row(48)));
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(r)));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  return reduce_wave(v, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ float wave_max(float v) {
+  return reduce_wave(v, [](float a, float b) { return fmaxf(a, b); });
+}
+// v plus the value of lane ^ 16, ^ 32 (all lanes active): the swap of a register with a copy
+// of itself leaves the two rows, or halves, in one register each
+__device__ __forceinline__ float sum_rows16(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float sum_rows32(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Raises a kernel's dynamic LDS limit to 160 KiB once per device: `done` holds
 // one bit per device index (indices past 63 set it on every launch).
 static inline int allow_lds(const void* fn, std::atomic<uint64_t>& done) {

@@ -448,30 +448,6 @@ __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, 
     for (int iq = 0; iq < 16 / M; ++iq) asm volatile("" : "+v"(sc[s][iq]));
 }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
-                                                               0xF, 0xF, true));
-}
-// reductions over the lane's 8, 16 or 32 neighbours (a power-of-two group), to all of them
-template <int N, class Op>
-__device__ __forceinline__ float reduce_lanes(float v, Op op) {
-  v = op(v, dpp<0xB1>(v));                       // quad_perm 1,0,3,2
-  v = op(v, dpp<0x4E>(v));                       // quad_perm 2,3,0,1
-  v = op(v, dpp<0x141>(v));                      // row_half_mirror
-  if (N > 8) v = op(v, dpp<0x140>(v));           // row_mirror
-  if (N > 16) v = op(v, __shfl_xor(v, 16));
-  return v;
-}
-
-// the same over the wave, from the sums of its rows of 16
-__device__ __forceinline__ float wave_sum(float v) {
-  v = reduce_lanes<16>(v, [](float a, float b) { return a + b; });
-  auto row = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
-  const float sum = (row(0) + row(16)) + (row(32) + row(48));
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(sum)));
-}
-
 // Chebyshev nodes cos th_k = cos(pi (k + 1/2) / 10), k < 5, and the weights of a function's
 // values there in its series: 2 (2 - [m = 0]) / 10 cos(m th_k) for T_m, m < M.
 __device__ constexpr float kNodes[5] = {0.987688341f, 0.891006524f, 0.707106781f, 0.4539905f,

@@ -154,8 +154,9 @@ struct CombineHead {
 };
 
 // Kernel arguments lie in host memory (see PolyParams): the combine kernel reads the
-// scalars and a word of every line of the head records at once at its start, then its
-// head's record.
+// scalars at once at its start, then its head's record, which is waited for where it is
+// used.  (With a word of every line of the records touched at the start calls took
+// 0.2 us more.)
 struct CombineParams {
   const float* part;
   const float2* cand;
