@@ -1392,7 +1392,7 @@ __device__ __forceinline__ void key_chunk(const CombineParams& p, const CombineH
 // [rmax][8 NW] with the B_k block behind them ([rmax][D/2] fp16 pairs j, j + D/2), its value
 // sums [NW][rv] and the up-projection's partial sums [NW][Dc].
 __host__ __device__ constexpr int combine_head_floats(int rv, int nw) {
-  return (rv + 2 * kCombineMaxSplits + 4 * kRescoreMax + kCandChunk + 4 * nw + 4 + 3 * nw + 3) / 4 * 4;
+  return (rv + 2 * kCombineMaxSplits + 4 * kRescoreMax + kCandChunk + 7 * nw + 3) / 4 * 4;
 }
 // B_k's place in the region: behind the split sums (it is loaded before they are read) and
 // the latents.  At the largest ranks (1024, 128) and sixteen waves the kernel holds 107 KB.
@@ -1451,8 +1451,7 @@ void decode_combine_kernel(CombineParams p) {
   int* c_b = c_t + kRescoreMax;          // [kRescoreMax] their 16-token cache blocks
   int* kcnt = c_b + kRescoreMax;         // [kCandChunk] entries per split
   int* lcnt = kcnt + kCandChunk;         // [4][NW] entries per threshold
-  float* misc = reinterpret_cast<float*>(lcnt + 4 * NW);
-  float* wmax = misc + 4;                // [NW] per-wave split maxima
+  float* wmax = reinterpret_cast<float*>(lcnt + 4 * NW);   // [NW] per-wave split maxima
   float* wsum = wmax + NW;               // [NW] per-wave weighted sums
   int* wfl = reinterpret_cast<int*>(wsum + NW);   // [NW] per-wave: a split flagged candidates
   float* uni = sm + combine_head_floats(p.rv, NW);

@@ -48,6 +48,9 @@
 
 namespace starkv {
 
+// terms of the series T_0 .. T_7; a 32-row matrix tile holds those of four queries
+constexpr int M = 8;
+
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u4a __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u2a __attribute__((ext_vector_type(2), aligned(4)));
@@ -66,13 +69,13 @@ struct PolyLds {
   static constexpr int kBlockPad = 64;
 };
 __host__ __device__ constexpr int poly_p_block(int ct) { return 4 * ct * 256 + PolyLds::kBlockPad; }
-__host__ __device__ constexpr PolyLds poly_lds(int D, int nhb, int m, int ct) {
+__host__ __device__ constexpr PolyLds poly_lds(int D, int nhb, int ct) {
   PolyLds L{};
   const int qs = (D + 8) * 2, ks = (D - 32 * nhb) / 16;
   L.q = 0;
-  L.zero = L.q + kWaves * (32 / m) * qs;
+  L.zero = L.q + kWaves * (32 / M) * qs;
   L.coef = L.zero + qs;
-  L.cs = L.coef + ks * 2 * m * 16;
+  L.cs = L.coef + ks * 2 * M * 16;
   L.red = L.cs + nhb * 8192;
   L.alpha = L.red + ct * 16 * 2 * 4;
   L.flag = L.alpha + ct * 16 * 4;
@@ -319,7 +322,7 @@ struct PolyWave {
 };
 
 // Scores of the wave's tokens: x[s][iq] for the lane's token s and query hf + 2 iq.
-template <int D, int QM, int NHB, int M, int NS, int NP>
+template <int D, int QM, int NHB, int NS, int NP>
 __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, NS, NP>& raw, int lane,
                                             int G, float x0, float s_scale,
                                             float (&sc)[NS][16 / M]) {
@@ -335,7 +338,6 @@ __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, 
   const uint8_t *qsrc_lo, *qsrc_hi, *qop, *coef, *cs;
   {
     // row (query i, term m) of the products with W_m
-    static_assert(M == 8, "four queries of eight terms per tile");
     const int m = 4 * ((cl >> 3) & 1) + (cl & 3);
     const int i = ((cl >> 2) & 1) + 2 * (cl >> 4);
     const uint8_t* row = (i < G ? W.q + i * ((D + 8) * 2) : W.zero) + 16 * hf;
@@ -459,11 +461,11 @@ __device__ constexpr float kWeights8[5][8] = {
     {0.2f, 0.1815962f, -0.235114101f, -0.395075336f, -0.123606798f, 0.282842712f, 0.380422607f, 0.062573786f},
     {0.2f, 0.062573786f, -0.380422607f, -0.1815962f, 0.323606798f, 0.282842712f, -0.235114101f, -0.35640261f}};
 
-// NHB: fast blocks of 16 RoPE pairs; M: polynomial terms; NS: tokens per lane;
+// NHB: fast blocks of 16 RoPE pairs; NS: tokens per lane;
 // CT: 16-query tiles; NTW: 16-channel value tiles per wave; MAXP: most pairs (of 8
 // channels) of a key head (heads of up to 64 channels have instances of their own, whose
 // registers the longer heads' loops do not crowd).
-template <int D, int QM, int NHB, int M, int NS, int CT, int NTW, int MAXP>
+template <int D, int QM, int NHB, int NS, int CT, int NTW, int MAXP>
 __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyParams p) {
   extern __shared__ __align__(16) uint8_t smem[];
   constexpr int HALF = D / 2;
@@ -492,7 +494,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   // Loads that need no work item are issued before the context lengths are waited
   // for: the head's B_k rows.
   const int l_ctx = p.dyn ? (lane < p.batch ? p.ctx_len[lane] : 0) : p.ctx_len[blockIdx.y];
-  constexpr PolyLds LL = poly_lds(D, NHB, M, CT);
+  constexpr PolyLds LL = poly_lds(D, NHB, CT);
   const int vmeta_bytes = poly_meta_bytes(p.v_ng);
   uint8_t* frag = smem + LL.meta + 2 * vmeta_bytes + info.frag;
   const int slot = info.slot, tb = info.tb;
@@ -597,23 +599,14 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   };
   // value meta of a step: loaded into registers a step ahead, written to LDS before
   // the step's barrier (a buffer per parity: the other one may still be read)
-  constexpr int MW = 1;
-  u4 vmr[MW];
+  u4 vmr;                                    // (one 16-byte vector per thread, see plan_poly)
   auto load_vmeta = [&](int step) {
     const uint8_t* src = p.cache + p.v_meta_off + (step_row(step) >> 5) * p.v_ng * 128;
-#pragma unroll
-    for (int k = 0; k < MW; ++k) {
-      const int o = (tid + k * kThreads) * 16;
-      if (o < vmeta_bytes) vmr[k] = load_at<u4>(src, (uint32_t)o);
-    }
+    if (tid * 16 < vmeta_bytes) vmr = load_at<u4>(src, (uint32_t)tid * 16);
   };
   auto store_vmeta = [&](int step) {
-    uint8_t* dst = smem + LL.meta + (step & 1) * vmeta_bytes;
-#pragma unroll
-    for (int k = 0; k < MW; ++k) {
-      const int o = (tid + k * kThreads) * 16;
-      if (o < vmeta_bytes) *reinterpret_cast<u4*>(dst + o) = vmr[k];
-    }
+    if (tid * 16 < vmeta_bytes)
+      *reinterpret_cast<u4*>(smem + LL.meta + (step & 1) * vmeta_bytes + tid * 16) = vmr;
   };
   if (QM != STARKV_Q_F16) load_vmeta(0);
   load_values(0);
@@ -898,7 +891,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     bool any_over = false;
     if constexpr (has) {
       store_q();
-      poly_scores<D, QM, NHB, M, NS, NP>(W, raw, lane, G, x0, s_scale, x);
+      poly_scores<D, QM, NHB, NS, NP>(W, raw, lane, G, x0, s_scale, x);
       load_raw(next);
       // a score's token (step and, below, its place among the lanes of a slot)
       // replaces the low 8 of its 24 significand bits, far below the score's
@@ -1197,9 +1190,9 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
 }
 
 // ------------------------------------------------------------------ launchers
-template <int D, int QM, int NHB, int M, int NS, int CT, int NTW, int MAXP>
+template <int D, int QM, int NHB, int NS, int CT, int NTW, int MAXP>
 static int launch_poly_t(const PolyParams& p, size_t lds, hipStream_t st) {
-  auto k = decode_split_poly_kernel<D, QM, NHB, M, NS, CT, NTW, MAXP>;
+  auto k = decode_split_poly_kernel<D, QM, NHB, NS, CT, NTW, MAXP>;
   static std::atomic<uint64_t> attr{0};
   if (const int e = allow_lds(reinterpret_cast<const void*>(k), attr)) return e;
   dim3 grid(p.dyn ? p.cap : p.n_split, p.dyn ? 1 : p.batch, p.n_hg);
@@ -1207,32 +1200,34 @@ static int launch_poly_t(const PolyParams& p, size_t lds, hipStream_t st) {
   return (int)hipGetLastError();
 }
 
-template <int D, int QM, int NHB, int M, int NS, int CT, int NTW>
+template <int D, int QM, int NHB, int NS, int CT, int NTW>
 static int dispatch_maxp(const PolyParams& p, int maxp, size_t lds, hipStream_t st) {
-  if (maxp <= 4) return launch_poly_t<D, QM, NHB, M, NS, CT, NTW, 4>(p, lds, st);
-  if constexpr (D == 128 && QM != STARKV_Q_F16) return launch_poly_t<D, QM, NHB, M, NS, CT, NTW, 8>(p, lds, st);
+  if (maxp <= 4) return launch_poly_t<D, QM, NHB, NS, CT, NTW, 4>(p, lds, st);
+  if constexpr (D == 128 && QM != STARKV_Q_F16) return launch_poly_t<D, QM, NHB, NS, CT, NTW, 8>(p, lds, st);
   return (int)hipErrorInvalidValue;
 }
 
-template <int D, int QM, int NHB, int M, int NS, int CT>
+template <int D, int QM, int NHB, int NS, int CT>
 static int dispatch_ntw(const PolyParams& p, const PolyShape& s, size_t lds, hipStream_t st) {
-  if (s.ntw == 2) return dispatch_maxp<D, QM, NHB, M, NS, CT, 2>(p, s.maxp, lds, st);
+  if (s.ntw == 2) return dispatch_maxp<D, QM, NHB, NS, CT, 2>(p, s.maxp, lds, st);
   if constexpr (QM != STARKV_Q_F16)
-    if (s.ntw == 3) return dispatch_maxp<D, QM, NHB, M, NS, CT, 3>(p, s.maxp, lds, st);
+    if (s.ntw == 3) return dispatch_maxp<D, QM, NHB, NS, CT, 3>(p, s.maxp, lds, st);
   return (int)hipErrorInvalidValue;
 }
 
 #define SK_CAT2(a, b) launch_poly_d##a##_q##b
 #define SK_NAME(a, b) SK_CAT2(a, b)
 int SK_NAME(SK_D, SK_QM)(const PolyParams& p, const PolyShape& s, size_t lds, hipStream_t st) {
-  if (s.m == 8 && s.nhb == 1) {
-    if (s.ns == 4 && s.ct == 2) return dispatch_ntw<SK_D, SK_QM, 1, 8, 4, 2>(p, s, lds, st);
-    if (s.ns == 2 && s.ct == 1) return dispatch_ntw<SK_D, SK_QM, 1, 8, 2, 1>(p, s, lds, st);
+  if (s.nhb == 1) {
+    if (s.ns == 4 && s.ct == 2) return dispatch_ntw<SK_D, SK_QM, 1, 4, 2>(p, s, lds, st);
+    if (s.ns == 2 && s.ct == 1) return dispatch_ntw<SK_D, SK_QM, 1, 2, 1>(p, s, lds, st);
   }
 #if SK_D == 128
-  if (s.m == 8 && s.nhb == 2) {
-    if (s.ns == 4 && s.ct == 2) return dispatch_ntw<SK_D, SK_QM, 2, 8, 4, 2>(p, s, lds, st);
-    if (s.ns == 2 && s.ct == 1) return dispatch_ntw<SK_D, SK_QM, 2, 8, 2, 1>(p, s, lds, st);
+  if (s.nhb == 2) {
+    // (fp16 caches with two fast blocks take groups of at most four heads)
+    if constexpr (SK_QM != STARKV_Q_F16)
+      if (s.ns == 4 && s.ct == 2) return dispatch_ntw<SK_D, SK_QM, 2, 4, 2>(p, s, lds, st);
+    if (s.ns == 2 && s.ct == 1) return dispatch_ntw<SK_D, SK_QM, 2, 2, 1>(p, s, lds, st);
   }
 #endif
   return (int)hipErrorInvalidValue;
@@ -1240,7 +1235,7 @@ int SK_NAME(SK_D, SK_QM)(const PolyParams& p, const PolyShape& s, size_t lds, hi
 #else
 
 int poly_lds_bytes(const PolyShape& s, int head_dim, int frag_bytes, int v_ng) {
-  return poly_lds(head_dim, s.nhb, s.m, s.ct).meta + 2 * poly_meta_bytes(v_ng) + frag_bytes;
+  return poly_lds(head_dim, s.nhb, s.ct).meta + 2 * poly_meta_bytes(v_ng) + frag_bytes;
 }
 
 #define SK_DECL(a, b) \

@@ -66,7 +66,7 @@ constexpr int kMaxCtx = 64 * kMaxSplitTokens;   // longest context (524288 token
 struct PolyPlan {
   bool ok;
   PolyShape shape;
-  int32_t n_hg, lds, frag_bytes;
+  int32_t n_hg, lds;
   int32_t most;                            // KV heads of the largest group
   int32_t nql[kPolyMaxGroups];
   PolyWaveInfo wave[kPolyMaxGroups][kWaves];
@@ -104,12 +104,16 @@ namespace {
 // first dropped Chebyshev term of the fastest frequency left to the polynomial,
 // 2 J_8(64 w_j), must stay below 2^-12, fp16's rounding of a value below one:
 // 64 w_j <= 2.44 (w_j = theta^(-2j/d); at theta = 5e5, d = 128: one fast block of 16
-// pairs).  The general kernel stays for more than four query heads per KV head (four
-// terms and two fast blocks would serve eight; measured at 64 query and 8 KV heads,
-// 2 x 64K tokens: first calls 164 us against 149, repeated ones no faster), rope bases whose frequencies are all fast, value ranks above
-// 512 (accumulators beyond the register file), fp16 caches of ranks above 64 or 256
-// (a lane's prefetched codes), and at most two KV heads per workgroup, where a
-// wave per head leaves waves without key work (measured, one KV head: 4 of 8).
+// pairs).  The general kernel stays for
+//   more than four query heads per KV head (four terms and two fast blocks would serve
+//     eight; measured at 64 query and 8 KV heads, 2 x 64K tokens: first calls 164 us
+//     against 149, repeated ones no faster),
+//   rope bases whose frequencies are all fast,
+//   value ranks above 384 (accumulators of more than three value tiles a wave beyond the
+//     register file) and, with fp16 caches, above 256 or key ranks above 64 (a lane's
+//     prefetched codes),
+//   and at most two KV heads per workgroup, where a wave per head leaves waves without
+//     key work (measured, one KV head: 4 of 8).
 //
 // Head groups: as few of at most max_heads heads as fit the LDS, balanced by cost; a group
 // of up to four heads gives a head two waves of 64 tokens a step, a larger one a wave of
@@ -120,7 +124,6 @@ bool plan_poly(const starkv_plan* P, int max_heads, PolyPlan* R) {
   R->ok = false;
   if (G > 4) return false;
   PolyShape s;
-  s.m = 8;
   for (s.nhb = 1; s.nhb <= 2; ++s.nhb)
     if (64.0 * std::pow(c.rope_theta, -2.0 * 16 * s.nhb / D) <= 2.44) break;
   if (s.nhb > 2 || 32 * s.nhb >= D) return false;
@@ -168,7 +171,6 @@ bool plan_poly(const starkv_plan* P, int max_heads, PolyPlan* R) {
   if (n_hg > n_kv || n_hg > kPolyMaxGroups || most < 3) return false;
   R->n_hg = n_hg;
   R->most = most;
-  R->frag_bytes = 0;
   const int tb_n = 4 / s.ns;
   std::memset(R->nql, 0, sizeof(R->nql));
   std::memset(R->wave, 0, sizeof(R->wave));
@@ -196,7 +198,6 @@ bool plan_poly(const starkv_plan* P, int max_heads, PolyPlan* R) {
       }
       frag += frag_of(g);
     }
-    R->frag_bytes = std::max(R->frag_bytes, frag);
     // waves w and w + 4 share a SIMD: the costliest unit is paired with the cheapest
     for (int w = 0; w < kWaves; ++w) {
       const int u = w < 4 ? w : 11 - w;
@@ -835,7 +836,6 @@ starkv_status starkv_decode_split(const starkv_plan* P, const void* cache, const
     PolyParams p;
     common(p);
     p.log2_theta = std::log2(c.rope_theta);
-    p.frag_bytes = poly->frag_bytes;
     p.n_hg = poly->n_hg;
     std::memcpy(p.nql, poly->nql, sizeof(p.nql));
     std::memcpy(p.wave, poly->wave, sizeof(p.wave));

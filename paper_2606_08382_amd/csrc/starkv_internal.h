@@ -97,7 +97,6 @@ struct DecodeParams {
   uint32_t o_code[STARKV_MAX_KV_HEADS], o_meta[STARKV_MAX_KV_HEADS];
 };
 
-constexpr int kPolyMaxDegree = 8;   // polynomial coefficients per RoPE frequency
 constexpr int kPolyMaxGroups = 6;   // head groups of the polynomial-rotation split kernel
 
 // A wave's work in the polynomial-rotation split kernel: one KV head and a token
@@ -135,7 +134,6 @@ struct PolyParams {
   int32_t q_bf16;
   int32_t rv, v_ro, v_ng8, v_ng, v_row_bytes;
   int32_t part_stride;
-  int32_t frag_bytes;          // LDS bytes of the up-projection operands (largest group)
   int32_t n_hg;
   int32_t nql[kPolyMaxGroups]; // query heads of each group
   alignas(64) PolyWaveInfo wave[kPolyMaxGroups][kWaves];
@@ -236,12 +234,11 @@ int split_lds_bytes(int frags, int nql, int head_dim, int ct, int raw_bytes, int
                     int v_row_bytes);
 int launch_decode_split_ntw(const DecodeParams& p, int head_dim, int qmode, int ct, int ntw,
                             size_t lds_bytes, void* stream);
-// Shape of a polynomial-rotation instance: high frequency blocks (16 RoPE pairs
-// each, rebuilt and rotated per token), polynomial terms of the others, tokens
-// per lane of a 128-token step, 16-query tiles, value tiles per wave, most pairs of
-// 8-channel chunks of a key head.
+// Shape of a polynomial-rotation instance: high frequency blocks (16 RoPE pairs each,
+// rebuilt and rotated per token), tokens per lane of a 128-token step, 16-query tiles,
+// value tiles per wave, most pairs of 8-channel chunks of a key head.
 struct PolyShape {
-  int32_t nhb, m, ns, ct, ntw, maxp;
+  int32_t nhb, ns, ct, ntw, maxp;
 };
 int poly_lds_bytes(const PolyShape& s, int head_dim, int frag_bytes, int v_ng);
 int launch_decode_split_poly(const PolyParams& p, const PolyShape& s, int head_dim, int qmode,
