@@ -30,7 +30,7 @@ MFMA_F16_PEAK_TFLOPS = 2500.0   # dense fp16 matrix peak
 COPY_BYTES = 256 << 20           # the plain device-to-device copy timed beside the path
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "decode_split_c3_traffic.json")
 SQ_SUMMARY = os.path.join(ROOT, "profiles", "decode_split_c3_sq_counters.json")
-SPLIT_SOURCE = os.path.join(ROOT, "paper_2606_08382_amd", "csrc", "decode.hip")
+SPLIT_SOURCE = os.path.join(ROOT, "paper_2606_08382_amd", "csrc", "split_poly.hip")   # the default workload's split kernel
 
 
 _DT_NAMES = {0: "f16", 1: "bf16", 2: "f32"}

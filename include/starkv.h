@@ -127,7 +127,9 @@ typedef struct starkv_plan starkv_plan;   /* opaque, immutable after creation */
  * are numbered outlier region first.  Per token and group: z = min over the
  * group's fp16 values, s = the smallest fp16 >= (max - min)/(2^b - 1) (s = 0 when
  * max == min), code = round-half-even((x - z)/s) clamped to [0, 2^b - 1]
- * (evaluated in fp64, which is exact for these operands); decode x-hat = z + code*s.
+ * (decided exactly, as in fp64 arithmetic); decode x-hat = z + code*s.  With an infinity
+ * in the group s is infinite and all codes 0; a NaN has code 0 and is left out of
+ * min and max.
  * Row bytes: F16 2r; INT4 r/2; MIX8_4 r_out + (r - r_out)/2; MIX4_3
  * r_out/2 + 3(r - r_out)/8.
  *
@@ -330,9 +332,12 @@ typedef struct {
   int32_t head_dim, qmode;
   int32_t score_tiles;       /* 16-column score tiles of a head group */
   int32_t value_tiles;       /* 16-channel value tiles per wave */
-  int32_t head_groups;       /* workgroups per work item (KV heads split by LDS size) */
+  int32_t head_groups;       /* workgroups per work item (KV heads split by LDS size and,
+                                for few tokens, to fill the compute units) */
   int32_t device_plan;       /* 1: split length chosen on the device from ctx_len */
-  int32_t k_lo, items;       /* device plan: smallest k, work items (grid.x) */
+  int32_t k_lo, items;       /* device plan: smallest k, work items (grid.x): one per
+                                compute unit and head group, fewer where the workspace
+                                would exceed the no-allocation scratch array */
   int32_t split_tokens;      /* split length for max_ctx in every sequence */
   int32_t lds_bytes;         /* dynamic LDS of a split workgroup */
 } starkv_decode_info;

@@ -28,8 +28,9 @@
 // Per 32 tokens and 16 channels this takes 1 + NHB matrix instructions
 // (32x32x16) instead of D/16 (16x16x32, half as long), and rotates 32 NHB of the D
 // dimensions: at d = 128, NHB = 1 the rotation and rebuilding fall to a quarter.
-// The vector ALUs, which bound the pass, then spend most of their time on
-// dequantization and softmax.
+// Counters of the 8/4-bit instance at 4 x 128K tokens (d = 128, NHB = 1): 53.6 vector
+// instructions a token (the general kernel 81.1), vector ALUs active in 63 % of the SIMD
+// cycles, matrix cores in 23 %, both at once in 11 %; waves wait 39 % of their time.
 //
 // Work: one workgroup of eight waves per (context split, sequence, group of KV
 // heads); a step covers 128 tokens.  A wave owns one KV head and all 128 tokens (NS = 4
