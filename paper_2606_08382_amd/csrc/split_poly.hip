@@ -5,30 +5,33 @@
 //     cos(w_j d) (q'_j k_j + q'_j+h k_j+h) + sin(w_j d) (q'_j+h k_j - q'_j k_j+h),
 // with h = D/2, q' the query rotated back to the middle of the 128-token step and
 // d = -64 .. 63 the token's offset from it.  Only the first frequencies turn
-// far inside a step.  For the others cos and sin of w_j d are Chebyshev series of
-// degree M - 1 in x = d/64 (|w_j d| <= 2.44 for M = 8; what is cut off stays below
-// 2^-12), so their part of the score is
-//     sum_m T_m(x) (W_m . c),   W_m = sum_j coef_mj (B_k rows of j applied to q'),
+// far inside a step.  For the others cos and sin of w_j d are polynomials of degree
+// M - 1 in x = d/64, the Chebyshev series cut off (|w_j d| <= 2.44 for M = 8; what is cut
+// off stays below 2^-12), written in b_m(x) = z^(m/2) for even m and x z^(m/2) (rounded
+// down) for odd ones, z = T_2(x) = 2 x^2 - 1.  Their part of the score is
+//     sum_m b_m(x) (W_m . c),   W_m = sum_j coef_mj (B_k rows of j applied to q'),
 // with c the token's dequantized latent: the key is never rebuilt nor rotated
 // in those dimensions.  W_m (r channels) is formed once per step, head and query
 // with MFMA and serves 128 tokens.
 //
-// Rounding: q', a coefficient, their product and W_m are fp16.  In the basis T_m a
-// coefficient is at most 1.17, so that the eight terms weigh no more than the one key of
+// Rounding: q', a coefficient, their product and W_m are fp16.  In these functions
+// coefficients stay below 1.45, so that the eight terms weigh hardly more than the one key of
 // the general kernel (in powers of x they reach 3 and cancel), and the largest one of a
 // pair is moved into q' before that is rounded, which leaves it exactly one.  Root mean
 // square error of scores against float64, relative to the general kernel's: 0.90 at
-// (d, theta) = (64, 700), (128, 700), 0.86 at (128, 5e5), 0.91 at (128, 1e4), at most 0.98
-// over any 16 tokens of a step; in powers of x, coefficients rounded as they are, 1.02 at
-// (64, 700) and up to 1.18 over the first tokens.
+// (d, theta) = (64, 700), 0.89 at (128, 700), 0.86 at (128, 5e5), 0.91 at (128, 1e4), at
+// most 0.98 over any 16 tokens of a step; in powers of x, coefficients rounded as they
+// are, 1.02 at (64, 700) and up to 1.18 over the first tokens.  The T_m themselves are as
+// exact, but their recurrence made the 8/4-bit pass over 4 x 128K tokens 84.9 us long,
+// two chains in z 81.4 us.
 //
-// The 16 NHB fastest pairs are rebuilt,
-// rotated and scored per token as the paper describes.
+// The 16 NHB fastest pairs are rebuilt, rotated and scored per token as the paper
+// describes.
 //
 // Per 32 tokens and 16 channels this takes 1 + NHB matrix instructions
 // (32x32x16) instead of D/16 (16x16x32, half as long), and rotates 32 NHB of the D
 // dimensions: at d = 128, NHB = 1 the rotation and rebuilding fall to a quarter.
-// Counters of the 8/4-bit instance at 4 x 128K tokens (d = 128, NHB = 1): 53.6 vector
+// Counters of the 8/4-bit instance at 4 x 128K tokens (d = 128, NHB = 1): 52.1 vector
 // instructions a token (the general kernel 81.1), vector ALUs active in 63 % of the SIMD
 // cycles, matrix cores in 23 %, both at once in 11 %; waves wait 39 % of their time.
 //
@@ -49,7 +52,7 @@
 
 namespace starkv {
 
-// terms of the series T_0 .. T_7; a 32-row matrix tile holds those of four queries
+// terms of a polynomial; a 32-row matrix tile holds those of four queries
 constexpr int M = 8;
 
 typedef float f16v __attribute__((ext_vector_type(16)));
@@ -325,8 +328,7 @@ struct PolyWave {
 // Scores of the wave's tokens: x[s][iq] for the lane's token s and query hf + 2 iq.
 template <int D, int QM, int NHB, int NS, int NP>
 __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, NS, NP>& raw, int lane,
-                                            int G, float x0, float s_scale,
-                                            float (&sc)[NS][16 / M]) {
+                                            int G, float x0, float (&sc)[NS][16 / M]) {
   constexpr int KS = (D - 32 * NHB) / 16;    // 16-dimension steps of the slow dimensions
   constexpr int NT2 = (NP + 1) / 2;
   constexpr int R = 16 * NP;
@@ -427,20 +429,18 @@ __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, 
       d = mfma32(qlo[b], __builtin_bit_cast(h8, kl), d);
       d = mfma32(qhi[b], __builtin_bit_cast(h8, kh), d);
     }
-    // T_m(x), formed for every token: kept across the step loop they would be spilled
     float x = x0 + (float)s * (1.0f / 64.0f);
     asm volatile("" : "+v"(x));
-    float T[M];
-    T[0] = 1.0f;
-    T[1] = x;
-#pragma unroll
-    for (int m = 2; m < M; ++m) T[m] = __builtin_fmaf(x + x, T[m - 1], -T[m - 2]);
+    const float z = __builtin_fmaf(x + x, x, -1.0f);
 #pragma unroll
     for (int iq = 0; iq < 16 / M; ++iq) {
-      float v = d[iq * M];
+      float even = d[iq * M + M - 2], odd = d[iq * M + M - 1];
 #pragma unroll
-      for (int m = 1; m < M; ++m) v = __builtin_fmaf(d[iq * M + m], T[m], v);
-      sc[s][iq] = v * s_scale;
+      for (int m = M - 4; m >= 0; m -= 2) {
+        even = __builtin_fmaf(even, z, d[iq * M + m]);
+        odd = __builtin_fmaf(odd, z, d[iq * M + m + 1]);
+      }
+      sc[s][iq] = __builtin_fmaf(odd, x, even);
     }
   }
   // the scores are evaluated here (not after the next step's key loads, where they
@@ -452,15 +452,17 @@ __device__ __forceinline__ void poly_scores(const PolyWave& W, const KeyRaw<QM, 
 }
 
 // Chebyshev nodes cos th_k = cos(pi (k + 1/2) / 10), k < 5, and the weights of a function's
-// values there in its series: 2 (2 - [m = 0]) / 10 cos(m th_k) for T_m, m < M.
+// values there in its coefficients of z^(m/2) and x z^(m/2), z = T_2(x): those of T_m in the
+// series, 2 (2 - [m = 0]) / 10 cos(m th_k), with T_2i = 1, z, 2 z^2 - 1, 4 z^3 - 3 z and
+// T_2i+1 / x = 1, 2 z - 1, 4 z^2 - 2 z - 1, 8 z^3 - 4 z^2 - 4 z + 1 collected by powers.
 __device__ constexpr float kNodes[5] = {0.987688341f, 0.891006524f, 0.707106781f, 0.4539905f,
                                         0.156434465f};
 __device__ constexpr float kWeights8[5][8] = {
-    {0.2f, 0.395075336f, 0.380422607f, 0.35640261f, 0.323606798f, 0.282842712f, 0.235114101f, 0.1815962f},
-    {0.2f, 0.35640261f, 0.235114101f, 0.062573786f, -0.123606798f, -0.282842712f, -0.380422607f, -0.395075336f},
-    {0.2f, 0.282842712f, 2.4492936e-17f, -0.282842712f, -0.4f, -0.282842712f, -7.34788079e-17f, 0.282842712f},
-    {0.2f, 0.1815962f, -0.235114101f, -0.395075336f, -0.123606798f, 0.282842712f, 0.380422607f, 0.062573786f},
-    {0.2f, 0.062573786f, -0.380422607f, -0.1815962f, 0.323606798f, 0.282842712f, -0.235114101f, -0.35640261f}};
+    {-0.123606798f, -0.062573786f, -0.324919696f, -0.579265005f, 0.647213595f, 0.40498605f, 0.940456404f, 1.4527696f},
+    {0.323606798f, 0.1815962f, 1.37638192f, 2.27113434f, -0.247213595f, 0.448930495f, -1.52169043f, -3.16060269f},
+    {0.6f, 1.13137085f, 0.0f, -1.13137085f, -0.8f, -2.2627417f, 0.0f, 2.2627417f},
+    {0.323606798f, 0.35640261f, -1.37638192f, -1.60613124f, -0.247213595f, 0.881075706f, 1.52169043f, 0.500590288f},
+    {-0.123606798f, -0.395075336f, 0.324919696f, 0.496732614f, 0.647213595f, 2.55698129f, -0.940456404f, -2.85122088f}};
 
 // NHB: fast blocks of 16 RoPE pairs; NS: tokens per lane;
 // CT: 16-query tiles; NTW: 16-channel value tiles per wave; MAXP: most pairs (of 8
@@ -633,11 +635,11 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
   const double turn = 0.15915494309189533576888376337251 * exp2(-(2.0 * qj / D) * p.log2_theta);
   // Series coefficients of the slow pairs, [slow step][half of it][m][8 dims]: the
   // low dimensions of the pairs, then the high ones, whose odd terms are negated
-  // (q'_j k_j+h is subtracted).  Wave m forms T_m's: the Chebyshev series of cos (m
+  // (q'_j k_j+h is subtracted).  Wave m forms b_m's: the Chebyshev series of cos (m
   // even) or sin (m odd) of 64 w_j x, cut off at degree M - 1, by discrete
   // orthogonality over ten nodes (five of either sign: the weights are doubled;
-  // 64 w_j <= 2.44 leaves nothing the nodes cannot tell apart).  The largest, T_0's or
-  // T_1's there, scales the lane's pair of q' and divides the others.
+  // 64 w_j <= 2.44 leaves nothing the nodes cannot tell apart).  The largest, b_0's or
+  // b_1's there, scales the lane's pair of q' and divides the others.
   float q_coef = 1.0f;
   if (qj >= J0) {
     const float a = (float)(128.0 * turn);   // 64 w_j in half turns
@@ -786,12 +788,12 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     }
   };
   // A query row is scaled by a power of two that keeps its products within fp16: an
-  // element of W_m is at most 1.2 |q'| |B_k| (the coefficients moved into q' are below 1.17,
-  // the others at most one;
-  // the norms are those of the head's queries and of its B_k, whole), and an operand
-  // coef * q' at most 1.2 |q'|.  With the larger of the two at 2^13 .. 2^15, W_m neither
+  // element of W_m is at most 1.5 |q'| |B_k| (the coefficients moved into q' are below 1.45,
+  // the others at most one; the norms are those of the head's queries and of its B_k, whole), and an operand
+  // coef * q' at most 1.5 |q'|.  With the larger of the two at 2^13 .. 2^15, W_m neither
   // overflows nor loses bits to subnormals wherever the key itself stays in fp16.  The
-  // scores are scaled back, which is exact.  (alpha_s is free until the loop's first
+  // scores stay scaled up to the softmax and the candidates, where a product with s_scale
+  // (a power of two, exact) replaces them.  (alpha_s is free until the loop's first
   // barrier.)
   float q_norm = 0.0f;
   float* alpha_s = reinterpret_cast<float*>(smem + LL.alpha);
@@ -806,16 +808,17 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     b_norm = wave_sum(b_norm);
     if (lane == 0) alpha_s[slot * TB + tb] = b_norm;
   }
-  float q_scale = p.score_scale, s_scale = 1.0f;
+  float q_scale = p.score_scale, s_scale = 1.0f, lazy = kLazyMargin;
   auto set_scale = [&]() {
     float bn = alpha_s[slot * TB];
     if (TB > 1) bn += alpha_s[slot * TB + 1];
-    const float u2 = 1.44f * p.score_scale * p.score_scale * q_norm * fmaxf(bn, 1.0f);
+    const float u2 = 2.25f * p.score_scale * p.score_scale * q_norm * fmaxf(bn, 1.0f);
     // u2 < 2^(2x), at least a quarter of it; norms that are not finite scale nothing
     const int e = u2 < INFINITY ? __builtin_amdgcn_frexp_expf(u2) : 30;
     const int x = __builtin_amdgcn_readfirstlane(min(max((e + 1) >> 1, -60), 60));
     q_scale = __int_as_float(__float_as_int(p.score_scale) + ((15 - x) << 23));   // times 2^(15 - x)
     s_scale = __int_as_float((127 - 15 + x) << 23);
+    lazy = __int_as_float(__float_as_int(kLazyMargin) + ((15 - x) << 23));
   };
   auto store_q = [&]() {
     wave_sync();
@@ -892,7 +895,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
     bool any_over = false;
     if constexpr (has) {
       store_q();
-      poly_scores<D, QM, NHB, NS, NP>(W, raw, lane, G, x0, s_scale, x);
+      poly_scores<D, QM, NHB, NS, NP>(W, raw, lane, G, x0, x);
       load_raw(next);
       // a score's token (step and, below, its place among the lanes of a slot)
       // replaces the low 8 of its 24 significand bits, far below the score's
@@ -930,7 +933,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
             b2[s][iq] = __builtin_amdgcn_fmed3f(b1[s][iq], b2[s][iq], v);   // b1 >= b2
             b1[s][iq] = fmaxf(b1[s][iq], v);
           }
-          over |= (ALL || hf + 2 * iq < G) && mx[iq] > m_run[iq] + kLazyMargin;
+          over |= (ALL || hf + 2 * iq < G) && mx[iq] > m_run[iq] + lazy;
         }
         any_over = __any(over);
         if (any_over) {
@@ -949,9 +952,10 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
           float l = 0.0f;
           if (ALL || hf + 2 * iq < G) {
             uint8_t* pr = pb + (row0 + hf + 2 * iq) * 16;
+            const float ms = m_run[iq] * s_scale;
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-              const float e = __builtin_amdgcn_exp2f(x[s][iq] - m_run[iq]);
+              const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x[s][iq], s_scale, -ms));
               l += e;
               *reinterpret_cast<_Float16*>(pr + p_off(s)) = (_Float16)e;
             }
@@ -976,13 +980,14 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
             float mn = m_run[iq];
 #pragma unroll
             for (int k = 0; k < TB; ++k) mn = fmaxf(mn, red[(row0 + i) * 2 + k]);
-            const float al = __builtin_amdgcn_exp2f(m_run[iq] - mn);   // m_run = -inf first: 0
+            const float ms = mn * s_scale;
+            const float al = __builtin_amdgcn_exp2f(__builtin_fmaf(m_run[iq], s_scale, -ms));   // m_run = -inf first: 0
             m_run[iq] = mn;
             uint8_t* pr = pb + (row0 + i) * 16;
             float l = 0.0f;
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-              const float e = __builtin_amdgcn_exp2f(x[s][iq] - mn);
+              const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x[s][iq], s_scale, -ms));
               l += e;
               *reinterpret_cast<_Float16*>(pr + p_off(s)) = (_Float16)e;
             }
@@ -1116,9 +1121,10 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
       const int row = row0 + (ok ? i : 0);
       const float lt = TB > 1 ? red[row * 2] + red[row * 2 + 1] : l_part[iq];
       const float bar = 0.5f * kRescoreTau * lt;
-      const float mr = m_run[iq];
+      const float mr = m_run[iq] * s_scale;
       auto bound = [&](float v) {
-        return v == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(v - mr) * (1.0f + fabsf(v));
+        const float u = v * s_scale;
+        return v == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(u - mr) * (1.0f + fabsf(u));
       };
       float qb = 0.0f;
 #pragma unroll
@@ -1159,7 +1165,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
           float2* e = cd + ((u & 3) * 2 + ((u >> 4) & 1)) * 2;
           auto entry = [&](float v) {
             const uint32_t k = __float_as_uint(v) & 0xFFu;
-            return make_float2(v, __int_as_float(t_begin + (int)(k >> 2) * kStepTokens +
+            return make_float2(v * s_scale, __int_as_float(t_begin + (int)(k >> 2) * kStepTokens +
                                                  4 * (int)(k & 3u) + (u & ~15) + (u & 3)));
           };
           e[0] = entry(b1[s][iq]);
@@ -1168,7 +1174,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_split_poly_kernel(PolyPara
       }
       if (ok && cl == 0 && tb == 0) {
         float* dst = p.part + qrow_out * p.part_stride + p.rv;
-        dst[0] = m_run[iq];
+        dst[0] = mr;
         dst[1] = lt;
       }
     }
